@@ -1,0 +1,55 @@
+// Fine levels evaluated per cell (kernels_cell.hpp): arguments and launchers.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "launch.hpp"
+
+namespace dgmg {
+
+// Constants of the operator on identical axis-aligned boxes: 1D tables on
+// [0,1] (Q = p + 1 Lobatto nodes, Q Gauss points) and the box geometry; D
+// points to the per-cell packed (scaled) conductivity.
+constexpr int kMfMaxQ = 5;
+template <typename T>
+struct MfConst {
+    T Ig[kMfMaxQ * kMfMaxQ];   // Ig[g*Q + j] = l_j(gauss_g)
+    T Gc[kMfMaxQ * kMfMaxQ];   // Gc[g*Q + h] = c_h'(gauss_g), c_h the Lagrange basis on the Gauss points
+    T M1[kMfMaxQ * kMfMaxQ];   // M1[i*Q + j] = int l_i l_j
+    T N1[kMfMaxQ * kMfMaxQ];   // N1[i*Q + j] = int l_i l_j'
+    T Ed[2 * kMfMaxQ];         // Ed[e*Q + j] = l_j'(e), e = 0, 1 (l_j(e) is 0 or 1: Lobatto ends)
+    T gw[kMfMaxQ];             // Gauss weights on [0,1]
+    T hinv[3];                 // 1 / h_k
+    T vol;                     // |K|
+    T area[3];                 // |F| of a face normal to axis k
+    T eta[3];                  // penalty factor of a face normal to axis k
+    T cM;                      // mass coefficient of A_0
+    const T* D;                // per cell: packed symmetric D (d(d+1)/2 values)
+};
+template <typename T>
+struct CellArgs {
+    const int32_t* __restrict__ up;        // [d][n] upper neighbour (itself if none)
+    const int32_t* __restrict__ lo;        // [d][n] lower neighbour (-1 if none)
+    const T* __restrict__ dinv;
+    int32_t n;
+    MfConst<T> mf;
+};
+
+// Workgroups of the cell kernels on a level of n cells with b x b blocks (the
+// number of partial sums they write).
+unsigned cell_groups(int b, int n);
+
+// The cell forms of k_apply, k_residual and k_cheb_step (same arguments).
+template <typename T>
+void cell_apply(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* va, T* y, const T* w, double* partial,
+                hipStream_t st);
+template <typename T>
+void cell_residual(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* va, const T* vb, const T* rhs, T* r,
+                   T* d, T c1, T* xout, double* partial, const T* P, T* rp, const int32_t* ptype, const T* bj,
+                   hipStream_t st);
+template <typename T>
+void cell_step(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* d, T* x, T* r, T* dn, T cd, T cr,
+               int assign, int last, const T* bj, hipStream_t st);
+
+}  // namespace dgmg

@@ -36,34 +36,9 @@
 
 #include <cstdint>
 
+#include "kernels_common.hpp"
+
 namespace dgmg {
-
-constexpr int kWG = 256;
-
-__device__ __forceinline__ int xcd_tile(int bid, int nblk) {
-    // bijective remap of [0, nblk): XCD x = bid % 8 gets tiles [x*q + min(x,r), ...)
-    const int x = bid & 7, k = bid >> 3;
-    const int q = nblk >> 3, r = nblk & 7;
-    return x * q + (x < r ? x : r) + k;
-}
-
-// Constants of the matrix-free fine level on identical axis-aligned boxes:
-// 1D tables on [0,1] (Q = p + 1 Lobatto nodes, Q Gauss points) and the box
-// geometry; D points to the per-cell packed (scaled) conductivity.
-constexpr int kMfMaxQ = 5;
-template <typename T>
-struct MfConst {
-    T Ig[kMfMaxQ * kMfMaxQ];   // Ig[g*Q + j] = l_j(gauss_g)
-    T Dg[kMfMaxQ * kMfMaxQ];   // Dg[g*Q + j] = l_j'(gauss_g)
-    T Ed[2 * kMfMaxQ];         // Ed[e*Q + j] = l_j'(e), e = 0, 1 (l_j(e) is 0 or 1: Lobatto ends)
-    T gw[kMfMaxQ];             // Gauss weights on [0,1]
-    T hinv[3];                 // 1 / h_k
-    T vol;                     // |K|
-    T area[3];                 // |F| of a face normal to axis k
-    T eta[3];                  // penalty factor of a face normal to axis k
-    T cM;                      // mass coefficient of A_0
-    const T* D;                // per cell: packed symmetric D (d(d+1)/2 values)
-};
 
 template <typename T>
 struct LevelArgs {
@@ -74,20 +49,7 @@ struct LevelArgs {
     int32_t n;
     const int32_t* __restrict__ up;        // axis-ELL: [d][n] upper neighbour (itself if none)
     const int32_t* __restrict__ lo;        // axis-ELL: [d][n] lower neighbour (-1 if none)
-    MfConst<T> mf;                         // matrix-free fine level (layout 2)
     const int32_t* __restrict__ cmap;      // tile-ELL: tile position -> cell (null: identity)
-};
-
-// spatial dimension of a block size (Q1..Q3 in 2D: 4, 9, 16; in 3D: 8, 27, 64)
-template <int B>
-constexpr int dim_of() {
-    return (B == 8 || B == 27 || B == 64) ? 3 : 2;
-}
-
-template <typename T, int B>
-struct Tile {
-    static constexpr int TC = kWG / B;   // cells per tile / workgroup
-    static constexpr int TR = TC * B;    // rows per tile
 };
 
 // Axis-ELL storage of a cell's diagonal block, which is symmetric: plane k
@@ -110,12 +72,6 @@ constexpr int ax_tile_planes(int b, int d) { return ax_cell_planes(b) + d * b; }
 // tangential index) and b - nF sparse planes (the other columns, ordered by
 // (tangential index, coordinate - 1); each holds only the nF rows on the
 // upper face: TC nF values, by cell slot then the row's tangential index).
-__host__ __device__ constexpr int ax_nodes_1d(int b, int d) { return d == 2 ? (b == 4 ? 2 : b == 9 ? 3 : b == 16 ? 4 : 5) : (b == 8 ? 2 : b == 27 ? 3 : 4); }
-// coordinate of node j along axis a, and its index among the nodes of a face normal to a
-__host__ __device__ constexpr int node_coord(int j, int a, int q) { return a == 0 ? j % q : a == 1 ? (j / q) % q : j / (q * q); }
-__host__ __device__ constexpr int node_tan(int j, int a, int q) {
-    return a == 0 ? (j / q) % q + q * (j / (q * q)) : a == 1 ? j % q + q * (j / (q * q)) : j % (q * q);
-}
 // values per axis and per tile of the sparse-face axis layout (tiles of tc cells)
 constexpr int64_t ax_sparse_axis_values(int b, int d, int tc) {
     return (int64_t)(b / ax_nodes_1d(b, d)) * tc * b + (int64_t)(b - b / ax_nodes_1d(b, d)) * tc * (b / ax_nodes_1d(b, d));
@@ -367,64 +323,33 @@ __device__ __forceinline__ T ax_row_apply(const LevelArgs<T>& L, int tile, int c
     return acc;
 }
 
-template <typename T, int B, bool VB>
-__device__ __forceinline__ T mf_row_apply(const LevelArgs<T>& L, int lc, int cell, bool active,
-                                          const T* __restrict__ va, const T* __restrict__ vb,
-                                          T** lds_free);
+// Operator layouts of a level: tile-ELL, axis-ELL, axis-ELL with sparse face
+// blocks (nodal fine levels, single column); LY_CELL levels evaluate the
+// operator per cell and have kernels of their own (kernels_cell.hpp).
+enum { LY_TILE = 0, LY_AXIS = 1, LY_CELL = 2, LY_AXS = 3 };
 
-// Operator layouts of a level: tile-ELL, axis-ELL, matrix-free boxes,
-// axis-ELL with sparse face blocks (nodal fine levels, single column).
-enum { LY_TILE = 0, LY_AXIS = 1, LY_MF = 2, LY_AXS = 3 };
-
-// (A (va + vb)) at the thread's row for layout LY.  The matrix-free product
-// synchronises the workgroup, so every thread calls this; rows of inactive
-// threads are not used.  When lds_free is given, the matrix-free product
-// stores there an LDS region of at least kWG values that no thread reads
-// any more (usable by the caller's epilogue without a further barrier).
-// ri is the thread's row within the tile (lc B + i), i its row of the cell.
+// (A (va + vb)) at the thread's row for layout LY; ri is the thread's row
+// within the tile (lc B + i), i its row of the cell.  A cell's lanes are all
+// active or all inactive, so the shuffles of an active cell read active
+// lanes only.
 template <typename T, int B, bool VB, int LY>
 __device__ __forceinline__ T row_apply(const LevelArgs<T>& L, int tile, int lc, int cell, int ri, int i,
-                                       bool active, const T* __restrict__ va, const T* __restrict__ vb,
-                                       T** lds_free = nullptr) {
-    if constexpr (LY == LY_MF) {
-        return mf_row_apply<T, B, VB>(L, lc, cell, active, va, vb, lds_free);
-    } else {
-        // a cell's lanes are all active or all inactive, so the shuffles of
-        // an active cell read active lanes only
-        if (!active) return T(0);
-        if constexpr (LY == LY_AXIS || LY == LY_AXS)
-            return ax_row_apply<T, B, VB, whole_wave_cells<B>(), LY == LY_AXS>(L, tile, cell, ri, i, va, vb);
-        else
-            return ell_row_apply<T, B, VB, whole_wave_cells<B>()>(L, tile, lc, ri, i, va, vb);
-    }
-}
-
-// Workgroup sum of a double into partial[blockIdx.x] (deterministic order).
-__device__ __forceinline__ void wg_sum_store(double v, double* partial) {
-    __shared__ double red[kWG / 64];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) red[w] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int k = 0; k < (int)(blockDim.x >> 6); ++k) s += red[k];
-        partial[blockIdx.x] = s;
-    }
+                                       bool active, const T* __restrict__ va, const T* __restrict__ vb) {
+    if (!active) return T(0);
+    if constexpr (LY == LY_AXIS || LY == LY_AXS)
+        return ax_row_apply<T, B, VB, whole_wave_cells<B>(), LY == LY_AXS>(L, tile, cell, ri, i, va, vb);
+    else
+        return ell_row_apply<T, B, VB, whole_wave_cells<B>()>(L, tile, lc, ri, i, va, vb);
 }
 
 // Cell-block Jacobi term of the smoother at the thread's row (i of `cell`):
 // z_i = sum_j (D_K^-1)_ij v_j over the cell's rows, with D_K^-1 symmetric and
 // row-major per cell (the lanes of a cell read consecutive words of column
-// j).  v is the workgroup's row values, staged in LDS here (the matrix-free
-// product passes its free region; the block layouts use their own), so every
-// thread of the workgroup must call this; inactive threads pass v = 0.
-template <typename T, int B, int LY>
+// j).  v is the workgroup's row values, staged in LDS here, so every thread of the workgroup must call this; inactive threads pass v = 0.
+template <typename T, int B>
 __device__ __forceinline__ T block_jacobi_row(const T* __restrict__ Dinv, T v, int lc, int cell, int ri,
-                                              int i, bool active, T* lds_free) {
-    __shared__ T vs_own[LY == LY_MF ? 1 : kWG];
-    T* vs = LY == LY_MF ? lds_free : vs_own;
+                                              int i, bool active) {
+    __shared__ T vs[kWG];
     if (ri < Tile<T, B>::TR) vs[ri] = v;
     __syncthreads();
     T z = 0;
@@ -457,7 +382,6 @@ __device__ __forceinline__ T block_jacobi_row(const T* __restrict__ Dinv, T v, i
     const bool active = lc < Tile<T, B>::TC && pos < L.n;                                      \
     const int cell = ((MAPPED) && L.cmap && active) ? L.cmap[pos] : pos;                       \
     const int t = cell * B + ti;
-#define DGMG_TILE_WW(B, LY) (whole_wave_cells<B>() && (LY) != LY_MF)
 #define DGMG_TILE_THREAD(T, B) DGMG_TILE_THREAD_M(T, B, false, false)
 
 // y = A va; optional partial of dot(w, y).
@@ -465,7 +389,7 @@ template <typename T, int B, int LY>
 __global__ __launch_bounds__(kWG) void k_apply(LevelArgs<T> L, const T* __restrict__ va,
                                                T* __restrict__ y,
                                                const T* __restrict__ w, double* __restrict__ partial) {
-    DGMG_TILE_THREAD_M(T, B, LY == LY_TILE, DGMG_TILE_WW(B, LY))
+    DGMG_TILE_THREAD_M(T, B, LY == LY_TILE, whole_wave_cells<B>())
     double contrib = 0.0;
     const T a = row_apply<T, B, false, LY>(L, tile, lc, cell, ri, ti, active, va, nullptr);
     if (active) {
@@ -488,16 +412,15 @@ __global__ __launch_bounds__(kWG) void k_residual(LevelArgs<T> L, const T* __res
                                                   const T* __restrict__ P, T* __restrict__ rp,
                                                   const int32_t* __restrict__ ptype,
                                                   const T* __restrict__ bj) {
-    DGMG_TILE_THREAD_M(T, B, LY == LY_TILE, DGMG_TILE_WW(B, LY))
+    DGMG_TILE_THREAD_M(T, B, LY == LY_TILE, whole_wave_cells<B>())
     double contrib = 0.0;
     T rr = 0;
-    T* lds_free = nullptr;
-    const T a = row_apply<T, B, VB, LY>(L, tile, lc, cell, ri, ti, active, va, vb, &lds_free);
+    const T a = row_apply<T, B, VB, LY>(L, tile, lc, cell, ri, ti, active, va, vb);
     if (active) rr = rhs[t] - a;
     // the block term stages the workgroup's residuals in LDS (uniform branch)
     T zb = 0;
     if constexpr (BJ) {
-        if (d) zb = block_jacobi_row<T, B, LY>(bj, rr, lc, cell, ri, ti, active, lds_free);
+        if (d) zb = block_jacobi_row<T, B>(bj, rr, lc, cell, ri, ti, active);
     }
     if (active) {
         if (r) r[t] = rr;
@@ -506,10 +429,7 @@ __global__ __launch_bounds__(kWG) void k_residual(LevelArgs<T> L, const T* __res
         contrib = (double)rr * (double)rr;
     }
     if (P) {
-        // the matrix-free product hands back a free LDS region (its own
-        // occupancy is LDS-bound); the block layouts use their own
-        __shared__ T rs_own[LY == LY_MF ? 1 : kWG];
-        T* rs = LY == LY_MF ? lds_free : rs_own;
+        __shared__ T rs[kWG];
         if (ri < Tile<T, B>::TR) rs[ri] = rr;
         __syncthreads();
         if (active) {
@@ -542,8 +462,7 @@ __global__ __launch_bounds__(kWG) void k_cheb_step(LevelArgs<T> L, const T* __re
                                                    T* __restrict__ x, T* __restrict__ r,
                                                    T* __restrict__ dn, T cd, T cr, int assign,
                                                    int last, const T* __restrict__ bj) {
-    DGMG_TILE_THREAD_M(T, B, LY == LY_TILE, DGMG_TILE_WW(B, LY))
-    T* lds_free = nullptr;
+    DGMG_TILE_THREAD_M(T, B, LY == LY_TILE, whole_wave_cells<B>())
     // FP32: the row's own operands are requested before the product, so that
     // their loads overlap its memory chain (FP64 keeps its register count;
     // for 3D Q1 blocks the three registers would cost a wave per SIMD)
@@ -554,13 +473,12 @@ __global__ __launch_bounds__(kWG) void k_cheb_step(LevelArgs<T> L, const T* __re
         if (!assign) x0 = x[t];
         if constexpr (!BJ) di = L.dinv[t];
     }
-    const T a = row_apply<T, B, false, LY>(L, tile, lc, cell, ri, ti, active, d, nullptr,
-                                           BJ ? &lds_free : nullptr);
+    const T a = row_apply<T, B, false, LY>(L, tile, lc, cell, ri, ti, active, d, nullptr);
     T rr = 0;
     if (active) rr = (EARLY ? r0 : r[t]) - a;
     // the block term stages the workgroup's residuals in LDS (all threads)
     T zb = 0;
-    if constexpr (BJ) zb = block_jacobi_row<T, B, LY>(bj, rr, lc, cell, ri, ti, active, lds_free);
+    if constexpr (BJ) zb = block_jacobi_row<T, B>(bj, rr, lc, cell, ri, ti, active);
     if (!active) return;
     const T dt = d[t];
     const T x1 = assign ? dt : (EARLY ? x0 : x[t]) + dt;

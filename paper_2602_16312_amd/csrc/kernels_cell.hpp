@@ -1,0 +1,691 @@
+// Matrix-free fine-level operator for meshes of identical axis-aligned boxes
+// (section 3: cell and interior-face terms of a_h and the mass term of eq.
+// fully_discrete, evaluated by sum factorisation instead of stored blocks).
+//
+// On a box of extents h the Q_p basis is a tensor product of 1D Lagrange
+// polynomials on Gauss-Lobatto nodes, the Gauss-Legendre rule with p+1 points
+// integrates every cell and face term exactly, and the only per-cell data is
+// the (scaled) conductivity D_K.
+//
+// Mapping: a workgroup takes 64 consecutive cells, one per lane, and has 1 + D
+// waves.  Wave 0 evaluates the cell terms, wave 1 + a both faces normal to
+// axis a, each lane with its cell's B values in registers: every 1D pass is
+// register arithmetic with wave-uniform (scalar register) table entries, so
+// there is no LDS traffic or barrier between passes.  Each wave leaves its
+// share of the B rows in LDS; after the only barrier the epilogue sums the
+// shares in wave order, a lane per row, with coalesced vector accesses.
+//   cell:  nodal values to the Gauss points by D 1D passes, gradients there by
+//          the collocation derivative G, the weighted fluxes, and the
+//          transposed passes;
+//   face:  the traces (Lobatto end layers) and normal derivatives of both
+//          sides; on a box the tangential integrals are the 1D matrices
+//          M_ij = int l_i l_j and N_ij = int l_i l_j', applied to
+//            q0 = -s/2 (k_a d_K + k_a^N d_N) + sigma (u_K - u_N),
+//            q_t = -s/2 (k_t u_K + k_t^N u_N),  jc = -s/2 (u_K - u_N),
+//          with k_c = D[a][c] / h_c and s = +1 on the cell's upper side.
+// Bound: FP32 arithmetic of one lane per cell (about 3,800 multiply-adds per
+// 3D Q2 cell, 140 per DoF) beside the vector streams; 64^3 Q2, FP32 Chebyshev
+// step: 46 us, 4.4 TB/s on its 202 MB (a thread per DoF with every pass through
+// LDS and eight barriers: 150 us, LDS busy 91%); FP64 130 us (286 us); 128^2 Q4
+// FP64 8.3 us (17.2 us); 16^3 Q3 FP64 8.3 us (18.0 us).
+// Included by cell.hip.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+#include <type_traits>
+
+#include "cell.hpp"
+#include "kernels_common.hpp"
+
+namespace dgmg {
+
+template <int D>
+constexpr int npack() {
+    return D * (D + 1) / 2;
+}
+// packed symmetric index of (a, b): 2D (xx, xy, yy); 3D (xx, xy, xz, yy, yz, zz)
+template <int D>
+constexpr int pk(int a, int b) {
+    const int lo = a < b ? a : b, hi = a < b ? b : a;
+    return D == 2 ? lo + hi : (lo == 0 ? hi : (lo == 1 ? 2 + hi : 5));
+}
+
+// threads per workgroup: a wave for the cell terms and one per axis
+template <int B>
+constexpr int cell_threads() {
+    return 64 * (1 + dim_of<B>());
+}
+template <typename T, int B, int NCELL>
+struct CellTile {
+    static constexpr int D = dim_of<B>(), Q = ax_nodes_1d(B, D), QN = B / Q;
+    static constexpr int NC = NCELL;                  // cells per workgroup, one per lane
+    static constexpr int NW = 1 + D;                  // waves: cell terms, faces of each axis
+    static constexpr int NT = cell_threads<B>();
+    static constexpr int SB = B | 1;                  // odd LDS stride of a cell's rows
+};
+
+// vector of 16 bytes at the alignment of its elements (a cell's values start
+// at a multiple of B elements)
+template <typename T>
+struct Vec16;
+template <>
+struct Vec16<float> {
+    typedef float type __attribute__((ext_vector_type(4), aligned(4)));
+};
+template <>
+struct Vec16<double> {
+    typedef double type __attribute__((ext_vector_type(2), aligned(8)));
+};
+
+// the B values of cell c of va (+ vb)
+template <typename T, int B, bool VB>
+__device__ __forceinline__ void load_cell(const T* __restrict__ va, const T* __restrict__ vb, int c, T* x) {
+    using V = typename Vec16<T>::type;
+    constexpr int W = 16 / sizeof(T);
+    const T* p = va + (size_t)c * B;
+#pragma unroll
+    for (int k = 0; k + W <= B; k += W) {
+        const V v = *reinterpret_cast<const V*>(p + k);
+#pragma unroll
+        for (int q = 0; q < W; ++q) x[k + q] = v[q];
+    }
+#pragma unroll
+    for (int k = B / W * W; k < B; ++k) x[k] = p[k];
+    if constexpr (VB) {
+        T y[B];
+        load_cell<T, B, false>(vb, nullptr, c, y);
+#pragma unroll
+        for (int k = 0; k < B; ++k) x[k] += y[k];
+    }
+}
+
+constexpr int ipow(int q, int e) { return e == 0 ? 1 : q * ipow(q, e - 1); }
+
+// u <- (1D matrix M along axis A of the Q^D array) u; TR: its transpose
+template <typename T, int Q, int D, int A, bool TR>
+__device__ __forceinline__ void line_pass(T* u, const T* M) {
+    constexpr int S = ipow(Q, A), N = ipow(Q, D);
+#pragma unroll
+    for (int k = 0; k < N / Q; ++k) {
+        const int base = (k / S) * S * Q + k % S;
+        T t[Q];
+#pragma unroll
+        for (int g = 0; g < Q; ++g) {
+            T s = 0;
+#pragma unroll
+            for (int j = 0; j < Q; ++j) s += (TR ? M[j * Q + g] : M[g * Q + j]) * u[base + j * S];
+            t[g] = s;
+        }
+#pragma unroll
+        for (int g = 0; g < Q; ++g) u[base + g * S] = t[g];
+    }
+}
+template <typename T, int Q, int D, bool TR>
+__device__ __forceinline__ void all_passes(T* u, const T* M) {
+    if constexpr (D > 0) line_pass<T, Q, D, 0, TR>(u, M);
+    if constexpr (D > 1) line_pass<T, Q, D, 1, TR>(u, M);
+    if constexpr (D > 2) line_pass<T, Q, D, 2, TR>(u, M);
+}
+
+// Cell terms of cell c: cM w u and the fluxes w D grad u, tested.
+template <typename T, int B, int NC, bool VB>
+__device__ __forceinline__ void cell_terms(const CellArgs<T>& L, int c, const T* __restrict__ va,
+                                           const T* __restrict__ vb, T* ys) {
+    using Ct = CellTile<T, B, NC>;
+    constexpr int D = Ct::D, Q = Ct::Q, NP = npack<D>();
+    const MfConst<T>& C = L.mf;
+    T u[B], y[B], Dk[NP];
+    load_cell<T, B, VB>(va, vb, c, u);
+#pragma unroll
+    for (int k = 0; k < NP; ++k) Dk[k] = C.D[(size_t)c * NP + k];
+#pragma unroll
+    for (int a = 0; a < D; ++a)
+#pragma unroll
+        for (int b = a; b < D; ++b) Dk[pk<D>(a, b)] *= C.vol * C.hinv[a] * C.hinv[b];
+    const T mass = C.vol * C.cM;
+    all_passes<T, Q, D, false>(u, C.Ig);
+#pragma unroll
+    for (int g = 0; g < B; ++g) y[g] = 0;
+#pragma unroll
+    for (int g = 0; g < B; ++g) {
+        const int gc[3] = {node_coord(g, 0, Q), node_coord(g, 1, Q), D == 3 ? node_coord(g, 2, Q) : 0};
+        const T w = D == 3 ? C.gw[gc[0]] * C.gw[gc[1]] * C.gw[gc[2]] : C.gw[gc[0]] * C.gw[gc[1]];
+        T gr[D];
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            T s = 0;
+#pragma unroll
+            for (int h = 0; h < Q; ++h) s += C.Gc[gc[a] * Q + h] * u[g + (h - gc[a]) * ipow(Q, a)];
+            gr[a] = s;
+        }
+        y[g] += w * mass * u[g];
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            T f = 0;
+#pragma unroll
+            for (int b = 0; b < D; ++b) f += Dk[pk<D>(a, b)] * gr[b];
+            f *= w;
+#pragma unroll
+            for (int h = 0; h < Q; ++h) y[g + (h - gc[a]) * ipow(Q, a)] += C.Gc[gc[a] * Q + h] * f;
+        }
+    }
+    all_passes<T, Q, D, true>(y, C.Ig);
+#pragma unroll
+    for (int i = 0; i < B; ++i) ys[i] = y[i];
+}
+
+// Both faces of cell c normal to axis A.
+template <typename T, int B, int NC, bool VB, int A>
+__device__ __forceinline__ void face_terms(const CellArgs<T>& L, int c, const T* __restrict__ va,
+                                           const T* __restrict__ vb, T* ys) {
+    using Ct = CellTile<T, B, NC>;
+    constexpr int D = Ct::D, Q = Ct::Q, QN = Ct::QN, NP = npack<D>();
+    constexpr int SA = ipow(Q, A);                        // stride of the normal direction
+    constexpr int t1 = A == 0 ? 1 : 0, t2 = D == 3 ? (A == 2 ? 1 : 2) : t1;
+    constexpr int S1 = ipow(Q, t1), S2 = D == 3 ? ipow(Q, t2) : 0;
+    const MfConst<T>& C = L.mf;
+    const int lo = L.lo[(size_t)A * L.n + c], up = L.up[(size_t)A * L.n + c];
+    const int nb[2] = {lo >= 0 ? lo : c, up};
+    const bool has[2] = {lo >= 0, up != c};
+    T xk[B], DK[D], DN[2][D];
+    load_cell<T, B, VB>(va, vb, c, xk);
+    const T daa = C.D[(size_t)c * NP + pk<D>(A, A)];
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        DK[k] = C.D[(size_t)c * NP + pk<D>(A, k)] * C.hinv[k];
+        DN[0][k] = C.D[(size_t)nb[0] * NP + pk<D>(A, k)] * C.hinv[k];
+        DN[1][k] = C.D[(size_t)nb[1] * NP + pk<D>(A, k)] * C.hinv[k];
+    }
+    T T0[2][QN], Tn[2][QN];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        T xn[B];
+        load_cell<T, B, VB>(va, vb, nb[s], xn);
+        const T ar = has[s] ? C.area[A] : T(0);
+        const T hs = (s ? T(-0.5) : T(0.5)) * ar;         // -s/2, area folded in
+        const T sig = C.eta[A] * T(0.5) * (daa + C.D[(size_t)nb[s] * NP + pk<D>(A, A)]) * ar;
+        T q0[QN], q1[QN], q2[QN], jc[QN];
+#pragma unroll
+        for (int m = 0; m < QN; ++m) {
+            const int J0 = (m % Q) * S1 + (m / Q) * S2;
+            T dK = 0, dN = 0;
+#pragma unroll
+            for (int j = 0; j < Q; ++j) {
+                dK += C.Ed[s * Q + j] * xk[J0 + j * SA];
+                dN += C.Ed[(1 - s) * Q + j] * xn[J0 + j * SA];
+            }
+            const T uK = xk[J0 + s * (Q - 1) * SA], uN = xn[J0 + (1 - s) * (Q - 1) * SA];
+            const T j = uK - uN;
+            q0[m] = hs * (DK[A] * dK + DN[s][A] * dN) + sig * j;
+            q1[m] = hs * (DK[t1] * uK + DN[s][t1] * uN);
+            q2[m] = D == 3 ? hs * (DK[t2] * uK + DN[s][t2] * uN) : T(0);
+            jc[m] = hs * j;
+        }
+        if constexpr (D == 2) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) {
+                T v = 0, n = 0, w = 0;
+#pragma unroll
+                for (int j = 0; j < Q; ++j) {
+                    v += C.M1[i * Q + j] * q0[j] + C.N1[i * Q + j] * q1[j];
+                    w += C.N1[j * Q + i] * jc[j];
+                    n += C.M1[i * Q + j] * jc[j];
+                }
+                T0[s][i] = v + DK[t1] * w;
+                Tn[s][i] = DK[A] * n;
+            }
+        } else {
+            // tangential direction t1, in place line by line: q0 <- M q0 + N q1
+            // + k1 N^T jc, q2 <- M q2, jc <- M jc; then t2
+#pragma unroll
+            for (int m2 = 0; m2 < Q; ++m2) {
+                T a[Q], b[Q], e[Q];
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    T v = 0, w = 0, x = 0, z = 0;
+#pragma unroll
+                    for (int j = 0; j < Q; ++j) {
+                        const int m = j + Q * m2;
+                        v += C.M1[i * Q + j] * q0[m] + C.N1[i * Q + j] * q1[m];
+                        w += C.N1[j * Q + i] * jc[m];
+                        x += C.M1[i * Q + j] * q2[m];
+                        z += C.M1[i * Q + j] * jc[m];
+                    }
+                    a[i] = v + DK[t1] * w;
+                    b[i] = x;
+                    e[i] = z;
+                }
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    q0[i + Q * m2] = a[i];
+                    q2[i + Q * m2] = b[i];
+                    jc[i + Q * m2] = e[i];
+                }
+            }
+#pragma unroll
+            for (int m1 = 0; m1 < Q; ++m1)
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    T v = 0, n = 0, w = 0;
+#pragma unroll
+                    for (int j = 0; j < Q; ++j) {
+                        const int m = m1 + Q * j;
+                        v += C.M1[i * Q + j] * q0[m] + C.N1[i * Q + j] * q2[m];
+                        w += C.N1[j * Q + i] * jc[m];
+                        n += C.M1[i * Q + j] * jc[m];
+                    }
+                    T0[s][m1 + Q * i] = v + DK[t2] * w;
+                    Tn[s][m1 + Q * i] = DK[A] * n;
+                }
+        }
+    }
+    // test functions: the trace at the two end layers, the end derivative on every layer
+#pragma unroll
+    for (int m = 0; m < QN; ++m) {
+        const int J0 = (m % Q) * S1 + (m / Q) * S2;
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            T v = C.Ed[j] * Tn[0][m] + C.Ed[Q + j] * Tn[1][m];
+            if (j == 0) v += T0[0][m];
+            if (j == Q - 1) v += T0[1][m];
+            ys[J0 + j * SA] = v;
+        }
+    }
+}
+
+// ---- 3D Q3 cells: four lanes per cell
+// A lane per cell would hold 64 values per array and issue 4,000 dependent
+// instructions (19 us on a single cell in FP64, more than the launch of a
+// whole small level).  Here lane l of a quad holds the 16 values with index l
+// along one axis, passes along that axis read the other three lanes through
+// DPP, and a wave takes 16 cells.
+template <int J>
+__device__ __forceinline__ float quad_lane(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), J * 0x55, 0xf, 0xf, true));
+}
+template <int J>
+__device__ __forceinline__ double quad_lane(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), J * 0x55, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), J * 0x55, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+// sum_j c[j] v(lane j of the quad)
+template <typename T>
+__device__ __forceinline__ T quad_dot(const T* c, T v) {
+    return c[0] * quad_lane<0>(v) + c[1] * quad_lane<1>(v) + c[2] * quad_lane<2>(v) + c[3] * quad_lane<3>(v);
+}
+template <typename T>
+__device__ __forceinline__ T quad_pick(const T* a, int stride, int l) {
+    return l == 0 ? a[0] : l == 1 ? a[stride] : l == 2 ? a[2 * stride] : a[3 * stride];
+}
+// row l of a 4 x 4 table, or column l
+template <typename T>
+__device__ __forceinline__ void quad_row(const T* M, int l, T* c) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) c[j] = quad_pick(M + j, 4, l);
+}
+template <typename T>
+__device__ __forceinline__ void quad_col(const T* M, int l, T* c) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) c[j] = quad_pick(M + 4 * j, 1, l);
+}
+
+template <typename T, bool VB>
+__device__ __forceinline__ void cell_terms_quad(const CellArgs<T>& L, int c, int l, const T* __restrict__ va,
+                                                const T* __restrict__ vb, T* ys) {
+    const MfConst<T>& C = L.mf;
+    T u[16], y[16], f2[16], Dk[6], cI[4], cG[4];
+    load_cell<T, 16, VB>(va, vb, c * 4 + l, u);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) Dk[k] = C.D[(size_t)c * 6 + k];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = a; b < 3; ++b) Dk[pk<3>(a, b)] *= C.vol * C.hinv[a] * C.hinv[b];
+    const T mass = C.vol * C.cM, wl = quad_pick(C.gw, 1, l);
+    all_passes<T, 4, 2, false>(u, C.Ig);
+    quad_row(C.Ig, l, cI);
+    quad_row(C.Gc, l, cG);
+#pragma unroll
+    for (int g = 0; g < 16; ++g) u[g] = quad_dot(cI, u[g]);
+#pragma unroll
+    for (int g = 0; g < 16; ++g) y[g] = 0;
+#pragma unroll
+    for (int g = 0; g < 16; ++g) {
+        const int g0 = g % 4, g1 = g / 4;
+        const T w = C.gw[g0] * C.gw[g1] * wl;
+        T gr[3] = {0, 0, quad_dot(cG, u[g])};
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            gr[0] += C.Gc[g0 * 4 + h] * u[h + 4 * g1];
+            gr[1] += C.Gc[g1 * 4 + h] * u[g0 + 4 * h];
+        }
+        T f[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) f[a] = w * (Dk[pk<3>(a, 0)] * gr[0] + Dk[pk<3>(a, 1)] * gr[1] + Dk[pk<3>(a, 2)] * gr[2]);
+        y[g] += w * mass * u[g];
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            y[h + 4 * g1] += C.Gc[g0 * 4 + h] * f[0];
+            y[g0 + 4 * h] += C.Gc[g1 * 4 + h] * f[1];
+        }
+        f2[g] = f[2];
+    }
+    quad_col(C.Ig, l, cI);
+    quad_col(C.Gc, l, cG);
+#pragma unroll
+    for (int g = 0; g < 16; ++g) {
+        y[g] += quad_dot(cG, f2[g]);
+        y[g] = quad_dot(cI, y[g]);
+    }
+    all_passes<T, 4, 2, true>(y, C.Ig);
+#pragma unroll
+    for (int g = 0; g < 16; ++g) ys[l * 16 + g] = y[g];
+}
+
+// Both faces normal to axis A; lane l holds the nodes with index l along the
+// second tangential axis.
+template <typename T, bool VB, int A>
+__device__ __forceinline__ void face_terms_quad(const CellArgs<T>& L, int c, int l, const T* __restrict__ va,
+                                                const T* __restrict__ vb, T* ys) {
+    constexpr int t1 = A == 0 ? 1 : 0, t2 = A == 2 ? 1 : 2;
+    constexpr int SA = ipow(4, A), S1 = ipow(4, t1), S2 = ipow(4, t2);
+    const MfConst<T>& C = L.mf;
+    const int lo = L.lo[(size_t)A * L.n + c], up = L.up[(size_t)A * L.n + c];
+    const int nb[2] = {lo >= 0 ? lo : c, up};
+    const bool has[2] = {lo >= 0, up != c};
+    // value (normal index j, first tangential index m) of a cell at x[at(j, m)]
+    auto at = [](int j, int m) { return A == 0 ? j + 4 * m : m + 4 * j; };
+    auto load = [&](int cell, T* x) {
+        if constexpr (A < 2) {
+            load_cell<T, 16, VB>(va, vb, cell * 4 + l, x);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) load_cell<T, 4, VB>(va, vb, cell * 16 + 4 * j + l, x + 4 * j);
+        }
+    };
+    T xk[16], DK[3], daa = C.D[(size_t)c * 6 + pk<3>(A, A)];
+    load(c, xk);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) DK[k] = C.D[(size_t)c * 6 + pk<3>(A, k)] * C.hinv[k];
+    T cM[4], cN[4], cT[4];
+    quad_row(C.M1, l, cM);
+    quad_row(C.N1, l, cN);
+    quad_col(C.N1, l, cT);
+    T T0[2][4], Tn[2][4];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        T xn[16], DN[3];
+        load(nb[s], xn);
+        const T dnn = C.D[(size_t)nb[s] * 6 + pk<3>(A, A)];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) DN[k] = C.D[(size_t)nb[s] * 6 + pk<3>(A, k)] * C.hinv[k];
+        const T ar = has[s] ? C.area[A] : T(0);
+        const T hs = (s ? T(-0.5) : T(0.5)) * ar;
+        const T sig = C.eta[A] * T(0.5) * (daa + dnn) * ar;
+        T q0[4], q1[4], q2[4], jc[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            T dK = 0, dN = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                dK += C.Ed[s * 4 + j] * xk[at(j, m)];
+                dN += C.Ed[(1 - s) * 4 + j] * xn[at(j, m)];
+            }
+            const T uK = xk[at(3 * s, m)], uN = xn[at(3 * (1 - s), m)], j = uK - uN;
+            q0[m] = hs * (DK[A] * dK + DN[A] * dN) + sig * j;
+            q1[m] = hs * (DK[t1] * uK + DN[t1] * uN);
+            q2[m] = hs * (DK[t2] * uK + DN[t2] * uN);
+            jc[m] = hs * j;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            T v = 0, w = 0, x = 0, z = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                v += C.M1[i * 4 + j] * q0[j] + C.N1[i * 4 + j] * q1[j];
+                w += C.N1[j * 4 + i] * jc[j];
+                x += C.M1[i * 4 + j] * q2[j];
+                z += C.M1[i * 4 + j] * jc[j];
+            }
+            v += DK[t1] * w;
+            T0[s][i] = quad_dot(cM, v) + quad_dot(cN, x) + DK[t2] * quad_dot(cT, z);
+            Tn[s][i] = DK[A] * quad_dot(cM, z);
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            T v = C.Ed[j] * Tn[0][m] + C.Ed[4 + j] * Tn[1][m];
+            if (j == 0) v += T0[0][m];
+            if (j == 3) v += T0[1][m];
+            ys[m * S1 + l * S2 + j * SA] = v;
+        }
+}
+
+// Evaluates the workgroup's shares: sh[w * NC * SB + cell * SB + row].  Lanes past
+// the last cell evaluate cell n - 1 and their rows are not read.  The caller
+// synchronises before it reads the shares.
+template <typename T, int B, int NC, bool VB>
+__device__ __forceinline__ void cell_product(const CellArgs<T>& L, int cell0, const T* __restrict__ va,
+                                             const T* __restrict__ vb, T* sh) {
+    using Ct = CellTile<T, B, NC>;
+    static_assert(NC <= (B == 64 ? 16 : 64), "cells of a workgroup do not fit a wave");
+    const int lane = (int)threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if constexpr (B == 64) {
+        const int c = min(cell0 + lane / 4, L.n - 1), l = lane & 3;
+        T* ys = sh + (w * Ct::NC + lane / 4) * Ct::SB;
+        if (w == 0) cell_terms_quad<T, VB>(L, c, l, va, vb, ys);
+        else if (w == 1) face_terms_quad<T, VB, 0>(L, c, l, va, vb, ys);
+        else if (w == 2) face_terms_quad<T, VB, 1>(L, c, l, va, vb, ys);
+        else face_terms_quad<T, VB, 2>(L, c, l, va, vb, ys);
+        return;
+    }
+    if (lane >= NC) return;
+    const int c = min(cell0 + lane, L.n - 1);
+    T* ys = sh + (w * Ct::NC + lane) * Ct::SB;
+    if (w == 0) cell_terms<T, B, NC, VB>(L, c, va, vb, ys);
+    else if (w == 1) face_terms<T, B, NC, VB, 0>(L, c, va, vb, ys);
+    else if (Ct::D == 2 || w == 2) face_terms<T, B, NC, VB, 1>(L, c, va, vb, ys);
+    else if constexpr (Ct::D == 3) face_terms<T, B, NC, VB, 2>(L, c, va, vb, ys);
+}
+// row k = cell * SB + i of the product
+template <typename T, int B, int NC>
+__device__ __forceinline__ T cell_row(const T* sh, int k) {
+    using Ct = CellTile<T, B, NC>;
+    T a = sh[k];
+#pragma unroll
+    for (int w = 1; w < Ct::NW; ++w) a += sh[w * Ct::NC * Ct::SB + k];
+    return a;
+}
+
+#define DGMG_CELL_GROUP(T, B)                                                        \
+    using Ct = CellTile<T, B, NC>;                                                       \
+    __shared__ T sh[Ct::NW * Ct::NC * Ct::SB];                                       \
+    const int cell0 = xcd_tile(blockIdx.x, gridDim.x) * Ct::NC;                      \
+    const int rows = min(Ct::NC, L.n - cell0) * B;                                   \
+    const size_t t0 = (size_t)cell0 * B;
+// The epilogue takes a row per lane, U rows of a thread at a time, whose
+// vector operands are requested together (the first ones before the barrier):
+// a loop that loaded row by row cost a memory latency per row, 7 of them on
+// 3D Q2 cells.
+template <int B, int NC>
+constexpr int cell_rows_at_once() {
+    constexpr int n = (NC * B + cell_threads<B>() - 1) / cell_threads<B>();
+    return n > 9 ? 8 : n;
+}
+#define DGMG_CELL_ROWS(B)                                                            \
+    constexpr int U = cell_rows_at_once<B, NC>(), NCH = (Ct::NC * B + U * Ct::NT - 1) / (U * Ct::NT); \
+    auto row = [&](int ch, int u) { return (int)threadIdx.x + (ch * U + u) * Ct::NT; };           \
+    auto at = [&](int e) { return e + (Ct::SB - B) * (e / B); };   // LDS index of row e
+
+// y = A va; optional partial of dot(w, y).
+template <typename T, int B, int NC>
+__global__ __launch_bounds__(cell_threads<B>()) void k_apply_cell(CellArgs<T> L, const T* __restrict__ va,
+                                                                  T* __restrict__ y, const T* __restrict__ w,
+                                                                  double* __restrict__ partial) {
+    DGMG_CELL_GROUP(T, B)
+    DGMG_CELL_ROWS(B)
+    cell_product<T, B, NC, false>(L, cell0, va, nullptr, sh);
+    T wv[U];
+    auto fetch = [&](int ch) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) wv[u] = w ? w[t0 + min(row(ch, u), rows - 1)] : T(0);
+    };
+    fetch(0);
+    __syncthreads();
+    double contrib = 0.0;
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+        if (ch) fetch(ch);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = row(ch, u);
+            if (e >= rows) continue;
+            const T a = cell_row<T, B, NC>(sh, at(e));
+            y[t0 + e] = a;
+            contrib += (double)wv[u] * (double)a;
+        }
+    }
+    if (partial) wg_sum_store(contrib, partial);
+}
+
+// Residual with the epilogues of k_residual.
+template <typename T, int B, int NC, bool VB, bool BJ>
+__global__ __launch_bounds__(cell_threads<B>()) void k_residual_cell(
+    CellArgs<T> L, const T* __restrict__ va, const T* __restrict__ vb, const T* __restrict__ rhs, T* __restrict__ r,
+    T* __restrict__ d, T c1, T* __restrict__ xout, double* __restrict__ partial, const T* __restrict__ P,
+    T* __restrict__ rp, const int32_t* __restrict__ ptype, const T* __restrict__ bj) {
+    DGMG_CELL_GROUP(T, B)
+    DGMG_CELL_ROWS(B)
+    cell_product<T, B, NC, VB>(L, cell0, va, vb, sh);
+    T bv[U], di[U];
+    auto fetch = [&](int ch) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const size_t t = t0 + min(row(ch, u), rows - 1);
+            bv[u] = rhs[t];
+            di[u] = d && !BJ ? L.dinv[t] : T(0);
+        }
+    };
+    fetch(0);
+    __syncthreads();
+    double contrib = 0.0;
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+        if (ch) fetch(ch);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = row(ch, u);
+            if (e >= rows) continue;
+            const size_t t = t0 + e;
+            const T rr = bv[u] - cell_row<T, B, NC>(sh, at(e));
+            if (r) r[t] = rr;
+            if (!BJ && d) d[t] = di[u] * rr * c1;
+            if (xout) xout[t] = VB ? va[t] + vb[t] : va[t];
+            contrib += (double)rr * (double)rr;
+            sh[at(e)] = rr;                           // a row's first share is read by its own thread only
+        }
+    }
+    if ((BJ && d) || P) {
+        __syncthreads();
+        for (int e = threadIdx.x; e < rows; e += Ct::NT) {
+            const size_t t = t0 + e;
+            const int lc = e / B, j = e - lc * B, cell = cell0 + lc;
+            const T* rc = sh + lc * Ct::SB;
+            if constexpr (BJ) {
+                if (d) {
+                    const T* Dc = bj + (size_t)cell * B * B + j;
+                    T z = 0;
+#pragma unroll
+                    for (int i = 0; i < B; ++i) z += Dc[(size_t)i * B] * rc[i];
+                    d[t] = c1 * z;
+                }
+            }
+            if (P) {
+                // column j of P_cell: a block of the type table (stride B) or
+                // the tile-interleaved block (contiguous)
+                constexpr int TC = Tile<T, B>::TC, TR = Tile<T, B>::TR;
+                const int ht = cell / TC, hl = cell - ht * TC;
+                const T* Pc = ptype ? P + (size_t)ptype[cell] * B * B + j : P + ((size_t)ht * B + j) * TR + hl * B;
+                const int ks = ptype ? B : 1;
+                T s = 0;
+#pragma unroll
+                for (int i = 0; i < B; ++i) s += Pc[i * ks] * rc[i];
+                rp[t] = s;
+            }
+        }
+    }
+    if (partial) wg_sum_store(contrib, partial);
+}
+
+// One inner Chebyshev step, as k_cheb_step.
+template <typename T, int B, int NC, bool BJ>
+__global__ __launch_bounds__(cell_threads<B>()) void k_cheb_step_cell(CellArgs<T> L, const T* __restrict__ d,
+                                                                      T* __restrict__ x, T* __restrict__ r,
+                                                                      T* __restrict__ dn, T cd, T cr, int assign,
+                                                                      int last, const T* __restrict__ bj) {
+    DGMG_CELL_GROUP(T, B)
+    DGMG_CELL_ROWS(B)
+    cell_product<T, B, NC, false>(L, cell0, d, nullptr, sh);
+    T rv[U], dv[U], xv[U], di[U];
+    auto fetch = [&](int ch) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const size_t t = t0 + min(row(ch, u), rows - 1);   // padded rows reread the last one
+            rv[u] = r[t];
+            dv[u] = d[t];
+            xv[u] = assign ? T(0) : x[t];
+            di[u] = BJ ? T(0) : L.dinv[t];
+        }
+    };
+    fetch(0);
+    __syncthreads();
+    if constexpr (BJ) {
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch) {
+            if (ch) fetch(ch);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int e = row(ch, u);
+                if (e >= rows) continue;
+                const T rr = rv[u] - cell_row<T, B, NC>(sh, at(e));
+                if (!last) r[t0 + e] = rr;
+                sh[at(e)] = rr;                       // a row's first share is read by its own thread only
+            }
+        }
+        __syncthreads();
+        if (NCH > 1) fetch(0);
+    }
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+        if (ch) fetch(ch);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = row(ch, u);
+            if (e >= rows) continue;
+            const size_t t = t0 + e;
+            T z;
+            if constexpr (BJ) {
+                const int lc = e / B;
+                const T* Dc = bj + (size_t)(cell0 + lc) * B * B + (e - lc * B);
+                const T* rc = sh + lc * Ct::SB;
+                z = 0;
+#pragma unroll
+                for (int i = 0; i < B; ++i) z += Dc[(size_t)i * B] * rc[i];
+            } else {
+                const T rr = rv[u] - cell_row<T, B, NC>(sh, at(e));
+                if (!last) r[t] = rr;
+                z = di[u] * rr;
+            }
+            const T x1 = assign ? dv[u] : xv[u] + dv[u];
+            const T dnew = cd * dv[u] + cr * z;
+            x[t] = last ? x1 + dnew : x1;
+            if (!last) dn[t] = dnew;
+        }
+    }
+}
+
+}  // namespace dgmg

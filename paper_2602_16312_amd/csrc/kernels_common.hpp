@@ -1,0 +1,54 @@
+// Block sizes, tiles, node indices and the workgroup sum shared by the device
+// kernels.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+namespace dgmg {
+
+constexpr int kWG = 256;
+
+__device__ __forceinline__ int xcd_tile(int bid, int nblk) {
+    // bijective remap of [0, nblk): XCD x = bid % 8 gets tiles [x*q + min(x,r), ...)
+    const int x = bid & 7, k = bid >> 3;
+    const int q = nblk >> 3, r = nblk & 7;
+    return x * q + (x < r ? x : r) + k;
+}
+
+// spatial dimension of a block size (Q1..Q3 in 2D: 4, 9, 16; in 3D: 8, 27, 64)
+template <int B>
+constexpr int dim_of() {
+    return (B == 8 || B == 27 || B == 64) ? 3 : 2;
+}
+
+template <typename T, int B>
+struct Tile {
+    static constexpr int TC = kWG / B;   // cells per tile / workgroup
+    static constexpr int TR = TC * B;    // rows per tile
+};
+
+// Nodes per axis of a block size.
+__host__ __device__ constexpr int ax_nodes_1d(int b, int d) { return d == 2 ? (b == 4 ? 2 : b == 9 ? 3 : b == 16 ? 4 : 5) : (b == 8 ? 2 : b == 27 ? 3 : 4); }
+// coordinate of node j along axis a, and its index among the nodes of a face normal to a
+__host__ __device__ constexpr int node_coord(int j, int a, int q) { return a == 0 ? j % q : a == 1 ? (j / q) % q : j / (q * q); }
+__host__ __device__ constexpr int node_tan(int j, int a, int q) {
+    return a == 0 ? (j / q) % q + q * (j / (q * q)) : a == 1 ? j % q + q * (j / (q * q)) : j % (q * q);
+}
+
+// Workgroup sum of a double into partial[blockIdx.x] (deterministic order).
+__device__ __forceinline__ void wg_sum_store(double v, double* partial) {
+    __shared__ double red[kWG / 64];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (lane == 0) red[w] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+        for (int k = 0; k < (int)(blockDim.x >> 6); ++k) s += red[k];
+        partial[blockIdx.x] = s;
+    }
+}
+
+}  // namespace dgmg

@@ -35,7 +35,7 @@
 #include "ionic.hpp"
 #include "kernels.hpp"
 #include "kernels_multi.hpp"
-#include "kernels_mf.hpp"
+#include "cell.hpp"
 
 namespace dgmg {
 
@@ -43,32 +43,13 @@ static thread_local std::string g_last_error;
 void set_last_error(const std::string& m) { g_last_error = m; }
 [[noreturn]] void fail(int code, const std::string& msg) { throw Error{code, msg}; }
 
-#define HIPCHK(expr)                                                                       \
-    do {                                                                                   \
-        hipError_t e_ = (expr);                                                            \
-        if (e_ != hipSuccess)                                                              \
-            fail(DGMG_EHIP, std::string(#expr) + ": " + hipGetErrorString(e_));            \
-    } while (0)
-
-// level layout: LYV (LY_TILE, LY_AXIS, LY_MF, LY_AXS) and AXV (axis-ELL) as constants
+// level layout of the block kernels: LYV (LY_TILE, LY_AXIS, LY_AXS) and AXV (axis-ELL) as constants
 #define DISPATCH_LY(lyval, ...)                                                        \
     switch (lyval) {                                                                   \
         case LY_TILE: { constexpr int LYV = LY_TILE; constexpr bool AXV = false; __VA_ARGS__; } break; \
         case LY_AXIS: { constexpr int LYV = LY_AXIS; constexpr bool AXV = true; __VA_ARGS__; } break;  \
         case LY_AXS: { constexpr int LYV = LY_AXS; constexpr bool AXV = true; __VA_ARGS__; } break;    \
-        default: { constexpr int LYV = LY_MF; constexpr bool AXV = false; __VA_ARGS__; } break;        \
-    }
-
-#define DISPATCH_B(bval, ...)                                                          \
-    switch (bval) {                                                                    \
-        case 4: { constexpr int BV = 4; __VA_ARGS__; } break;                          \
-        case 8: { constexpr int BV = 8; __VA_ARGS__; } break;                          \
-        case 9: { constexpr int BV = 9; __VA_ARGS__; } break;                          \
-        case 16: { constexpr int BV = 16; __VA_ARGS__; } break;                        \
-        case 25: { constexpr int BV = 25; __VA_ARGS__; } break;                        \
-        case 27: { constexpr int BV = 27; __VA_ARGS__; } break;                        \
-        case 64: { constexpr int BV = 64; __VA_ARGS__; } break;                        \
-        default: fail(DGMG_EUNSUPPORTED, "unsupported block size");                    \
+        default: fail(DGMG_EUNSUPPORTED, "the level has no stored blocks");                            \
     }
 
 void* DeviceMemory::alloc(size_t bytes) const {
@@ -262,13 +243,19 @@ template <typename T>
 static LevelArgs<T> largs(const DevLevel& L);
 template <>
 LevelArgs<double> largs<double>(const DevLevel& L) {
-    return {L.vals64, L.slot_ptr, L.snb, L.dinv64, L.n, L.up, L.lo, L.mf64, L.cmap};
+    return {L.vals64, L.slot_ptr, L.snb, L.dinv64, L.n, L.up, L.lo, L.cmap};
 }
 template <>
 LevelArgs<float> largs<float>(const DevLevel& L) {
-    return {L.vals32, L.slot_ptr, L.snb, L.dinv32, L.n, L.up, L.lo, L.mf32, L.cmap};
+    return {L.vals32, L.slot_ptr, L.snb, L.dinv32, L.n, L.up, L.lo, L.cmap};
 }
-static int level_ly(const DevLevel& L) { return L.mf ? LY_MF : (L.ax ? (L.sf ? LY_AXS : LY_AXIS) : LY_TILE); }
+template <typename T>
+static CellArgs<T> cargs(const DevLevel& L);
+template <>
+CellArgs<double> cargs<double>(const DevLevel& L) { return {L.up, L.lo, L.dinv64, L.n, L.mf64}; }
+template <>
+CellArgs<float> cargs<float>(const DevLevel& L) { return {L.up, L.lo, L.dinv32, L.n, L.mf32}; }
+static int level_ly(const DevLevel& L) { return L.mf ? LY_CELL : (L.ax ? (L.sf ? LY_AXS : LY_AXIS) : LY_TILE); }
 template <typename T>
 static const T* Pof(const DevLevel& L);
 template <>
@@ -304,21 +291,14 @@ struct ProfScope {
         idx = s->prof_used++;
         on = true;
     }
+    LaunchEvents events() const {
+        return on ? LaunchEvents{s->prof_ev[idx].first, s->prof_ev[idx].second} : LaunchEvents{};
+    }
 };
 
-// Launches kernel k on st.  When the scope is timing this launch, the start
-// and stop events ride on the kernel's own dispatch (hipExtLaunchKernelGGL),
-// so their interval is the kernel's execution alone, without the dispatch
-// gaps that separately recorded events would add.
 template <typename... KA, typename... A>
-static void klaunch(const ProfScope& ps, void (*k)(KA...), dim3 grid, dim3 block, hipStream_t st,
-                    A&&... a) {
-    if (!ps.on) {
-        hipLaunchKernelGGL(k, grid, block, 0, st, static_cast<KA>(a)...);
-        return;
-    }
-    hipExtLaunchKernelGGL(k, grid, block, 0, st, ps.s->prof_ev[ps.idx].first, ps.s->prof_ev[ps.idx].second, 0,
-                          static_cast<KA>(a)...);
+static void klaunch(const ProfScope& ps, void (*k)(KA...), dim3 grid, dim3 block, hipStream_t st, A&&... a) {
+    klaunch(ps.events(), k, grid, block, st, static_cast<KA>(a)...);
 }
 enum { PK_CHEB_STEP = 0, PK_RESIDUAL = 1, PK_APPLY = 2, PK_RESTRICT = 3, PK_PROLONG = 4,
        PK_COARSE = 5 };
@@ -335,6 +315,7 @@ static unsigned tiles_for(const DevLevel& L) {
 template <typename T>
 static unsigned level_tiles(const dgmg_solver* s, const DevLevel& L) {
     unsigned g = 0;
+    if (L.mf) return cell_groups(s->b, L.n);
     DISPATCH_B(s->b, g = tiles_for<T, BV>(L));
     return g;
 }
@@ -342,14 +323,17 @@ template <typename T, int R = 1>
 static void launch_apply(dgmg_solver* s, const DevLevel& L, const T* va, T* y, const T* w,
                          double* partial, hipStream_t st) {
     ProfScope ps(s, PK_APPLY, level_index(s, L), st);
+    if (L.mf) {
+        if (R != 1) fail(DGMG_EUNSUPPORTED, "the matrix-free fine level has no multi-column kernels");
+        cell_apply<T>(ps.events(), s->b, cargs<T>(L), va, y, w, partial, st);
+        return;
+    }
     DISPATCH_LY(level_ly(L), {
         if constexpr (R == 1) {
             DISPATCH_B(s->b, klaunch(ps, k_apply<T, BV, LYV>, tiles_for<T, BV>(L), kWG, st, largs<T>(L), va, y, w,
                                                                                         partial));
         } else if constexpr (LYV == LY_AXS) {
             fail(DGMG_EUNSUPPORTED, "sparse face blocks have no multi-column kernels");
-        } else if constexpr (LYV == LY_MF) {
-            fail(DGMG_EUNSUPPORTED, "the matrix-free fine level has no multi-column kernels");
         } else {
             DISPATCH_B(s->b, klaunch(ps, k_apply_m<T, BV, R, AXV>, tiles_for<T, BV>(L), kWG, st, largs<T>(L), va, y,
                                                                                             w, partial));
@@ -363,6 +347,11 @@ static void launch_residual(dgmg_solver* s, const DevLevel& L, const T* va, cons
                             const T* bj = nullptr) {
     ProfScope ps(s, PK_RESIDUAL, level_index(s, L), st);
     if (R != 1 && bj) fail(DGMG_EUNSUPPORTED, "cell-block Jacobi is single-column only");
+    if (L.mf) {
+        if (R != 1) fail(DGMG_EUNSUPPORTED, "the matrix-free fine level has no multi-column kernels");
+        cell_residual<T>(ps.events(), s->b, cargs<T>(L), va, vb, rhs, r, d, c1, xout, partial, P, rp, ptype, bj, st);
+        return;
+    }
     DISPATCH_LY(level_ly(L), {
         if constexpr (R == 1) {
             if (vb && bj) {
@@ -380,8 +369,6 @@ static void launch_residual(dgmg_solver* s, const DevLevel& L, const T* va, cons
             }
         } else if constexpr (LYV == LY_AXS) {
             fail(DGMG_EUNSUPPORTED, "sparse face blocks have no multi-column kernels");
-        } else if constexpr (LYV == LY_MF) {
-            fail(DGMG_EUNSUPPORTED, "the matrix-free fine level has no multi-column kernels");
         } else {
             bool done = false;
             if constexpr (std::is_same<T, float>::value && R == 8) {
@@ -414,6 +401,11 @@ static void launch_step(dgmg_solver* s, const DevLevel& L, const T* d, T* x, T* 
                         int assign, int last, hipStream_t st, const T* bj = nullptr) {
     ProfScope ps(s, PK_CHEB_STEP, level_index(s, L), st);
     if (R != 1 && bj) fail(DGMG_EUNSUPPORTED, "cell-block Jacobi is single-column only");
+    if (L.mf) {
+        if (R != 1) fail(DGMG_EUNSUPPORTED, "the matrix-free fine level has no multi-column kernels");
+        cell_step<T>(ps.events(), s->b, cargs<T>(L), d, x, r, dn, cd, cr, assign, last, bj, st);
+        return;
+    }
     DISPATCH_LY(level_ly(L), {
         if constexpr (R == 1) {
             if (bj) {
@@ -425,8 +417,6 @@ static void launch_step(dgmg_solver* s, const DevLevel& L, const T* d, T* x, T* 
             }
         } else if constexpr (LYV == LY_AXS) {
             fail(DGMG_EUNSUPPORTED, "sparse face blocks have no multi-column kernels");
-        } else if constexpr (LYV == LY_MF) {
-            fail(DGMG_EUNSUPPORTED, "the matrix-free fine level has no multi-column kernels");
         } else {
             bool done = false;
             if constexpr (std::is_same<T, float>::value && R == 8) {
@@ -1199,14 +1189,23 @@ template <typename T>
 static MfConst<T> mf_constants(const dgmg_solver* s, const RefElement& re, const T* dev_D) {
     MfConst<T> C{};
     const int Q = re.q;
-    std::vector<double> v(Q), dv(Q);
+    std::vector<double> v(Q), dv(Q), M(Q * Q, 0.0), Nm(Q * Q, 0.0);
     for (int g = 0; g < Q; ++g) {
         lagrange1d(re.nodes, re.gx[g], v.data(), dv.data());
         for (int j = 0; j < Q; ++j) {
             C.Ig[g * Q + j] = (T)v[j];
-            C.Dg[g * Q + j] = (T)dv[j];
+            for (int i = 0; i < Q; ++i) {
+                M[i * Q + j] += re.gw[g] * v[i] * v[j];
+                Nm[i * Q + j] += re.gw[g] * v[i] * dv[j];
+            }
         }
+        lagrange1d(re.gx, re.gx[g], v.data(), dv.data());
+        for (int h = 0; h < Q; ++h) C.Gc[g * Q + h] = (T)dv[h];
         C.gw[g] = (T)re.gw[g];
+    }
+    for (int k = 0; k < Q * Q; ++k) {
+        C.M1[k] = (T)M[k];
+        C.N1[k] = (T)Nm[k];
     }
     for (int e = 0; e < 2; ++e) {
         lagrange1d(re.nodes, (double)e, v.data(), dv.data());
