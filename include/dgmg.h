@@ -176,13 +176,17 @@ enum { DGMG_PREC_FP64 = 0, DGMG_PREC_MIXED = 1 };
  * upper faces along each axis; lower faces are read transposed from the
  * neighbour), TILE_ELL stores each face block twice, oriented for both
  * cells, as on the agglomerated levels; AUTO takes MATRIX_FREE for p >= 2 on
- * meshes of identical boxes with max_rhs <= 1, AXIS_ELL otherwise.  With
+ * meshes of identical boxes with max_rhs <= 1; on other meshes with p >= 2
+ * (not 3D Q3), max_rhs <= 1, at least 256 cells and a second level it keeps
+ * metric data at the Gauss points and evaluates the operator from them
+ * (reported as MATRIX_FREE); AXIS_ELL otherwise.  With
  * max_rhs <= 1, AXIS_ELL stores nodal face blocks in sparse form (see
  * dgmg_solver_info.sparse_faces); AXIS_ELL_DENSE keeps every face block
  * whole.
  * MATRIX_FREE (meshes of identical
  * axis-aligned boxes only, single-column calls only; DGMG_EUNSUPPORTED
- * otherwise) stores no fine-level operator: the cell, face and mass terms
+ * otherwise, also where AUTO holds metric data) stores no fine-level
+ * operator: the cell, face and mass terms
  * are evaluated by sum factorisation from the per-cell conductivity.
  * setup_on_device = 1 (needs device_setup = 1) computes the fine operator
  * and mass blocks (except with adjoint = 1), the prolongation blocks, the

@@ -4,6 +4,7 @@
 
 #include <cstdint>
 
+#include "kernels_common.hpp"
 #include "launch.hpp"
 
 namespace dgmg {
@@ -27,12 +28,34 @@ struct MfConst {
     T cM;                      // mass coefficient of A_0
     const T* D;                // per cell: packed symmetric D (d(d+1)/2 values)
 };
+// How a level's cells are evaluated: identical boxes, bilinear / trilinear
+// cells with their metric data at the Gauss points, or stored blocks of a
+// nodal level on a conforming grid of boxes.
+enum { GEO_BOX = 0, GEO_MAP = 1, GEO_BLK = 2 };
+
+// entry (i, j) of a nodal face block along axis a: node i on the lower cell's
+// upper face or node j on the upper cell's lower face
+__host__ __device__ constexpr bool face_entry(int i, int j, int a, int q) {
+    return node_coord(i, a, q) == q - 1 || node_coord(j, a, q) == 0;
+}
+// entries and 16-byte groups per cell (layout in kernels_cell.hpp)
+template <int B, int GEO>
+struct CellPack {
+    static constexpr int D = dim_of<B>(), Q = ax_nodes_1d(B, D), QN = B / Q;
+    static constexpr int NEC = GEO == GEO_MAP ? B * (D * (D + 1) / 2 + 1) : GEO == GEO_BLK ? B * (B + 1) / 2 : 0;
+    static constexpr int NEF = GEO == GEO_MAP ? QN * (2 * D + 1) : GEO == GEO_BLK ? 2 * QN * B - QN * QN : 0;
+    static constexpr int cell_groups(int w) { return (NEC + w - 1) / w; }
+    static constexpr int face_groups(int w) { return (NEF + w - 1) / w; }
+    static constexpr int groups(int w) { return cell_groups(w) + D * face_groups(w); }
+};
+
 template <typename T>
 struct CellArgs {
     const int32_t* __restrict__ up;        // [d][n] upper neighbour (itself if none)
     const int32_t* __restrict__ lo;        // [d][n] lower neighbour (-1 if none)
     const T* __restrict__ dinv;
     int32_t n;
+    const T* __restrict__ data;            // mapped and stored cells: their entries
     MfConst<T> mf;
 };
 
@@ -41,15 +64,23 @@ struct CellArgs {
 unsigned cell_groups(int b, int n);
 
 // The cell forms of k_apply, k_residual and k_cheb_step (same arguments).
-template <typename T>
+template <typename T, int GEO>
 void cell_apply(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* va, T* y, const T* w, double* partial,
                 hipStream_t st);
-template <typename T>
+template <typename T, int GEO>
 void cell_residual(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* va, const T* vb, const T* rhs, T* r,
                    T* d, T c1, T* xout, double* partial, const T* P, T* rp, const int32_t* ptype, const T* bj,
                    hipStream_t st);
-template <typename T>
+template <typename T, int GEO>
 void cell_step(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* d, T* x, T* r, T* dn, T cd, T cr,
                int assign, int last, const T* bj, hipStream_t st);
+
+// geometry GEO of a level as a constant
+#define DISPATCH_GEO(gval, ...)                                                        \
+    switch (gval) {                                                                    \
+        case GEO_BOX: { constexpr int GEO = GEO_BOX; __VA_ARGS__; } break;             \
+        case GEO_MAP: { constexpr int GEO = GEO_MAP; __VA_ARGS__; } break;             \
+        default: { constexpr int GEO = GEO_BLK; __VA_ARGS__; } break;                  \
+    }
 
 }  // namespace dgmg

@@ -1,0 +1,14 @@
+// Cell kernels on identical boxes.
+#include "cell_launch.hpp"
+
+namespace dgmg {
+
+unsigned cell_groups(int b, int n) {
+    const int nc = cells_per_group(b, n);
+    return (unsigned)((n + nc - 1) / nc);
+}
+
+DGMG_CELL_LAUNCHERS(float, GEO_BOX)
+DGMG_CELL_LAUNCHERS(double, GEO_BOX)
+
+}  // namespace dgmg

@@ -1,0 +1,9 @@
+// Cell kernels on bilinear and trilinear cells.
+#include "cell_launch.hpp"
+
+namespace dgmg {
+
+DGMG_CELL_LAUNCHERS(float, GEO_MAP)
+DGMG_CELL_LAUNCHERS(double, GEO_MAP)
+
+}  // namespace dgmg

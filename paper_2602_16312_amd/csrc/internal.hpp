@@ -87,6 +87,18 @@ void assemble_fine(const Hierarchy& h, const Faces& F, const RefElement& re,
                    const dgmg_disc& disc, const dgmg_physics& ph, double cM, BlockOp& A0,
                    std::vector<double>& mass, AdjointBlocks* adj = nullptr);
 
+// A_0 as metric data at the Gauss points, for the sum-factorised operator on
+// bilinear / trilinear cells.  Per cell point: the packed tensor
+// w J^-1 D J^-T, then cM w.  Per face point: -w/2 J_+^-1 D_+ n and
+// -w/2 J_-^-1 D_- n (components along the normal reference axis, then the
+// tangential ones), then w sigma.
+struct MetricData {
+    int nec = 0, nef = 0;                     // values per cell and per face
+    std::vector<double> cell, face;
+};
+void metric_data(const Hierarchy& h, const Faces& F, const RefElement& re, const dgmg_disc& disc,
+                 const dgmg_physics& ph, double cM, MetricData& M);
+
 // Prolongation blocks P_e (n_l x b x b, row-major: fine node i, coarse basis j)
 // from level l+1 to level l, with per-level bounding boxes.
 void prolongation_blocks(const Hierarchy& h, const RefElement& re, int level,

@@ -51,17 +51,18 @@ constexpr int pk(int a, int b) {
     return D == 2 ? lo + hi : (lo == 0 ? hi : (lo == 1 ? 2 + hi : 5));
 }
 
-// threads per workgroup: a wave for the cell terms and one per axis
-template <int B>
+// threads per workgroup: a wave for the cell terms and one per axis, or per
+// face where the faces' blocks are streamed
+template <int B, int GEO>
 constexpr int cell_threads() {
-    return 64 * (1 + dim_of<B>());
+    return 64 * (1 + (GEO == GEO_BLK ? 2 : 1) * dim_of<B>());
 }
-template <typename T, int B, int NCELL>
+template <typename T, int B, int NCELL, int GEO = GEO_BOX>
 struct CellTile {
     static constexpr int D = dim_of<B>(), Q = ax_nodes_1d(B, D), QN = B / Q;
     static constexpr int NC = NCELL;                  // cells per workgroup, one per lane
-    static constexpr int NW = 1 + D;                  // waves: cell terms, faces of each axis
-    static constexpr int NT = cell_threads<B>();
+    static constexpr int NT = cell_threads<B, GEO>();
+    static constexpr int NW = NT / 64;
     static constexpr int SB = B | 1;                  // odd LDS stride of a cell's rows
 };
 
@@ -130,7 +131,7 @@ __device__ __forceinline__ void all_passes(T* u, const T* M) {
 
 // Cell terms of cell c: cM w u and the fluxes w D grad u, tested.
 template <typename T, int B, int NC, bool VB>
-__device__ __forceinline__ void cell_terms(const CellArgs<T>& L, int c, const T* __restrict__ va,
+__device__ __forceinline__ void box_cell_terms(const CellArgs<T>& L, int c, const T* __restrict__ va,
                                            const T* __restrict__ vb, T* ys) {
     using Ct = CellTile<T, B, NC>;
     constexpr int D = Ct::D, Q = Ct::Q, NP = npack<D>();
@@ -177,7 +178,7 @@ __device__ __forceinline__ void cell_terms(const CellArgs<T>& L, int c, const T*
 
 // Both faces of cell c normal to axis A.
 template <typename T, int B, int NC, bool VB, int A>
-__device__ __forceinline__ void face_terms(const CellArgs<T>& L, int c, const T* __restrict__ va,
+__device__ __forceinline__ void box_face_terms(const CellArgs<T>& L, int c, const T* __restrict__ va,
                                            const T* __restrict__ vb, T* ys) {
     using Ct = CellTile<T, B, NC>;
     constexpr int D = Ct::D, Q = Ct::Q, QN = Ct::QN, NP = npack<D>();
@@ -292,6 +293,297 @@ __device__ __forceinline__ void face_terms(const CellArgs<T>& L, int c, const T*
             ys[J0 + j * SA] = v;
         }
     }
+}
+
+// ---- per-cell data of mapped and stored cells
+// Entries of cell c, 16 bytes (W values) per lane and load: group g at
+// data + ((c / 64) NG + g) 64 W + (c % 64) W, so that the 64 lanes of
+// consecutive cells read 1 KiB.  Groups 0 .. NGC - 1 belong to the cell, then
+// NGF groups per axis to the face on its upper side.  The face on the lower
+// side is read from the lower neighbour's groups.
+template <typename T>
+struct Vec16a;
+template <>
+struct Vec16a<float> {
+    typedef float type __attribute__((ext_vector_type(4)));
+};
+template <>
+struct Vec16a<double> {
+    typedef double type __attribute__((ext_vector_type(2)));
+};
+template <typename T, int NE>
+struct Stream {
+    using V = typename Vec16a<T>::type;
+    static constexpr int W = 16 / sizeof(T);
+    const V* p;
+    V v;
+    __device__ __forceinline__ Stream(const T* base) : p(reinterpret_cast<const V*>(base)) {}
+    // entry e (compile-time after unrolling), entries in ascending order
+    __device__ __forceinline__ T get(int e) {
+        if (e % W == 0) v = p[(size_t)(e / W) * 64];
+        return v[e % W];
+    }
+};
+// Groups requested ahead: 64^3 Q2's level of 32,768 boxes, FP32 step at 4 / 8 /
+// 12 / 16 groups 44 / 49 / 42 / 42 us, FP64 94 / 97 / 102 / 102 us.
+template <typename T>
+constexpr int ring_groups() {
+    return sizeof(T) == 4 ? 12 : 4;
+}
+// f(e, entry e) for the NE entries of a stored block in order, with R groups
+// requested ahead of the one in use (the loads of the straight-line products
+// would otherwise all be hoisted into hundreds of live registers).
+template <typename T, int NE, int R, typename F>
+__device__ __forceinline__ void stream_entries(const T* base, F&& f) {
+    using V = typename Vec16a<T>::type;
+    constexpr int W = 16 / sizeof(T), NG = (NE + W - 1) / W, RG = R < NG ? R : NG;
+    const V* p = reinterpret_cast<const V*>(base);
+    V ring[RG];
+#pragma unroll
+    for (int g = 0; g < RG; ++g) ring[g] = p[(size_t)g * 64];
+    p += RG * 64;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        const V v = ring[g % RG];
+        if (g + RG < NG) {
+            int off = g * 64;
+            asm volatile("" : "+v"(off) : "v"(v[0]));   // the next request follows this group's arrival
+            ring[g % RG] = p[off];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+            if (g * W + w < NE) f(g * W + w, v[w]);
+    }
+}
+// (row, column) of the stored entries in their order
+template <int B>
+struct TriList {
+    unsigned char i[B * (B + 1) / 2] = {}, j[B * (B + 1) / 2] = {};
+    constexpr TriList() {
+        int e = 0;
+        for (int a = 0; a < B; ++a)
+            for (int b = a; b < B; ++b, ++e) {
+                i[e] = (unsigned char)a;
+                j[e] = (unsigned char)b;
+            }
+    }
+};
+template <int B, int A>
+struct FaceList {
+    unsigned char i[CellPack<B, GEO_BLK>::NEF] = {}, j[CellPack<B, GEO_BLK>::NEF] = {};
+    constexpr FaceList() {
+        int e = 0;
+        for (int a = 0; a < B; ++a)
+            for (int b = 0; b < B; ++b)
+                if (face_entry(a, b, A, CellPack<B, GEO_BLK>::Q)) {
+                    i[e] = (unsigned char)a;
+                    j[e++] = (unsigned char)b;
+                }
+    }
+};
+template <typename T, int B, int GEO>
+__device__ __forceinline__ const T* cell_data(const CellArgs<T>& L, int c, int group) {
+    using P = CellPack<B, GEO>;
+    constexpr int W = 16 / sizeof(T), NG = P::groups(W);
+    return L.data + (((size_t)(c >> 6) * NG + group) * 64 + (c & 63)) * W;
+}
+
+// ---- mapped cells (bilinear / trilinear geometry): per Gauss point the
+// weighted metric tensor w J^-1 D J^-T and the mass weight
+template <typename T, int B, int NC, bool VB>
+__device__ __forceinline__ void map_cell_terms(const CellArgs<T>& L, int c, const T* __restrict__ va,
+                                               const T* __restrict__ vb, T* ys) {
+    using Ct = CellTile<T, B, NC>;
+    constexpr int D = Ct::D, Q = Ct::Q, NP = npack<D>();
+    const MfConst<T>& C = L.mf;
+    T u[B], y[B];
+    load_cell<T, B, VB>(va, vb, c, u);
+    all_passes<T, Q, D, false>(u, C.Ig);
+#pragma unroll
+    for (int g = 0; g < B; ++g) y[g] = 0;
+    Stream<T, B*(NP + 1)> K(cell_data<T, B, GEO_MAP>(L, c, 0));
+#pragma unroll
+    for (int g = 0; g < B; ++g) {
+        const int gc[3] = {node_coord(g, 0, Q), node_coord(g, 1, Q), D == 3 ? node_coord(g, 2, Q) : 0};
+        T k[NP + 1], gr[D];
+#pragma unroll
+        for (int q = 0; q <= NP; ++q) k[q] = K.get(g * (NP + 1) + q);
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            T s = 0;
+#pragma unroll
+            for (int h = 0; h < Q; ++h) s += C.Gc[gc[a] * Q + h] * u[g + (h - gc[a]) * ipow(Q, a)];
+            gr[a] = s;
+        }
+        y[g] += k[NP] * u[g];
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            T f = 0;
+#pragma unroll
+            for (int b = 0; b < D; ++b) f += k[pk<D>(a, b)] * gr[b];
+#pragma unroll
+            for (int h = 0; h < Q; ++h) y[g + (h - gc[a]) * ipow(Q, a)] += C.Gc[gc[a] * Q + h] * f;
+        }
+    }
+    all_passes<T, Q, D, true>(y, C.Ig);
+#pragma unroll
+    for (int i = 0; i < B; ++i) ys[i] = y[i];
+}
+
+// Both faces normal to A.  Per Gauss point of a face: p = -w/2 J_+^-1 D_+ n and
+// m = -w/2 J_-^-1 D_- n as weights of the reference gradients (normal, t1, t2)
+// of the lower (+) and upper (-) cell, and w sigma.  With j = u_own - u_nb, the
+// value flux is (o + v)_t d_t u_own - v_t d_t j + o_n d_own + v_n d_nb + w sigma j
+// up to the side's sign (o, v: the own and the neighbour's weights), and the
+// conormal flux o j is tested against the reference gradient.
+template <typename T, int B, int NC, bool VB, int A>
+__device__ __forceinline__ void map_face_terms(const CellArgs<T>& L, int c, const T* __restrict__ va,
+                                               const T* __restrict__ vb, T* ys) {
+    using Ct = CellTile<T, B, NC>;
+    constexpr int D = Ct::D, Q = Ct::Q, QN = Ct::QN;
+    constexpr int SA = ipow(Q, A);
+    constexpr int t1 = A == 0 ? 1 : 0, t2 = D == 3 ? (A == 2 ? 1 : 2) : t1;
+    constexpr int S1 = ipow(Q, t1), S2 = D == 3 ? ipow(Q, t2) : 0;
+    constexpr int NE = 2 * D + 1, W = 16 / sizeof(T);
+    using P = CellPack<B, GEO_MAP>;
+    const MfConst<T>& C = L.mf;
+    const int lo = L.lo[(size_t)A * L.n + c], up = L.up[(size_t)A * L.n + c];
+    const int nb[2] = {lo >= 0 ? lo : c, up};
+    const bool has[2] = {lo >= 0, up != c};
+    T xk[B], T0[2][QN], Tn[2][QN];
+    load_cell<T, B, VB>(va, vb, c, xk);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        T xn[B];
+        load_cell<T, B, VB>(va, vb, nb[s], xn);
+        Stream<T, NE * QN> F(cell_data<T, B, GEO_MAP>(L, s ? c : nb[0], P::cell_groups(W) + A * P::face_groups(W)));
+        T uK[QN], jp[QN], dK[QN], dN[QN], acc[QN], cn[QN];
+#pragma unroll
+        for (int m = 0; m < QN; ++m) {
+            const int J0 = (m % Q) * S1 + (m / Q) * S2;
+            T a = 0, b = 0;
+#pragma unroll
+            for (int j = 0; j < Q; ++j) {
+                a += C.Ed[s * Q + j] * xk[J0 + j * SA];
+                b += C.Ed[(1 - s) * Q + j] * xn[J0 + j * SA];
+            }
+            dK[m] = a;
+            dN[m] = b;
+            uK[m] = xk[J0 + s * (Q - 1) * SA];
+            jp[m] = uK[m] - xn[J0 + (1 - s) * (Q - 1) * SA];
+            acc[m] = 0;
+        }
+        all_passes<T, Q, D - 1, false>(uK, C.Ig);
+        all_passes<T, Q, D - 1, false>(jp, C.Ig);
+        all_passes<T, Q, D - 1, false>(dK, C.Ig);
+        all_passes<T, Q, D - 1, false>(dN, C.Ig);
+#pragma unroll
+        for (int q = 0; q < QN; ++q) {
+            const int q1 = q % Q, q2 = q / Q;
+            T f[NE];
+#pragma unroll
+            for (int k = 0; k < NE; ++k) f[k] = F.get(q * NE + k);
+            const T* o = s ? f : f + D;                   // own weights, then the neighbour's
+            const T* v = s ? f + D : f;
+            T val = o[0] * dK[q] + v[0] * dN[q] + (s ? f[2 * D] : -f[2 * D]) * jp[q];
+            // the jump u_+ - u_- is j on the upper face, -j on the lower one;
+            // the own test function enters with the same sign
+            const T js = s ? jp[q] : -jp[q];
+#pragma unroll
+            for (int h = 0; h < Q; ++h) {
+                const int m = h + Q * q2;
+                val += C.Gc[q1 * Q + h] * ((o[1] + v[1]) * uK[m] - v[1] * jp[m]);
+                acc[m] += C.Gc[q1 * Q + h] * (o[1] * js);
+                if constexpr (D == 3) {
+                    const int n = q1 + Q * h;
+                    val += C.Gc[q2 * Q + h] * ((o[2] + v[2]) * uK[n] - v[2] * jp[n]);
+                    acc[n] += C.Gc[q2 * Q + h] * (o[2] * js);
+                }
+            }
+            acc[q] += s ? val : -val;
+            cn[q] = o[0] * js;
+        }
+        all_passes<T, Q, D - 1, true>(acc, C.Ig);
+        all_passes<T, Q, D - 1, true>(cn, C.Ig);
+#pragma unroll
+        for (int m = 0; m < QN; ++m) {
+            T0[s][m] = has[s] ? acc[m] : T(0);
+            Tn[s][m] = has[s] ? cn[m] : T(0);
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < QN; ++m) {
+        const int J0 = (m % Q) * S1 + (m / Q) * S2;
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            T v = C.Ed[j] * Tn[0][m] + C.Ed[Q + j] * Tn[1][m];
+            if (j == 0) v += T0[0][m];
+            if (j == Q - 1) v += T0[1][m];
+            ys[J0 + j * SA] = v;
+        }
+    }
+}
+
+// ---- stored blocks: the upper triangle of the cell block, and the face
+// block's entries (i, j) with node i on the upper face or node j on the
+// neighbour's lower face (the others vanish on a nodal level).  Every entry is
+// read coalesced, also by the cell above a face, whose transposed reads by a
+// thread per row touched a line per lane: level 1 of the 64^3 Q2 cube (32,768
+// boxes of 27 DoFs, 209 MB of entries), FP32 step 92 -> 42 us, FP64 260 -> 94.
+template <typename T, int B, int NC, bool VB>
+__device__ __forceinline__ void blk_cell_terms(const CellArgs<T>& L, int c, const T* __restrict__ va,
+                                               const T* __restrict__ vb, T* ys) {
+    T x[B], y[B];
+    load_cell<T, B, VB>(va, vb, c, x);
+#pragma unroll
+    for (int i = 0; i < B; ++i) y[i] = 0;
+    constexpr TriList<B> tri;
+    stream_entries<T, B*(B + 1) / 2, ring_groups<T>()>(cell_data<T, B, GEO_BLK>(L, c, 0), [&](int e, T a) {
+        const int i = tri.i[e], j = tri.j[e];
+        y[i] += a * x[j];
+        if (j > i) y[j] += a * x[i];
+    });
+#pragma unroll
+    for (int i = 0; i < B; ++i) ys[i] = y[i];
+}
+template <typename T, int B, bool VB, int A, int S>
+__device__ __forceinline__ void blk_face_terms(const CellArgs<T>& L, int c, const T* __restrict__ va,
+                                               const T* __restrict__ vb, T* ys) {
+    constexpr int W = 16 / sizeof(T);
+    using P = CellPack<B, GEO_BLK>;
+    constexpr FaceList<B, A> list;
+    // no lower neighbour: the products are dropped with zero values (a missing
+    // upper face has zero entries)
+    const int v = (S ? L.up : L.lo)[(size_t)A * L.n + c], nb = v >= 0 ? v : c;
+    T x[B], y[B];
+    load_cell<T, B, VB>(va, vb, nb, x);
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+        x[i] = v >= 0 ? x[i] : T(0);
+        y[i] = 0;
+    }
+    stream_entries<T, P::NEF, ring_groups<T>()>(
+        cell_data<T, B, GEO_BLK>(L, S ? c : nb, P::cell_groups(W) + A * P::face_groups(W)), [&](int e, T a) {
+            const int i = list.i[e], j = list.j[e];
+            if (S) y[i] += a * x[j];
+            else y[j] += a * x[i];
+        });
+#pragma unroll
+    for (int i = 0; i < B; ++i) ys[i] = y[i];
+}
+
+template <typename T, int B, int NC, bool VB, int GEO>
+__device__ __forceinline__ void cell_terms(const CellArgs<T>& L, int c, const T* __restrict__ va,
+                                           const T* __restrict__ vb, T* ys) {
+    if constexpr (GEO == GEO_BOX) box_cell_terms<T, B, NC, VB>(L, c, va, vb, ys);
+    else map_cell_terms<T, B, NC, VB>(L, c, va, vb, ys);
+}
+template <typename T, int B, int NC, bool VB, int GEO, int A>
+__device__ __forceinline__ void face_terms(const CellArgs<T>& L, int c, const T* __restrict__ va,
+                                           const T* __restrict__ vb, T* ys) {
+    if constexpr (GEO == GEO_BOX) box_face_terms<T, B, NC, VB, A>(L, c, va, vb, ys);
+    else map_face_terms<T, B, NC, VB, A>(L, c, va, vb, ys);
 }
 
 // ---- 3D Q3 cells: four lanes per cell
@@ -468,13 +760,14 @@ __device__ __forceinline__ void face_terms_quad(const CellArgs<T>& L, int c, int
 // Evaluates the workgroup's shares: sh[w * NC * SB + cell * SB + row].  Lanes past
 // the last cell evaluate cell n - 1 and their rows are not read.  The caller
 // synchronises before it reads the shares.
-template <typename T, int B, int NC, bool VB>
+template <typename T, int B, int NC, bool VB, int GEO>
 __device__ __forceinline__ void cell_product(const CellArgs<T>& L, int cell0, const T* __restrict__ va,
                                              const T* __restrict__ vb, T* sh) {
-    using Ct = CellTile<T, B, NC>;
+    using Ct = CellTile<T, B, NC, GEO>;
     static_assert(NC <= (B == 64 ? 16 : 64), "cells of a workgroup do not fit a wave");
     const int lane = (int)threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     if constexpr (B == 64) {
+        static_assert(GEO == GEO_BOX, "3D Q3 cells: boxes only");
         const int c = min(cell0 + lane / 4, L.n - 1), l = lane & 3;
         T* ys = sh + (w * Ct::NC + lane / 4) * Ct::SB;
         if (w == 0) cell_terms_quad<T, VB>(L, c, l, va, vb, ys);
@@ -486,15 +779,27 @@ __device__ __forceinline__ void cell_product(const CellArgs<T>& L, int cell0, co
     if (lane >= NC) return;
     const int c = min(cell0 + lane, L.n - 1);
     T* ys = sh + (w * Ct::NC + lane) * Ct::SB;
-    if (w == 0) cell_terms<T, B, NC, VB>(L, c, va, vb, ys);
-    else if (w == 1) face_terms<T, B, NC, VB, 0>(L, c, va, vb, ys);
-    else if (Ct::D == 2 || w == 2) face_terms<T, B, NC, VB, 1>(L, c, va, vb, ys);
-    else if constexpr (Ct::D == 3) face_terms<T, B, NC, VB, 2>(L, c, va, vb, ys);
+    if constexpr (GEO == GEO_BLK) {
+        if (w == 0) blk_cell_terms<T, B, NC, VB>(L, c, va, vb, ys);
+        else if (w == 1) blk_face_terms<T, B, VB, 0, 0>(L, c, va, vb, ys);
+        else if (w == 2) blk_face_terms<T, B, VB, 0, 1>(L, c, va, vb, ys);
+        else if (w == 3) blk_face_terms<T, B, VB, 1, 0>(L, c, va, vb, ys);
+        else if (Ct::D == 2 || w == 4) blk_face_terms<T, B, VB, 1, 1>(L, c, va, vb, ys);
+        else if constexpr (Ct::D == 3) {
+            if (w == 5) blk_face_terms<T, B, VB, 2, 0>(L, c, va, vb, ys);
+            else blk_face_terms<T, B, VB, 2, 1>(L, c, va, vb, ys);
+        }
+        return;
+    }
+    if (w == 0) cell_terms<T, B, NC, VB, GEO>(L, c, va, vb, ys);
+    else if (w == 1) face_terms<T, B, NC, VB, GEO, 0>(L, c, va, vb, ys);
+    else if (Ct::D == 2 || w == 2) face_terms<T, B, NC, VB, GEO, 1>(L, c, va, vb, ys);
+    else if constexpr (Ct::D == 3) face_terms<T, B, NC, VB, GEO, 2>(L, c, va, vb, ys);
 }
 // row k = cell * SB + i of the product
-template <typename T, int B, int NC>
+template <typename T, int B, int NC, int GEO>
 __device__ __forceinline__ T cell_row(const T* sh, int k) {
-    using Ct = CellTile<T, B, NC>;
+    using Ct = CellTile<T, B, NC, GEO>;
     T a = sh[k];
 #pragma unroll
     for (int w = 1; w < Ct::NW; ++w) a += sh[w * Ct::NC * Ct::SB + k];
@@ -502,7 +807,7 @@ __device__ __forceinline__ T cell_row(const T* sh, int k) {
 }
 
 #define DGMG_CELL_GROUP(T, B)                                                        \
-    using Ct = CellTile<T, B, NC>;                                                       \
+    using Ct = CellTile<T, B, NC, GEO>;                                                       \
     __shared__ T sh[Ct::NW * Ct::NC * Ct::SB];                                       \
     const int cell0 = xcd_tile(blockIdx.x, gridDim.x) * Ct::NC;                      \
     const int rows = min(Ct::NC, L.n - cell0) * B;                                   \
@@ -511,24 +816,24 @@ __device__ __forceinline__ T cell_row(const T* sh, int k) {
 // vector operands are requested together (the first ones before the barrier):
 // a loop that loaded row by row cost a memory latency per row, 7 of them on
 // 3D Q2 cells.
-template <int B, int NC>
+template <int B, int NC, int GEO>
 constexpr int cell_rows_at_once() {
-    constexpr int n = (NC * B + cell_threads<B>() - 1) / cell_threads<B>();
+    constexpr int n = (NC * B + cell_threads<B, GEO>() - 1) / cell_threads<B, GEO>();
     return n > 9 ? 8 : n;
 }
 #define DGMG_CELL_ROWS(B)                                                            \
-    constexpr int U = cell_rows_at_once<B, NC>(), NCH = (Ct::NC * B + U * Ct::NT - 1) / (U * Ct::NT); \
+    constexpr int U = cell_rows_at_once<B, NC, GEO>(), NCH = (Ct::NC * B + U * Ct::NT - 1) / (U * Ct::NT); \
     auto row = [&](int ch, int u) { return (int)threadIdx.x + (ch * U + u) * Ct::NT; };           \
     auto at = [&](int e) { return e + (Ct::SB - B) * (e / B); };   // LDS index of row e
 
 // y = A va; optional partial of dot(w, y).
-template <typename T, int B, int NC>
-__global__ __launch_bounds__(cell_threads<B>()) void k_apply_cell(CellArgs<T> L, const T* __restrict__ va,
+template <typename T, int B, int NC, int GEO>
+__global__ __launch_bounds__((cell_threads<B, GEO>())) void k_apply_cell(CellArgs<T> L, const T* __restrict__ va,
                                                                   T* __restrict__ y, const T* __restrict__ w,
                                                                   double* __restrict__ partial) {
     DGMG_CELL_GROUP(T, B)
     DGMG_CELL_ROWS(B)
-    cell_product<T, B, NC, false>(L, cell0, va, nullptr, sh);
+    cell_product<T, B, NC, false, GEO>(L, cell0, va, nullptr, sh);
     T wv[U];
     auto fetch = [&](int ch) {
 #pragma unroll
@@ -544,7 +849,7 @@ __global__ __launch_bounds__(cell_threads<B>()) void k_apply_cell(CellArgs<T> L,
         for (int u = 0; u < U; ++u) {
             const int e = row(ch, u);
             if (e >= rows) continue;
-            const T a = cell_row<T, B, NC>(sh, at(e));
+            const T a = cell_row<T, B, NC, GEO>(sh, at(e));
             y[t0 + e] = a;
             contrib += (double)wv[u] * (double)a;
         }
@@ -553,14 +858,14 @@ __global__ __launch_bounds__(cell_threads<B>()) void k_apply_cell(CellArgs<T> L,
 }
 
 // Residual with the epilogues of k_residual.
-template <typename T, int B, int NC, bool VB, bool BJ>
-__global__ __launch_bounds__(cell_threads<B>()) void k_residual_cell(
+template <typename T, int B, int NC, int GEO, bool VB, bool BJ>
+__global__ __launch_bounds__((cell_threads<B, GEO>())) void k_residual_cell(
     CellArgs<T> L, const T* __restrict__ va, const T* __restrict__ vb, const T* __restrict__ rhs, T* __restrict__ r,
     T* __restrict__ d, T c1, T* __restrict__ xout, double* __restrict__ partial, const T* __restrict__ P,
     T* __restrict__ rp, const int32_t* __restrict__ ptype, const T* __restrict__ bj) {
     DGMG_CELL_GROUP(T, B)
     DGMG_CELL_ROWS(B)
-    cell_product<T, B, NC, VB>(L, cell0, va, vb, sh);
+    cell_product<T, B, NC, VB, GEO>(L, cell0, va, vb, sh);
     T bv[U], di[U];
     auto fetch = [&](int ch) {
 #pragma unroll
@@ -581,7 +886,7 @@ __global__ __launch_bounds__(cell_threads<B>()) void k_residual_cell(
             const int e = row(ch, u);
             if (e >= rows) continue;
             const size_t t = t0 + e;
-            const T rr = bv[u] - cell_row<T, B, NC>(sh, at(e));
+            const T rr = bv[u] - cell_row<T, B, NC, GEO>(sh, at(e));
             if (r) r[t] = rr;
             if (!BJ && d) d[t] = di[u] * rr * c1;
             if (xout) xout[t] = VB ? va[t] + vb[t] : va[t];
@@ -622,14 +927,14 @@ __global__ __launch_bounds__(cell_threads<B>()) void k_residual_cell(
 }
 
 // One inner Chebyshev step, as k_cheb_step.
-template <typename T, int B, int NC, bool BJ>
-__global__ __launch_bounds__(cell_threads<B>()) void k_cheb_step_cell(CellArgs<T> L, const T* __restrict__ d,
+template <typename T, int B, int NC, int GEO, bool BJ>
+__global__ __launch_bounds__((cell_threads<B, GEO>())) void k_cheb_step_cell(CellArgs<T> L, const T* __restrict__ d,
                                                                       T* __restrict__ x, T* __restrict__ r,
                                                                       T* __restrict__ dn, T cd, T cr, int assign,
                                                                       int last, const T* __restrict__ bj) {
     DGMG_CELL_GROUP(T, B)
     DGMG_CELL_ROWS(B)
-    cell_product<T, B, NC, false>(L, cell0, d, nullptr, sh);
+    cell_product<T, B, NC, false, GEO>(L, cell0, d, nullptr, sh);
     T rv[U], dv[U], xv[U], di[U];
     auto fetch = [&](int ch) {
 #pragma unroll
@@ -651,7 +956,7 @@ __global__ __launch_bounds__(cell_threads<B>()) void k_cheb_step_cell(CellArgs<T
             for (int u = 0; u < U; ++u) {
                 const int e = row(ch, u);
                 if (e >= rows) continue;
-                const T rr = rv[u] - cell_row<T, B, NC>(sh, at(e));
+                const T rr = rv[u] - cell_row<T, B, NC, GEO>(sh, at(e));
                 if (!last) r[t0 + e] = rr;
                 sh[at(e)] = rr;                       // a row's first share is read by its own thread only
             }
@@ -676,7 +981,7 @@ __global__ __launch_bounds__(cell_threads<B>()) void k_cheb_step_cell(CellArgs<T
 #pragma unroll
                 for (int i = 0; i < B; ++i) z += Dc[(size_t)i * B] * rc[i];
             } else {
-                const T rr = rv[u] - cell_row<T, B, NC>(sh, at(e));
+                const T rr = rv[u] - cell_row<T, B, NC, GEO>(sh, at(e));
                 if (!last) r[t] = rr;
                 z = di[u] * rr;
             }

@@ -508,4 +508,95 @@ void assemble_fine(const Hierarchy& h, const Faces& F, const RefElement& re,
     }
 }
 
+// Metric data of the sum-factorised operator at the Gauss points (the same
+// geometry, weights and penalty as assemble_fine).
+void metric_data(const Hierarchy& h, const Faces& F, const RefElement& re, const dgmg_disc& disc,
+                 const dgmg_physics& ph, double cM, MetricData& M) {
+    const int d = re.d, symn = d * (d + 1) / 2;
+    const int64_t n = h.n_cells, nf = (int64_t)F.plus.size();
+    FaceRef fr;
+    fr.init(re);
+    const int qf = fr.qf;
+    M.nec = re.qc * (symn + 1);
+    M.nef = qf * (2 * d + 1);
+    M.cell.assign((size_t)n * M.nec, 0.0);
+    M.face.assign((size_t)nf * M.nef, 0.0);
+    std::vector<double> vol(n, 0.0);
+    auto tensor = [&](int64_t c, double* D) {
+        unpack_D(d, &ph.D_cell[(size_t)c * symn], ph.cell_scale ? ph.cell_scale[c] : 1.0, D);
+    };
+#pragma omp parallel for schedule(static)
+    for (int64_t c = 0; c < n; ++c) {
+        double X[24], D[9], J[9], det, JiT[9];
+        corners_of(h, c, X);
+        tensor(c, D);
+        for (int iq = 0; iq < re.qc; ++iq) {
+            cell_map(d, X, &re.cq_xi[(size_t)iq * d], nullptr, J, &det, JiT);
+            const double w = re.cq_w[iq] * std::fabs(det);
+            vol[c] += w;
+            double* e = &M.cell[((size_t)c * re.qc + iq) * (symn + 1)];
+            for (int k = 0; k < d; ++k)
+                for (int l = k; l < d; ++l) {
+                    double s = 0.0;
+                    for (int a = 0; a < d; ++a)
+                        for (int b = 0; b < d; ++b) s += JiT[a * d + k] * D[a * d + b] * JiT[b * d + l];
+                    *e++ = w * s;
+                }
+            *e = cM * w;
+        }
+    }
+#pragma omp parallel for schedule(static)
+    for (int64_t f = 0; f < nf; ++f) {
+        const int64_t cp = F.plus[f], cm = F.minus[f];
+        const int ax = F.axis[f];
+        double Xp[24], Xm[24], Dp[9], Dm[9], J[9], detp, detm, JiTp[9], JiTm[9];
+        corners_of(h, cp, Xp);
+        corners_of(h, cm, Xm);
+        tensor(cp, Dp);
+        tensor(cm, Dm);
+        std::vector<double> nrm((size_t)qf * d), dS(qf);
+        double area = 0.0;
+        for (int iq = 0; iq < qf; ++iq) {
+            const size_t o = (size_t)ax * qf + iq;
+            cell_map(d, Xp, &fr.xi_p[o * d], nullptr, J, &detp, JiTp);
+            double nn = 0.0;
+            for (int a = 0; a < d; ++a) nn += JiTp[a * d + ax] * JiTp[a * d + ax];
+            nn = std::sqrt(nn);
+            for (int a = 0; a < d; ++a) nrm[(size_t)iq * d + a] = JiTp[a * d + ax] / nn;
+            dS[iq] = fr.w[o] * std::fabs(detp) * nn;
+            area += dS[iq];
+        }
+        const double eta = disc.penalty_mode == DGMG_PENALTY_FIXED
+                               ? disc.eta
+                               : (disc.eta > 0.0 ? disc.eta : 1.0) * re.p * (re.p + 1) * 0.5 *
+                                     (area / vol[cp] + area / vol[cm]);
+        for (int iq = 0; iq < qf; ++iq) {
+            const size_t o = (size_t)ax * qf + iq;
+            cell_map(d, Xp, &fr.xi_p[o * d], nullptr, J, &detp, JiTp);
+            cell_map(d, Xm, &fr.xi_m[o * d], nullptr, J, &detm, JiTm);
+            const double* nv = &nrm[(size_t)iq * d];
+            double Dnp[3] = {0, 0, 0}, Dnm[3] = {0, 0, 0}, nDn = 0.0;
+            for (int a = 0; a < d; ++a)
+                for (int k = 0; k < d; ++k) {
+                    Dnp[a] += Dp[a * d + k] * nv[k];
+                    Dnm[a] += Dm[a * d + k] * nv[k];
+                }
+            for (int a = 0; a < d; ++a) nDn += 0.5 * nv[a] * (Dnp[a] + Dnm[a]);
+            double* e = &M.face[((size_t)f * qf + iq) * (2 * d + 1)];
+            // reference directions: the normal axis, then the tangential ones
+            for (int r = 0; r < d; ++r) {
+                const int k = r == 0 ? ax : (r - 1 < ax ? r - 1 : r);
+                double gp = 0.0, gm = 0.0;
+                for (int a = 0; a < d; ++a) {
+                    gp += JiTp[a * d + k] * Dnp[a];
+                    gm += JiTm[a * d + k] * Dnm[a];
+                }
+                e[r] = -0.5 * dS[iq] * gp;
+                e[d + r] = -0.5 * dS[iq] * gm;
+            }
+            e[2 * d] = dS[iq] * eta * nDn;
+        }
+    }
+}
+
 }  // namespace dgmg

@@ -81,6 +81,17 @@ static double now_s() {
 
 static inline unsigned blocks_for(int64_t threads) { return (unsigned)((threads + kWG - 1) / kWG); }
 
+// Fine levels of distorted cells (p >= 2) hold metric data from this size on.
+// Below one cell per CU both forms take a launch and its latencies; at 576 Q2
+// squares a step takes 3.3 us against 3.7 us with stored blocks, at 65,536 5.9
+// against 12.0 us.
+constexpr int64_t kMinMappedCells = 256;
+// Agglomerated boxes whose blocks go to the cell kernels.  Their straight-line
+// products exceed the instruction cache from b = 25 on, which a small level
+// pays on every launch: a step at 1,024 cells of 25 DoFs (FP64) took 8.8 us
+// against 8.6 us by rows, at 1,000 of 27 DoFs 7.7 against 6.6 us, at 4,096 8.2
+// against 12.1 us; 1,600 cells of 9 DoFs 3.3 against 4.4 us.
+static int64_t min_stored_cells(int b) { return b <= 16 ? 1000 : 2000; }
 // coarse problems above this size are factorised on the device at set-up
 constexpr int64_t kHostCholeskyMax = 4096;
 
@@ -90,7 +101,9 @@ struct DevLevel {
     int32_t *slot_ptr = nullptr, *snb = nullptr;          // tile-ELL structure
     bool ax = false;                                       // axis-ELL layout instead
     bool sf = false;                                       // axis-ELL with sparse face blocks
-    bool mf = false;                                       // matrix-free boxes (fine level)
+    int geo = -1;                                          // evaluated per cell: GEO_* (cell.hpp)
+    double* data64 = nullptr;                              // entries of mapped and stored cells
+    float* data32 = nullptr;
     MfConst<double> mf64{};
     MfConst<float> mf32{};
     int32_t *up = nullptr, *lo = nullptr;                  // axis-ELL neighbours
@@ -125,6 +138,8 @@ struct dgmg_solver {
     double mf_h[3] = {0, 0, 0};
     double mf_cM = 0.0, mf_eta[3] = {0, 0, 0};
     std::vector<double> mf_D;
+    bool mapped = false;              // fine level as metric data (GEO_MAP)
+    MetricData metric;
     std::vector<int> axis0;           // axis of every fine face (face order of ops[0])
     // levels >= 1 whose agglomerates form a conforming grid of boxes: axis of
     // every face and whether its stored (plus, minus) order runs downwards
@@ -252,10 +267,10 @@ LevelArgs<float> largs<float>(const DevLevel& L) {
 template <typename T>
 static CellArgs<T> cargs(const DevLevel& L);
 template <>
-CellArgs<double> cargs<double>(const DevLevel& L) { return {L.up, L.lo, L.dinv64, L.n, L.mf64}; }
+CellArgs<double> cargs<double>(const DevLevel& L) { return {L.up, L.lo, L.dinv64, L.n, L.data64, L.mf64}; }
 template <>
-CellArgs<float> cargs<float>(const DevLevel& L) { return {L.up, L.lo, L.dinv32, L.n, L.mf32}; }
-static int level_ly(const DevLevel& L) { return L.mf ? LY_CELL : (L.ax ? (L.sf ? LY_AXS : LY_AXIS) : LY_TILE); }
+CellArgs<float> cargs<float>(const DevLevel& L) { return {L.up, L.lo, L.dinv32, L.n, L.data32, L.mf32}; }
+static int level_ly(const DevLevel& L) { return L.geo >= 0 ? LY_CELL : (L.ax ? (L.sf ? LY_AXS : LY_AXIS) : LY_TILE); }
 template <typename T>
 static const T* Pof(const DevLevel& L);
 template <>
@@ -315,7 +330,7 @@ static unsigned tiles_for(const DevLevel& L) {
 template <typename T>
 static unsigned level_tiles(const dgmg_solver* s, const DevLevel& L) {
     unsigned g = 0;
-    if (L.mf) return cell_groups(s->b, L.n);
+    if (L.geo >= 0) return cell_groups(s->b, L.n);
     DISPATCH_B(s->b, g = tiles_for<T, BV>(L));
     return g;
 }
@@ -323,9 +338,9 @@ template <typename T, int R = 1>
 static void launch_apply(dgmg_solver* s, const DevLevel& L, const T* va, T* y, const T* w,
                          double* partial, hipStream_t st) {
     ProfScope ps(s, PK_APPLY, level_index(s, L), st);
-    if (L.mf) {
-        if (R != 1) fail(DGMG_EUNSUPPORTED, "the matrix-free fine level has no multi-column kernels");
-        cell_apply<T>(ps.events(), s->b, cargs<T>(L), va, y, w, partial, st);
+    if (L.geo >= 0) {
+        if (R != 1) fail(DGMG_EUNSUPPORTED, "levels evaluated per cell have no multi-column kernels");
+        DISPATCH_GEO(L.geo, cell_apply<T, GEO>(ps.events(), s->b, cargs<T>(L), va, y, w, partial, st));
         return;
     }
     DISPATCH_LY(level_ly(L), {
@@ -347,9 +362,10 @@ static void launch_residual(dgmg_solver* s, const DevLevel& L, const T* va, cons
                             const T* bj = nullptr) {
     ProfScope ps(s, PK_RESIDUAL, level_index(s, L), st);
     if (R != 1 && bj) fail(DGMG_EUNSUPPORTED, "cell-block Jacobi is single-column only");
-    if (L.mf) {
-        if (R != 1) fail(DGMG_EUNSUPPORTED, "the matrix-free fine level has no multi-column kernels");
-        cell_residual<T>(ps.events(), s->b, cargs<T>(L), va, vb, rhs, r, d, c1, xout, partial, P, rp, ptype, bj, st);
+    if (L.geo >= 0) {
+        if (R != 1) fail(DGMG_EUNSUPPORTED, "levels evaluated per cell have no multi-column kernels");
+        DISPATCH_GEO(L.geo, cell_residual<T, GEO>(ps.events(), s->b, cargs<T>(L), va, vb, rhs, r, d, c1, xout, partial, P,
+                                                  rp, ptype, bj, st));
         return;
     }
     DISPATCH_LY(level_ly(L), {
@@ -401,9 +417,9 @@ static void launch_step(dgmg_solver* s, const DevLevel& L, const T* d, T* x, T* 
                         int assign, int last, hipStream_t st, const T* bj = nullptr) {
     ProfScope ps(s, PK_CHEB_STEP, level_index(s, L), st);
     if (R != 1 && bj) fail(DGMG_EUNSUPPORTED, "cell-block Jacobi is single-column only");
-    if (L.mf) {
-        if (R != 1) fail(DGMG_EUNSUPPORTED, "the matrix-free fine level has no multi-column kernels");
-        cell_step<T>(ps.events(), s->b, cargs<T>(L), d, x, r, dn, cd, cr, assign, last, bj, st);
+    if (L.geo >= 0) {
+        if (R != 1) fail(DGMG_EUNSUPPORTED, "levels evaluated per cell have no multi-column kernels");
+        DISPATCH_GEO(L.geo, cell_step<T, GEO>(ps.events(), s->b, cargs<T>(L), d, x, r, dn, cd, cr, assign, last, bj, st));
         return;
     }
     DISPATCH_LY(level_ly(L), {
@@ -1215,6 +1231,7 @@ static MfConst<T> mf_constants(const dgmg_solver* s, const RefElement& re, const
     for (int k = 0; k < s->dim; ++k) vol *= s->mf_h[k];
     C.vol = (T)vol;
     for (int k = 0; k < s->dim; ++k) {
+        if (!dev_D) break;   // tables only
         C.hinv[k] = (T)(1.0 / s->mf_h[k]);
         C.area[k] = (T)(vol / s->mf_h[k]);
         C.eta[k] = (T)s->mf_eta[k];
@@ -1223,6 +1240,57 @@ static MfConst<T> mf_constants(const dgmg_solver* s, const RefElement& re, const
     C.D = dev_D;
     return C;
 }
+
+// Entries of the cells of a level in the cell kernels' order: groups of 16
+// bytes, 64 cells interleaved (kernels_cell.hpp).  cell(c, e) and
+// face(c, a, e) give entry e of cell c and of the face on its upper a-side.
+template <typename T, typename FC, typename FF>
+static std::vector<T> pack_cells(int64_t n, int d, int nec, int nef, FC&& cell, FF&& face) {
+    const int W = 16 / sizeof(T), gc = (nec + W - 1) / W, gf = (nef + W - 1) / W, ng = gc + d * gf;
+    std::vector<T> out((size_t)((n + 63) / 64) * ng * 64 * W, (T)0);
+#pragma omp parallel for schedule(static)
+    for (int64_t c = 0; c < n; ++c) {
+        T* base = &out[(size_t)(c / 64) * ng * 64 * W + (size_t)(c % 64) * W];
+        for (int e = 0; e < nec; ++e) base[(size_t)(e / W) * 64 * W + e % W] = (T)cell(c, e);
+        for (int a = 0; a < d; ++a)
+            for (int e = 0; e < nef; ++e)
+                base[(size_t)(gc + a * gf + e / W) * 64 * W + e % W] = (T)face(c, a, e);
+    }
+    return out;
+}
+// face on the upper a-side of each cell (-1: none), [d][n]
+static std::vector<int64_t> upper_faces(const BlockOp& A, const std::vector<int>& axis, int d) {
+    std::vector<int64_t> up((size_t)d * A.n, -1);
+    for (int64_t f = 0; f < A.nf; ++f) up[(size_t)axis[f] * A.n + A.fc[2 * f]] = f;
+    return up;
+}
+template <typename T>
+static std::vector<T> pack_metric(const BlockOp& A, const MetricData& M, const std::vector<int64_t>& up, int d) {
+    return pack_cells<T>(A.n, d, M.nec, M.nef, [&](int64_t c, int e) { return M.cell[(size_t)c * M.nec + e]; },
+                         [&](int64_t c, int a, int e) {
+                             const int64_t f = up[(size_t)a * A.n + c];
+                             return f < 0 ? 0.0 : M.face[(size_t)f * M.nef + e];
+                         });
+}
+template <typename T>
+static std::vector<T> pack_blocks(const BlockOp& A, const std::vector<int64_t>& up, int d) {
+    const int b = A.b, q = ax_nodes_1d(b, d), nf = b / q;
+    std::vector<int> tri, fl[3];
+    for (int i = 0; i < b; ++i)
+        for (int j = 0; j < b; ++j) {
+            if (j >= i) tri.push_back(i * b + j);
+            for (int a = 0; a < d; ++a)
+                if (face_entry(i, j, a, q)) fl[a].push_back(i * b + j);
+        }
+    return pack_cells<T>(A.n, d, (int)tri.size(), 2 * nf * b - nf * nf,
+                         [&](int64_t c, int e) { return A.diag[(size_t)c * b * b + tri[e]]; },
+                         [&](int64_t c, int a, int e) {
+                             const int64_t f = up[(size_t)a * A.n + c];
+                             return f < 0 ? 0.0 : A.fblk[(size_t)f * b * b + fl[a][e]];
+                         });
+}
+// block sizes of the cell kernels on mapped and stored cells
+static bool cell_block_size(int b) { return b == 9 || b == 16 || b == 25 || b == 27; }
 
 static void upload_level(dgmg_solver* s, int l) {
     const BlockOp& A = s->ops[l];
@@ -1241,8 +1309,9 @@ static void upload_level(dgmg_solver* s, int l) {
     const bool ax = l == 0 && !mf && s->fine_layout != DGMG_LAYOUT_TILE_ELL && !s->axis0.empty();
     // agglomerated levels that form a conforming grid of boxes also store each
     // face block once (faces reoriented from the lower to the upper box)
-    bool axc = false;
+    bool axc = false, blk = false;
     AxisEll Ec;
+    std::vector<int64_t> upf;
     if (l > 0 && !last && s->fine_layout != DGMG_LAYOUT_TILE_ELL && (size_t)l < s->axisl.size() &&
         !s->axisl[l].empty()) {
         BlockOp Ao;
@@ -1261,7 +1330,19 @@ static void upload_level(dgmg_solver* s, int l) {
                     for (int j = i + 1; j < b; ++j) std::swap(blk[i * b + j], blk[j * b + i]);
             }
         try {
-            Ec = build_axis_ell(Ao, s->axisl[l], s->dim, true);
+            // above identical boxes the agglomerates are boxes with nodal
+            // bases: their blocks go to the cell kernels
+            if (s->fine_layout == DGMG_LAYOUT_MATRIX_FREE && cell_block_size(b) && A.n >= min_stored_cells(b)) {
+                Ec = build_axis_ell(Ao, s->axisl[l], s->dim, false);
+                upf = upper_faces(Ao, s->axisl[l], s->dim);
+                blk = faces_are_nodal(Ao, upf, s->dim);
+            }
+            if (blk) {
+                L.data64 = s->upload(pack_blocks<double>(Ao, upf, s->dim));
+                if (s->prec == DGMG_PREC_MIXED) L.data32 = s->upload(pack_blocks<float>(Ao, upf, s->dim));
+            } else {
+                Ec = build_axis_ell(Ao, s->axisl[l], s->dim, true);
+            }
             axc = true;
         } catch (const Error& e) {
             if (e.code != DGMG_EUNSUPPORTED) throw;   // two faces on one side: keep tile-ELL
@@ -1270,7 +1351,7 @@ static void upload_level(dgmg_solver* s, int l) {
     if (mf) {
         // neighbours as in the axis-ELL layout; no operator values are stored
         AxisEll E = build_axis_ell(A, s->axis0, s->dim, false);
-        L.mf = true;
+        L.geo = GEO_BOX;
         L.up = s->upload(E.up);
         L.lo = s->upload(E.lo);
         L.dinv64 = s->upload(dinv);
@@ -1280,6 +1361,23 @@ static void upload_level(dgmg_solver* s, int l) {
         if (s->prec == DGMG_PREC_MIXED) {
             L.dinv32 = s->upload(convert<float>(dinv));
             L.mf32 = mf_constants<float>(s, re, s->upload(convert<float>(s->mf_D)));
+        }
+    } else if (blk || (l == 0 && s->mapped)) {
+        AxisEll E = blk ? std::move(Ec) : build_axis_ell(A, s->axis0, s->dim, false);
+        L.geo = blk ? GEO_BLK : GEO_MAP;
+        L.up = s->upload(E.up);
+        L.lo = s->upload(E.lo);
+        L.dinv64 = s->upload(dinv);
+        if (s->prec == DGMG_PREC_MIXED) L.dinv32 = s->upload(convert<float>(dinv));
+        if (!blk) {
+            RefElement re;
+            re.init(s->dim, s->p);
+            upf = upper_faces(A, s->axis0, s->dim);
+            L.mf64 = mf_constants<double>(s, re, nullptr);
+            L.mf32 = mf_constants<float>(s, re, nullptr);
+            L.data64 = s->upload(pack_metric<double>(A, s->metric, upf, s->dim));
+            if (s->prec == DGMG_PREC_MIXED) L.data32 = s->upload(pack_metric<float>(A, s->metric, upf, s->dim));
+            s->metric = MetricData();
         }
     } else if (ax || axc) {
         // single-column solvers store nodal fine face blocks in sparse form
@@ -1704,6 +1802,9 @@ int dgmg_setup_levels(const dgmg_hierarchy* h, const dgmg_disc* disc, const dgmg
     // solvers), the axis-ELL blocks otherwise
     if (s->fine_layout == DGMG_LAYOUT_AUTO && s->p >= 2 && s->max_rhs == 1 && uniform_boxes(*h, s->mf_h))
         s->fine_layout = DGMG_LAYOUT_MATRIX_FREE;
+    s->mapped = s->fine_layout == DGMG_LAYOUT_AUTO && s->max_rhs == 1 && cell_block_size(s->b) && s->L > 1 &&
+                h->n_cells >= kMinMappedCells && mg->device_setup;
+    if (s->mapped) metric_data(*h, F, re, *disc, *ph, cM, s->metric);
     if (s->fine_layout == DGMG_LAYOUT_MATRIX_FREE) {
         if (!uniform_boxes(*h, s->mf_h))
             fail(DGMG_EUNSUPPORTED, "the matrix-free fine level needs identical axis-aligned box cells");
@@ -1869,8 +1970,8 @@ int dgmg_setup_levels(const dgmg_hierarchy* h, const dgmg_disc* disc, const dgmg
     for (int l = 0; l < s->L; ++l) {
         const DevLevel& Lv = s->lv[l];
         s->info.level_layout[l] = !s->on_device || (l == s->L - 1 && s->L > 1) ? 0
-                                  : Lv.mf ? DGMG_LAYOUT_MATRIX_FREE
-                                  : Lv.ax ? DGMG_LAYOUT_AXIS_ELL : DGMG_LAYOUT_TILE_ELL;
+                                  : Lv.geo == GEO_BOX || Lv.geo == GEO_MAP ? DGMG_LAYOUT_MATRIX_FREE
+                                  : Lv.ax || Lv.geo == GEO_BLK ? DGMG_LAYOUT_AXIS_ELL : DGMG_LAYOUT_TILE_ELL;
     }
     s->info.fine_layout = s->info.level_layout[0];
     for (int l = 0; l < s->L; ++l) s->info.prolong_types[l] = s->on_device ? s->lv[l].ntypes : 0;

@@ -1,0 +1,82 @@
+"""Cell kernels on distorted cells (metric data at the Gauss points) and on the
+stored blocks of agglomerated boxes: operator rows against the oracle, and
+V-cycles and level products against the row kernels of the axis layout."""
+import numpy as np
+import pytest
+
+from gpu_util import dev, host, need_gpu, rel, say, torch
+from oracle.assemble import assemble
+from paper_2602_16312_amd import api, problem
+from workloads import make_problem
+
+pytestmark = pytest.mark.gpu
+CUBE = dict(jitter=0.1, seed=3, penalty=("paper", 2.0))
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    need_gpu()
+
+
+# 256, 289, 4,225 squares (Q2, Q3, Q4) and 343, 4,913 hexahedra: both group sizes, ragged groups
+@pytest.mark.parametrize("name,kw", [
+    ("c2", dict(n=16, group=[4])), ("c2", dict(n=17, p=3, jitter=0.1, group=[17])),
+    ("c2", dict(n=17, p=4, jitter=0.1, penalty=("fixed", 900.0), group=[17])),
+    ("c2", dict(n=65, group=[13])), ("c2", dict(n=65, p=3, jitter=0.1, group=[13])),
+    ("c2", dict(n=65, p=4, jitter=0.1, group=[13])), ("c3", dict(n=7, group=[7], **CUBE)),
+    ("c3", dict(n=17, group=[17], **CUBE))])
+def test_mapped_rows_match_oracle(name, kw):
+    pr = make_problem(name, **kw)
+    n, b = pr["n_cells"], pr["b"]
+    scale = np.random.default_rng(3).uniform(0.5, 2.0, n)
+    h, s = problem.build(pr, precision="mixed", cell_scale=scale)
+    assert s.info()["fine_layout"] == "matrix_free"
+    rng = np.random.default_rng(4)
+    cells = np.unique(np.concatenate([[0, 15, 16, 63, 64, n - 1, n - 2], rng.integers(0, n, 24)]) % n)
+    M, A = assemble(pr, scale, row_cells=cells)
+    rows = (cells[:, None] * b + np.arange(b)).ravel()
+    x = rng.standard_normal(pr["N"])
+    ref = ((1.5 * pr["chi"] * pr["Cm"] / pr["dt"]) * M + A)[rows] @ x
+    y = torch.empty(pr["N"], dtype=torch.float64, device="cuda")
+    for prec, tol in (("fp64", 1e-13), ("mixed", 3e-6)):   # as for the operator on boxes
+        say("mapped rows", name, kw, prec)
+        api.apply(s, 0, dev(x), y, prec)
+        assert rel(host(y)[rows], ref) <= tol, prec
+
+
+@pytest.mark.parametrize("mg", [dict(), dict(cheb_degree=1), dict(jacobi="cell_block"),
+                                dict(cheb_degree=1, jacobi="cell_block")])
+@pytest.mark.parametrize("name,kw", [("c2", dict(n=20, group=[4])), ("c3", dict(n=8, group=[2], **CUBE))])
+def test_mapped_vcycle_matches_blocks(name, kw, mg):
+    pr = make_problem(name, **kw)
+    r = dev(np.random.default_rng(2).standard_normal(pr["N"]))
+    z = [torch.empty_like(r) for _ in range(2)]
+    for prec, tol in (("fp64", 1e-11), ("mixed", 2e-5)):   # as against the oracle's V-cycle
+        lam = None
+        for k, layout in enumerate(("axis_ell", "auto")):
+            h, s = problem.build(pr, precision=prec, fine_layout=layout, lam_override=lam, **mg)
+            i = s.info()
+            lam = np.stack([i["lam_lo"][:-1], i["lam_hi"][:-1]], axis=1)
+            say("mapped vcycle", name, mg, prec, layout)
+            api.vcycle(s, r, z[k])
+        assert rel(host(z[1]), host(z[0])) <= tol, prec
+
+
+# level 1: 1,024 boxes of 9 and 16 DoFs, 2,704 of 25, 2,197 of 27
+@pytest.mark.parametrize("name,kw", [
+    ("e1", dict(n=64, p=2, group=[2, 8])), ("e1", dict(n=64, p=3, group=[2, 8])),
+    ("e1", dict(n=104, p=4, group=[2, 13])), ("c3", dict(n=26, group=[2, 13]))])
+def test_stored_boxes_match_rows(name, kw):
+    pr = make_problem(name, **kw)
+    out = {}
+    for layout in ("axis_ell", "auto"):
+        h, s = problem.build(pr, precision="mixed", fine_layout=layout)
+        n = s.info()["n_cells"][1] * pr["b"]
+        x = dev(np.random.default_rng(5).standard_normal(n))
+        for prec in ("fp64", "mixed"):
+            y = torch.empty_like(x)
+            say("stored boxes", name, layout, prec)
+            api.apply(s, 1, x, y, prec)
+            out[layout, prec] = host(y)
+    assert rel(out["auto", "fp64"], out["axis_ell", "fp64"]) <= 1e-13
+    assert rel(out["auto", "mixed"], out["axis_ell", "fp64"]) <= 3e-6
