@@ -175,11 +175,13 @@ enum { DGMG_PREC_FP64 = 0, DGMG_PREC_MIXED = 1 };
  * stores every face block once (per cell: its block and the blocks of its
  * upper faces along each axis; lower faces are read transposed from the
  * neighbour), TILE_ELL stores each face block twice, oriented for both
- * cells, as on the agglomerated levels; AUTO takes MATRIX_FREE for p >= 2 on
- * meshes of identical boxes with max_rhs <= 1; on other meshes with p >= 2
- * (not 3D Q3), max_rhs <= 1, at least 256 cells and a second level it keeps
- * metric data at the Gauss points and evaluates the operator from them
- * (reported as MATRIX_FREE); AXIS_ELL otherwise.  With
+ * cells, as on the agglomerated levels.  AUTO with max_rhs <= 1 takes
+ * MATRIX_FREE on meshes of identical boxes (p >= 2, and p = 1 from 256 cells
+ * on); on other meshes of at least 256 cells and two levels it keeps metric
+ * data at the Gauss points and evaluates the operator from them: p >= 2 (not
+ * 3D Q3) for cells and faces, reported as MATRIX_FREE, p = 1 for the faces
+ * beside the cell blocks, reported as AXIS_ELL.  Otherwise AUTO takes
+ * AXIS_ELL.  With
  * max_rhs <= 1, AXIS_ELL stores nodal face blocks in sparse form (see
  * dgmg_solver_info.sparse_faces); AXIS_ELL_DENSE keeps every face block
  * whole.

@@ -29,9 +29,10 @@ struct MfConst {
     const T* D;                // per cell: packed symmetric D (d(d+1)/2 values)
 };
 // How a level's cells are evaluated: identical boxes, bilinear / trilinear
-// cells with their metric data at the Gauss points, or stored blocks of a
-// nodal level on a conforming grid of boxes.
-enum { GEO_BOX = 0, GEO_MAP = 1, GEO_BLK = 2 };
+// cells with their metric data at the Gauss points, stored blocks of a nodal
+// level on a conforming grid of boxes, or stored cell blocks (with the cell's
+// own face terms) and metric data at the faces' Gauss points.
+enum { GEO_BOX = 0, GEO_MAP = 1, GEO_BLK = 2, GEO_HYB = 3 };
 
 // entry (i, j) of a nodal face block along axis a: node i on the lower cell's
 // upper face or node j on the upper cell's lower face
@@ -42,8 +43,10 @@ __host__ __device__ constexpr bool face_entry(int i, int j, int a, int q) {
 template <int B, int GEO>
 struct CellPack {
     static constexpr int D = dim_of<B>(), Q = ax_nodes_1d(B, D), QN = B / Q;
-    static constexpr int NEC = GEO == GEO_MAP ? B * (D * (D + 1) / 2 + 1) : GEO == GEO_BLK ? B * (B + 1) / 2 : 0;
-    static constexpr int NEF = GEO == GEO_MAP ? QN * (2 * D + 1) : GEO == GEO_BLK ? 2 * QN * B - QN * QN : 0;
+    static constexpr int NEC = GEO == GEO_MAP ? B * (D * (D + 1) / 2 + 1)
+                               : GEO == GEO_BLK || GEO == GEO_HYB ? B * (B + 1) / 2 : 0;
+    static constexpr int NEF = GEO == GEO_MAP || GEO == GEO_HYB ? QN * (2 * D + 1)
+                               : GEO == GEO_BLK ? 2 * QN * B - QN * QN : 0;
     static constexpr int cell_groups(int w) { return (NEC + w - 1) / w; }
     static constexpr int face_groups(int w) { return (NEF + w - 1) / w; }
     static constexpr int groups(int w) { return cell_groups(w) + D * face_groups(w); }
@@ -80,7 +83,8 @@ void cell_step(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* d, 
     switch (gval) {                                                                    \
         case GEO_BOX: { constexpr int GEO = GEO_BOX; __VA_ARGS__; } break;             \
         case GEO_MAP: { constexpr int GEO = GEO_MAP; __VA_ARGS__; } break;             \
-        default: { constexpr int GEO = GEO_BLK; __VA_ARGS__; } break;                  \
+        case GEO_BLK: { constexpr int GEO = GEO_BLK; __VA_ARGS__; } break;             \
+        default: { constexpr int GEO = GEO_HYB; __VA_ARGS__; } break;                  \
     }
 
 }  // namespace dgmg

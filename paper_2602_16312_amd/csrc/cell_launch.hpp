@@ -16,16 +16,20 @@ static int cells_per_group(int b, int n) { return b == 64 || n <= 16 * 256 ? 16 
 #define DISPATCH_CELL(bval, nval, ...)                                                        \
     if constexpr (GEO == GEO_BOX) {                                                           \
         if ((bval) == 64) { constexpr int BV = 64, NC = 16; __VA_ARGS__; return; }            \
+    }                                                                                         \
+    if constexpr (GEO == GEO_BOX || GEO == GEO_HYB) {                                         \
         if ((bval) == 4) { DISPATCH_NC(4, nval, __VA_ARGS__) return; }                        \
         if ((bval) == 8) { DISPATCH_NC(8, nval, __VA_ARGS__) return; }                        \
     }                                                                                         \
-    switch (bval) {                                                                           \
-        case 9: { DISPATCH_NC(9, nval, __VA_ARGS__) } break;                                  \
-        case 16: { DISPATCH_NC(16, nval, __VA_ARGS__) } break;                                \
-        case 25: { DISPATCH_NC(25, nval, __VA_ARGS__) } break;                                \
-        case 27: { DISPATCH_NC(27, nval, __VA_ARGS__) } break;                                \
-        default: fail(DGMG_EUNSUPPORTED, "unsupported block size");                           \
-    }
+    if constexpr (GEO != GEO_HYB) {                                                           \
+        switch (bval) {                                                                       \
+            case 9: { DISPATCH_NC(9, nval, __VA_ARGS__) } return;                             \
+            case 16: { DISPATCH_NC(16, nval, __VA_ARGS__) } return;                           \
+            case 25: { DISPATCH_NC(25, nval, __VA_ARGS__) } return;                           \
+            case 27: { DISPATCH_NC(27, nval, __VA_ARGS__) } return;                           \
+        }                                                                                     \
+    }                                                                                         \
+    fail(DGMG_EUNSUPPORTED, "unsupported block size");
 #define DISPATCH_NC(bval, nval, ...)                                                          \
     constexpr int BV = bval;                                                                  \
     if (cells_per_group(BV, nval) == 16) { constexpr int NC = 16; __VA_ARGS__; }              \

@@ -531,7 +531,7 @@ __device__ __forceinline__ void map_face_terms(const CellArgs<T>& L, int c, cons
 // read coalesced, also by the cell above a face, whose transposed reads by a
 // thread per row touched a line per lane: level 1 of the 64^3 Q2 cube (32,768
 // boxes of 27 DoFs, 209 MB of entries), FP32 step 92 -> 42 us, FP64 260 -> 94.
-template <typename T, int B, int NC, bool VB>
+template <typename T, int B, int NC, bool VB, int GEO>
 __device__ __forceinline__ void blk_cell_terms(const CellArgs<T>& L, int c, const T* __restrict__ va,
                                                const T* __restrict__ vb, T* ys) {
     T x[B], y[B];
@@ -539,7 +539,7 @@ __device__ __forceinline__ void blk_cell_terms(const CellArgs<T>& L, int c, cons
 #pragma unroll
     for (int i = 0; i < B; ++i) y[i] = 0;
     constexpr TriList<B> tri;
-    stream_entries<T, B*(B + 1) / 2, ring_groups<T>()>(cell_data<T, B, GEO_BLK>(L, c, 0), [&](int e, T a) {
+    stream_entries<T, B*(B + 1) / 2, ring_groups<T>()>(cell_data<T, B, GEO>(L, c, 0), [&](int e, T a) {
         const int i = tri.i[e], j = tri.j[e];
         y[i] += a * x[j];
         if (j > i) y[j] += a * x[i];
@@ -573,16 +573,96 @@ __device__ __forceinline__ void blk_face_terms(const CellArgs<T>& L, int c, cons
     for (int i = 0; i < B; ++i) ys[i] = y[i];
 }
 
+// ---- Q1 cells: the stored cell block holds the cell's own face terms, and
+// the neighbours' terms come from the faces' metric data (28 values per 3D
+// face against 48 nonzeros of its block): map_face_terms with u_own = 0.
+template <typename T, int B, bool VB, int A>
+__device__ __forceinline__ void hyb_face_terms(const CellArgs<T>& L, int c, const T* __restrict__ va,
+                                               const T* __restrict__ vb, T* ys) {
+    using P = CellPack<B, GEO_HYB>;
+    constexpr int D = P::D, Q = P::Q, QN = P::QN, SA = ipow(Q, A);
+    constexpr int t1 = A == 0 ? 1 : 0, t2 = D == 3 ? (A == 2 ? 1 : 2) : t1;
+    constexpr int S1 = ipow(Q, t1), S2 = D == 3 ? ipow(Q, t2) : 0;
+    constexpr int NE = 2 * D + 1, W = 16 / sizeof(T);
+    const MfConst<T>& C = L.mf;
+    const int lo = L.lo[(size_t)A * L.n + c], up = L.up[(size_t)A * L.n + c];
+    const int nb[2] = {lo >= 0 ? lo : c, up};
+    const bool has[2] = {lo >= 0, up != c};
+    T T0[2][QN], Tn[2][QN];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        T xn[B], un[QN], dn[QN], acc[QN], cn[QN];
+        load_cell<T, B, VB>(va, vb, nb[s], xn);
+        Stream<T, NE * QN> F(cell_data<T, B, GEO_HYB>(L, s ? c : nb[0], P::cell_groups(W) + A * P::face_groups(W)));
+#pragma unroll
+        for (int m = 0; m < QN; ++m) {
+            const int J0 = (m % Q) * S1 + (m / Q) * S2;
+            T b = 0;
+#pragma unroll
+            for (int j = 0; j < Q; ++j) b += C.Ed[(1 - s) * Q + j] * xn[J0 + j * SA];
+            dn[m] = b;
+            un[m] = xn[J0 + (1 - s) * (Q - 1) * SA];
+            acc[m] = 0;
+        }
+        all_passes<T, Q, D - 1, false>(un, C.Ig);
+        all_passes<T, Q, D - 1, false>(dn, C.Ig);
+#pragma unroll
+        for (int q = 0; q < QN; ++q) {
+            const int q1 = q % Q, q2 = q / Q;
+            T f[NE];
+#pragma unroll
+            for (int k = 0; k < NE; ++k) f[k] = F.get(q * NE + k);
+            const T* o = s ? f : f + D;                   // own weights, then the neighbour's
+            const T* v = s ? f + D : f;
+            T val = v[0] * dn[q] - (s ? f[2 * D] : -f[2 * D]) * un[q];
+            const T js = s ? -un[q] : un[q];
+#pragma unroll
+            for (int h = 0; h < Q; ++h) {
+                const int m = h + Q * q2;
+                val += C.Gc[q1 * Q + h] * (v[1] * un[m]);
+                acc[m] += C.Gc[q1 * Q + h] * (o[1] * js);
+                if constexpr (D == 3) {
+                    const int n = q1 + Q * h;
+                    val += C.Gc[q2 * Q + h] * (v[2] * un[n]);
+                    acc[n] += C.Gc[q2 * Q + h] * (o[2] * js);
+                }
+            }
+            acc[q] += s ? val : -val;
+            cn[q] = o[0] * js;
+        }
+        all_passes<T, Q, D - 1, true>(acc, C.Ig);
+        all_passes<T, Q, D - 1, true>(cn, C.Ig);
+#pragma unroll
+        for (int m = 0; m < QN; ++m) {
+            T0[s][m] = has[s] ? acc[m] : T(0);
+            Tn[s][m] = has[s] ? cn[m] : T(0);
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < QN; ++m) {
+        const int J0 = (m % Q) * S1 + (m / Q) * S2;
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            T v = C.Ed[j] * Tn[0][m] + C.Ed[Q + j] * Tn[1][m];
+            if (j == 0) v += T0[0][m];
+            if (j == Q - 1) v += T0[1][m];
+            ys[J0 + j * SA] = v;
+        }
+    }
+}
+
 template <typename T, int B, int NC, bool VB, int GEO>
 __device__ __forceinline__ void cell_terms(const CellArgs<T>& L, int c, const T* __restrict__ va,
                                            const T* __restrict__ vb, T* ys) {
     if constexpr (GEO == GEO_BOX) box_cell_terms<T, B, NC, VB>(L, c, va, vb, ys);
+    else if constexpr (GEO == GEO_HYB) blk_cell_terms<T, B, NC, VB, GEO>(L, c, va, vb, ys);
     else map_cell_terms<T, B, NC, VB>(L, c, va, vb, ys);
 }
 template <typename T, int B, int NC, bool VB, int GEO, int A>
 __device__ __forceinline__ void face_terms(const CellArgs<T>& L, int c, const T* __restrict__ va,
                                            const T* __restrict__ vb, T* ys) {
     if constexpr (GEO == GEO_BOX) box_face_terms<T, B, NC, VB, A>(L, c, va, vb, ys);
+    else if constexpr (GEO == GEO_HYB) hyb_face_terms<T, B, VB, A>(L, c, va, vb, ys);
     else map_face_terms<T, B, NC, VB, A>(L, c, va, vb, ys);
 }
 
@@ -780,7 +860,7 @@ __device__ __forceinline__ void cell_product(const CellArgs<T>& L, int cell0, co
     const int c = min(cell0 + lane, L.n - 1);
     T* ys = sh + (w * Ct::NC + lane) * Ct::SB;
     if constexpr (GEO == GEO_BLK) {
-        if (w == 0) blk_cell_terms<T, B, NC, VB>(L, c, va, vb, ys);
+        if (w == 0) blk_cell_terms<T, B, NC, VB, GEO>(L, c, va, vb, ys);
         else if (w == 1) blk_face_terms<T, B, VB, 0, 0>(L, c, va, vb, ys);
         else if (w == 2) blk_face_terms<T, B, VB, 0, 1>(L, c, va, vb, ys);
         else if (w == 3) blk_face_terms<T, B, VB, 1, 0>(L, c, va, vb, ys);

@@ -84,7 +84,8 @@ static inline unsigned blocks_for(int64_t threads) { return (unsigned)((threads 
 // Fine levels of distorted cells (p >= 2) hold metric data from this size on.
 // Below one cell per CU both forms take a launch and its latencies; at 576 Q2
 // squares a step takes 3.3 us against 3.7 us with stored blocks, at 65,536 5.9
-// against 12.0 us.
+// against 12.0 us.  p = 1, 1,024 squares 2.7 against 3.7 us (FP64), boxes 2.6 us;
+// the shell of 1.0M hexahedra 148 against 214 us.
 constexpr int64_t kMinMappedCells = 256;
 // Agglomerated boxes whose blocks go to the cell kernels.  Their straight-line
 // products exceed the instruction cache from b = 25 on, which a small level
@@ -1272,16 +1273,33 @@ static std::vector<T> pack_metric(const BlockOp& A, const MetricData& M, const s
                              return f < 0 ? 0.0 : M.face[(size_t)f * M.nef + e];
                          });
 }
+// upper triangle of the cell block in row order
+static std::vector<int> triangle(int b) {
+    std::vector<int> tri;
+    for (int i = 0; i < b; ++i)
+        for (int j = i; j < b; ++j) tri.push_back(i * b + j);
+    return tri;
+}
+template <typename T>
+static std::vector<T> pack_hybrid(const BlockOp& A, const MetricData& M, const std::vector<int64_t>& up, int d) {
+    const int b = A.b;
+    const std::vector<int> tri = triangle(b);
+    return pack_cells<T>(A.n, d, (int)tri.size(), M.nef,
+                         [&](int64_t c, int e) { return A.diag[(size_t)c * b * b + tri[e]]; },
+                         [&](int64_t c, int a, int e) {
+                             const int64_t f = up[(size_t)a * A.n + c];
+                             return f < 0 ? 0.0 : M.face[(size_t)f * M.nef + e];
+                         });
+}
 template <typename T>
 static std::vector<T> pack_blocks(const BlockOp& A, const std::vector<int64_t>& up, int d) {
     const int b = A.b, q = ax_nodes_1d(b, d), nf = b / q;
-    std::vector<int> tri, fl[3];
+    const std::vector<int> tri = triangle(b);
+    std::vector<int> fl[3];
     for (int i = 0; i < b; ++i)
-        for (int j = 0; j < b; ++j) {
-            if (j >= i) tri.push_back(i * b + j);
+        for (int j = 0; j < b; ++j)
             for (int a = 0; a < d; ++a)
                 if (face_entry(i, j, a, q)) fl[a].push_back(i * b + j);
-        }
     return pack_cells<T>(A.n, d, (int)tri.size(), 2 * nf * b - nf * nf,
                          [&](int64_t c, int e) { return A.diag[(size_t)c * b * b + tri[e]]; },
                          [&](int64_t c, int a, int e) {
@@ -1290,7 +1308,7 @@ static std::vector<T> pack_blocks(const BlockOp& A, const std::vector<int64_t>& 
                          });
 }
 // block sizes of the cell kernels on mapped and stored cells
-static bool cell_block_size(int b) { return b == 9 || b == 16 || b == 25 || b == 27; }
+static bool cell_block_size(int b) { return b == 4 || b == 8 || b == 9 || b == 16 || b == 25 || b == 27; }
 
 static void upload_level(dgmg_solver* s, int l) {
     const BlockOp& A = s->ops[l];
@@ -1332,7 +1350,7 @@ static void upload_level(dgmg_solver* s, int l) {
         try {
             // above identical boxes the agglomerates are boxes with nodal
             // bases: their blocks go to the cell kernels
-            if (s->fine_layout == DGMG_LAYOUT_MATRIX_FREE && cell_block_size(b) && A.n >= min_stored_cells(b)) {
+            if (s->fine_layout == DGMG_LAYOUT_MATRIX_FREE && b >= 9 && cell_block_size(b) && A.n >= min_stored_cells(b)) {
                 Ec = build_axis_ell(Ao, s->axisl[l], s->dim, false);
                 upf = upper_faces(Ao, s->axisl[l], s->dim);
                 blk = faces_are_nodal(Ao, upf, s->dim);
@@ -1364,7 +1382,8 @@ static void upload_level(dgmg_solver* s, int l) {
         }
     } else if (blk || (l == 0 && s->mapped)) {
         AxisEll E = blk ? std::move(Ec) : build_axis_ell(A, s->axis0, s->dim, false);
-        L.geo = blk ? GEO_BLK : GEO_MAP;
+        const bool hyb = !blk && s->p == 1;
+        L.geo = blk ? GEO_BLK : hyb ? GEO_HYB : GEO_MAP;
         L.up = s->upload(E.up);
         L.lo = s->upload(E.lo);
         L.dinv64 = s->upload(dinv);
@@ -1375,8 +1394,11 @@ static void upload_level(dgmg_solver* s, int l) {
             upf = upper_faces(A, s->axis0, s->dim);
             L.mf64 = mf_constants<double>(s, re, nullptr);
             L.mf32 = mf_constants<float>(s, re, nullptr);
-            L.data64 = s->upload(pack_metric<double>(A, s->metric, upf, s->dim));
-            if (s->prec == DGMG_PREC_MIXED) L.data32 = s->upload(pack_metric<float>(A, s->metric, upf, s->dim));
+            L.data64 = s->upload(hyb ? pack_hybrid<double>(A, s->metric, upf, s->dim)
+                                     : pack_metric<double>(A, s->metric, upf, s->dim));
+            if (s->prec == DGMG_PREC_MIXED)
+                L.data32 = s->upload(hyb ? pack_hybrid<float>(A, s->metric, upf, s->dim)
+                                         : pack_metric<float>(A, s->metric, upf, s->dim));
             s->metric = MetricData();
         }
     } else if (ax || axc) {
@@ -1798,9 +1820,11 @@ int dgmg_setup_levels(const dgmg_hierarchy* h, const dgmg_disc* disc, const dgmg
         ds->assemble_fine(F, re, *disc, *ph, cM, s->ops[0], s->mass_h);
     else
         assemble_fine(*h, F, re, *disc, *ph, cM, s->ops[0], s->mass_h, want_adj ? &adj : nullptr);
-    // AUTO: matrix-free on meshes of identical boxes for p >= 2 (single-column
-    // solvers), the axis-ELL blocks otherwise
-    if (s->fine_layout == DGMG_LAYOUT_AUTO && s->p >= 2 && s->max_rhs == 1 && uniform_boxes(*h, s->mf_h))
+    // AUTO (single column): matrix-free on meshes of identical boxes for p >= 2,
+    // and for p = 1 from kMinMappedCells on; metric data on other meshes from
+    // that size on (p = 1: beside the cell blocks); else the axis-ELL blocks
+    if (s->fine_layout == DGMG_LAYOUT_AUTO && s->max_rhs == 1 &&
+        (s->p >= 2 || (s->L > 1 && h->n_cells >= kMinMappedCells)) && uniform_boxes(*h, s->mf_h))
         s->fine_layout = DGMG_LAYOUT_MATRIX_FREE;
     s->mapped = s->fine_layout == DGMG_LAYOUT_AUTO && s->max_rhs == 1 && cell_block_size(s->b) && s->L > 1 &&
                 h->n_cells >= kMinMappedCells && mg->device_setup;
@@ -1971,7 +1995,7 @@ int dgmg_setup_levels(const dgmg_hierarchy* h, const dgmg_disc* disc, const dgmg
         const DevLevel& Lv = s->lv[l];
         s->info.level_layout[l] = !s->on_device || (l == s->L - 1 && s->L > 1) ? 0
                                   : Lv.geo == GEO_BOX || Lv.geo == GEO_MAP ? DGMG_LAYOUT_MATRIX_FREE
-                                  : Lv.ax || Lv.geo == GEO_BLK ? DGMG_LAYOUT_AXIS_ELL : DGMG_LAYOUT_TILE_ELL;
+                                  : Lv.ax || Lv.geo == GEO_BLK || Lv.geo == GEO_HYB ? DGMG_LAYOUT_AXIS_ELL : DGMG_LAYOUT_TILE_ELL;
     }
     s->info.fine_layout = s->info.level_layout[0];
     for (int l = 0; l < s->L; ++l) s->info.prolong_types[l] = s->on_device ? s->lv[l].ntypes : 0;

@@ -18,19 +18,21 @@ def _gpu():
     need_gpu()
 
 
-# 256, 289, 4,225 squares (Q2, Q3, Q4) and 343, 4,913 hexahedra: both group sizes, ragged groups
+# 256, 289, 4,225 squares (Q1 to Q4) and 343, 4,913 hexahedra (Q1, Q2): both group sizes, ragged groups
 @pytest.mark.parametrize("name,kw", [
     ("c2", dict(n=16, group=[4])), ("c2", dict(n=17, p=3, jitter=0.1, group=[17])),
     ("c2", dict(n=17, p=4, jitter=0.1, penalty=("fixed", 900.0), group=[17])),
     ("c2", dict(n=65, group=[13])), ("c2", dict(n=65, p=3, jitter=0.1, group=[13])),
     ("c2", dict(n=65, p=4, jitter=0.1, group=[13])), ("c3", dict(n=7, group=[7], **CUBE)),
-    ("c3", dict(n=17, group=[17], **CUBE))])
+    ("c3", dict(n=17, group=[17], **CUBE)), ("c2", dict(n=17, p=1, group=[17])), ("c2", dict(n=65, p=1, group=[13])),
+    ("c3", dict(n=7, p=1, group=[7], **CUBE)), ("c3", dict(n=17, p=1, group=[17], **CUBE))])
 def test_mapped_rows_match_oracle(name, kw):
     pr = make_problem(name, **kw)
     n, b = pr["n_cells"], pr["b"]
     scale = np.random.default_rng(3).uniform(0.5, 2.0, n)
     h, s = problem.build(pr, precision="mixed", cell_scale=scale)
-    assert s.info()["fine_layout"] == "matrix_free"
+    assert s.info()["fine_layout"] == ("axis_ell" if pr["p"] == 1 else "matrix_free")
+    assert not s.info()["sparse_faces"]
     rng = np.random.default_rng(4)
     cells = np.unique(np.concatenate([[0, 15, 16, 63, 64, n - 1, n - 2], rng.integers(0, n, 24)]) % n)
     M, A = assemble(pr, scale, row_cells=cells)
@@ -46,7 +48,8 @@ def test_mapped_rows_match_oracle(name, kw):
 
 @pytest.mark.parametrize("mg", [dict(), dict(cheb_degree=1), dict(jacobi="cell_block"),
                                 dict(cheb_degree=1, jacobi="cell_block")])
-@pytest.mark.parametrize("name,kw", [("c2", dict(n=20, group=[4])), ("c3", dict(n=8, group=[2], **CUBE))])
+@pytest.mark.parametrize("name,kw", [("c2", dict(n=20, group=[4])), ("c3", dict(n=8, group=[2], **CUBE)),
+                                     ("c3", dict(n=8, p=1, group=[2], **CUBE)), ("c1", dict(n=16))])
 def test_mapped_vcycle_matches_blocks(name, kw, mg):
     pr = make_problem(name, **kw)
     r = dev(np.random.default_rng(2).standard_normal(pr["N"]))
