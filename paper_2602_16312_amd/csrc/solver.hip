@@ -18,6 +18,7 @@
 #include <rocsolver/rocsolver.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -159,7 +160,12 @@ struct dgmg_solver {
     double* partial = nullptr;
     double* sc = nullptr;
     double* sc_host = nullptr;
-    double* sc_host_dev = nullptr;   // device address of the pinned sc_host (mapped)
+    // single-column PCG: 8 scalars and the number of the stopping test that
+    // wrote them (mapped pinned memory, host and device address)
+    double *mirror = nullptr, *mirror_dev = nullptr;
+    uint64_t seq = 0;                // stopping tests launched
+    // the PCG's search directions as graphs (null: launched one by one)
+    hipGraphExec_t g_first = nullptr, g_next = nullptr;
     double* scratch = nullptr;     // this device's static PCG scratch (dgmg_pcg_solve_noalloc)
     int32_t* act = nullptr;        // per-column active mask of multi-column PCG
     int32_t* act_host = nullptr;   // pinned staging of that mask
@@ -222,6 +228,8 @@ struct dgmg_solver {
         return d;
     }
     ~dgmg_solver() {
+        if (g_first) (void)hipGraphExecDestroy(g_first);
+        if (g_next) (void)hipGraphExecDestroy(g_next);
         for (hipEvent_t e : phase_ev)
             if (e) (void)hipEventDestroy(e);
         for (auto& e : prof_ev) {
@@ -230,6 +238,7 @@ struct dgmg_solver {
         }
         for (void* p : allocs) mem.release(p);
         if (sc_host) (void)hipHostFree(sc_host);
+        if (mirror) (void)hipHostFree(mirror);
         if (act_host) (void)hipHostFree(act_host);
     }
 };
@@ -645,11 +654,22 @@ static double read_scalars(dgmg_solver* s, hipStream_t st, int R = 1, const doub
     HIPCHK(hipStreamSynchronize(st));
     return s->sc_host[0];
 }
-// The last finalize kernel before this already wrote the 8 scalars into the
-// mapped pinned host buffer: wait for it.
-static double wait_scalars(dgmg_solver* s, hipStream_t st) {
-    HIPCHK(hipStreamSynchronize(st));
-    return s->sc_host[0];
+// Waits for the finalize kernel launched with `seq`, which writes the 8 scalars
+// and then seq into the mapped pinned buffer.  Polling that word sees the
+// scalars before a stream synchronisation returns; every 20 ms or so the stream is
+// queried (which queues a marker behind the work), so that a failed launch or
+// kernel ends the wait.
+static void wait_scalars(dgmg_solver* s, hipStream_t st, uint64_t seq) {
+    const auto* word = reinterpret_cast<const std::atomic<uint64_t>*>(s->mirror + 8);
+    for (unsigned spin = 1; word->load(std::memory_order_acquire) != seq; ++spin) {
+        __builtin_ia32_pause();
+        if (spin % (1 << 20) != 0) continue;
+        const hipError_t e = hipStreamQuery(st);
+        if (e == hipErrorNotReady) continue;
+        if (e != hipSuccess) fail(DGMG_EHIP, std::string("PCG: ") + hipGetErrorString(e));
+        if (word->load(std::memory_order_acquire) == seq) break;
+        fail(DGMG_EHIP, "PCG: the stream ended without its scalars");
+    }
 }
 
 // Names the failed CG quantity: (p, A p) <= 0 means A_0 is not positive
@@ -666,9 +686,106 @@ static std::string breakdown_msg(int its, int col, double pq, double gam) {
 // 1 gamma = (r, z), 2 (p, A p), 3 the new (r, z), 4 beta, 5 (r_new, z_old),
 // 6 ||b||^2) is passed in: the solver's own buffers, or the static array of
 // the non-allocating entry point.
+// q = A p with the partials and value of (p, q).
+static void apply_p(dgmg_solver* s, hipStream_t st, double* partial, double* sc) {
+    DevLevel& L0 = s->lv[0];
+    launch_apply<double>(s, L0, s->pv, s->q, s->pv, partial, st);
+    k_finalize<<<1, kWG, 0, st>>>(level_tiles<double>(s, L0), partial, sc, 2, 0);
+}
+// whether the PCG update starts the V-cycle's first level-0 sweep (point Jacobi)
+static bool update_starts_sweep(const dgmg_solver* s) {
+    return s->L > 1 && s->cheb_s > 0 && s->jacobi != DGMG_JACOBI_CELL_BLOCK;
+}
+// The first search direction z = V(r), p = z, and q = A p.
+static void first_direction(dgmg_solver* s, hipStream_t st, double* partial, double* sc) {
+    const unsigned nb = blocks_for(s->N);
+    apply_vcycle(s, s->r, s->z, st);
+    k_dot<<<nb, kWG, 0, st>>>(s->N, s->r, s->z, partial);
+    k_finalize<<<1, kWG, 0, st>>>(nb, partial, sc, 1, 0);
+    k_update_p<<<nb, kWG, 0, st>>>(s->N, sc, s->z, s->pv, 1);
+    apply_p(s, st, partial, sc);
+}
+// The rest of an iteration after its stopping test: z = V(r), p, q = A p.
+static void next_direction(dgmg_solver* s, hipStream_t st, double* partial, double* sc, bool flexible) {
+    const int64_t N = s->N;
+    const unsigned nb = blocks_for(N);
+    const bool init0 = update_starts_sweep(s);
+    if (flexible) {
+        std::swap(s->z, s->zold);
+        apply_vcycle(s, s->r, s->z, st, true, nullptr, init0);
+        k_dot<<<nb, kWG, 0, st>>>(N, s->r, s->zold, partial);
+        k_finalize<<<1, kWG, 0, st>>>(nb, partial, sc, 5, 0);
+        k_dot<<<nb, kWG, 0, st>>>(N, s->r, s->z, partial);
+    } else {
+        // z = V(r) with the partials of (r, z) from the exit cast
+        apply_vcycle(s, s->r, s->z, st, true, partial, init0);
+    }
+    k_finalize<<<1, kWG, 0, st>>>(nb, partial, sc, 3, flexible ? 2 : 1);
+    k_update_p<<<nb, kWG, 0, st>>>(N, sc, s->z, s->pv, 0);
+    apply_p(s, st, partial, sc);
+}
+
+// Records what `work` launches into a graph.  Only kernels are launched, on the
+// solver's own buffers; `work` must leave the solver as it found it.
+template <typename F>
+static hipGraphExec_t record_graph(F&& work) {
+    hipStream_t st = nullptr;
+    hipGraph_t g = nullptr;
+    hipGraphExec_t x = nullptr;
+    HIPCHK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
+    hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
+    if (e == hipSuccess) {
+        try {
+            work(st);
+        } catch (...) {
+            (void)hipStreamEndCapture(st, &g);
+            if (g) (void)hipGraphDestroy(g);
+            (void)hipStreamDestroy(st);
+            throw;
+        }
+        e = hipStreamEndCapture(st, &g);
+    }
+    if (e == hipSuccess) e = hipGraphInstantiate(&x, g, nullptr, nullptr, 0);
+    if (g) (void)hipGraphDestroy(g);
+    (void)hipStreamDestroy(st);
+    if (e != hipSuccess) fail(DGMG_EHIP, std::string("recording the PCG's graph: ") + hipGetErrorString(e));
+    return x;
+}
+// Graphs of first_direction and next_direction (set-up).  Launched one by one,
+// a V-cycle's 24 kernels take the host 100 us, which bounds small solvers: a
+// time step of 32x32 Q1 cells 528 us, 348 us with the graphs; 256x256 Q2
+// 1,266 and 1,234 us; 64^3 Q2 no change.
+static void record_directions(dgmg_solver* s) {
+    auto names = [&]() {
+        std::vector<void*> v{s->r, s->z, s->zold, s->pv, s->q};
+        for (const DevLevel& L : s->lv) v.insert(v.end(), {L.vb, L.vx, L.vx2, L.vr, L.vd, L.vd2});
+        return v;
+    };
+    if (s->prec == DGMG_PREC_FP64) s->lv[0].vb = s->r;   // as every V-cycle sets it
+    const auto before = names();
+    s->g_first = record_graph([&](hipStream_t st) { first_direction(s, st, s->partial, s->sc); });
+    const bool same = names() == before;
+    if (same) s->g_next = record_graph([&](hipStream_t st) { next_direction(s, st, s->partial, s->sc, false); });
+    if (same && names() == before) return;
+    // the V-cycle renames its buffers from call to call (degree 1): launch by launch
+    if (s->g_first) (void)hipGraphExecDestroy(s->g_first);
+    if (s->g_next) (void)hipGraphExecDestroy(s->g_next);
+    s->g_first = s->g_next = nullptr;
+}
+
+// The reduction scratch (block partials and the 8 scalar slots: 0 ||r||^2,
+// 1 gamma = (r, z), 2 (p, A p), 3 the new (r, z), 4 beta, 5 (r_new, z_old),
+// 6 ||b||^2) is passed in: the solver's own buffers, or the static array of
+// the non-allocating entry point.
 static int pcg(dgmg_solver* s, const double* b, double* x, const dgmg_pcg_opts& o, dgmg_pcg_stats* stats,
                hipStream_t st, double* partial, double* sc) {
     RangeScope range(s, "dgmg PCG");
+    // the call returns, or fails, with the stream idle (also when work was
+    // queued ahead of a test that ended it)
+    struct StreamIdle {
+        hipStream_t st;
+        ~StreamIdle() { (void)hipStreamSynchronize(st); }
+    } idle{st};
     const int64_t N = s->N;
     const unsigned nb = blocks_for(N);
     DevLevel& L0 = s->lv[0];
@@ -676,15 +793,17 @@ static int pcg(dgmg_solver* s, const double* b, double* x, const dgmg_pcg_opts& 
     // r = b - A x, ||r||^2
     launch_residual<double>(s, L0, x, nullptr, b, s->r, nullptr, 1.0, nullptr, partial, st);
     const bool relb = o.tol_mode == DGMG_TOL_REL_B;
-    k_finalize<<<1, kWG, 0, st>>>(nt, partial, sc, 0, 0, relb ? nullptr : s->sc_host_dev);
+    uint64_t seq = ++s->seq;
+    k_finalize<<<1, kWG, 0, st>>>(nt, partial, sc, 0, 0, relb ? nullptr : s->mirror_dev, seq);
     double bnorm = 0.0;
     if (relb) {
         k_dot<<<nb, kWG, 0, st>>>(N, b, b, partial);
-        k_finalize<<<1, kWG, 0, st>>>(nb, partial, sc, 6, 0, s->sc_host_dev);
+        k_finalize<<<1, kWG, 0, st>>>(nb, partial, sc, 6, 0, s->mirror_dev, seq);
     }
-    wait_scalars(s, st);
-    const double r0 = std::sqrt(s->sc_host[0]);
-    if (o.tol_mode == DGMG_TOL_REL_B) bnorm = std::sqrt(s->sc_host[6]);
+    HIPCHK(hipGetLastError());
+    wait_scalars(s, st, seq);
+    const double r0 = std::sqrt(s->mirror[0]);
+    if (o.tol_mode == DGMG_TOL_REL_B) bnorm = std::sqrt(s->mirror[6]);
     if (!std::isfinite(r0)) fail(DGMG_ENAN, "non-finite initial residual");
     const double thresh = o.tol_mode == DGMG_TOL_ABS ? o.tol : (o.tol_mode == DGMG_TOL_REL_B ? o.tol * bnorm : o.tol * r0);
     stats->its = 0;
@@ -695,19 +814,24 @@ static int pcg(dgmg_solver* s, const double* b, double* x, const dgmg_pcg_opts& 
         stats->converged = 1;
         return DGMG_OK;
     }
-    apply_vcycle(s, s->r, s->z, st);
-    k_dot<<<nb, kWG, 0, st>>>(N, s->r, s->z, partial);
-    k_finalize<<<1, kWG, 0, st>>>(nb, partial, sc, 1, 0);
-    k_update_p<<<nb, kWG, 0, st>>>(N, sc, s->z, s->pv, 1);
+    const bool graphs = s->g_next && !o.flexible && partial == s->partial && s->prof_kind < 0 && !s->roctx;
+    auto first = [&]() {
+        if (graphs) HIPCHK(hipGraphLaunch(s->g_first, st));
+        else first_direction(s, st, partial, sc);
+    };
+    auto next = [&]() {
+        if (graphs) HIPCHK(hipGraphLaunch(s->g_next, st));
+        else next_direction(s, st, partial, sc, o.flexible != 0);
+    };
     int its = 0;
     // mixed precision: the update also writes the FP32 right-hand side of the next V-cycle;
     // with point Jacobi it also starts that V-cycle's first level-0 sweep (r, d)
     float* rb = s->prec == DGMG_PREC_MIXED ? (float*)L0.vb : nullptr;
-    const bool init0 = s->L > 1 && s->cheb_s > 0 && s->jacobi != DGMG_JACOBI_CELL_BLOCK;
+    const bool init0 = update_starts_sweep(s);
     const double c1_0 = 1.0 / (0.5 * (L0.lam_hi + L0.lam_lo));
+    first();
+    double rlast = r0, rate = 0.0;   // residual norm and its last reduction factor
     while (its < o.max_it) {
-        launch_apply<double>(s, L0, s->pv, s->q, s->pv, partial, st);
-        k_finalize<<<1, kWG, 0, st>>>(nt, partial, sc, 2, 0);
         if (s->prec == DGMG_PREC_MIXED)
             k_update_xr<float><<<nb, kWG, 0, st>>>(N, sc, s->pv, s->q, x, s->r, partial, rb,
                                                    init0 ? (float*)L0.vr : nullptr, init0 ? (float*)L0.vd : nullptr,
@@ -716,11 +840,21 @@ static int pcg(dgmg_solver* s, const double* b, double* x, const dgmg_pcg_opts& 
             k_update_xr<double><<<nb, kWG, 0, st>>>(N, sc, s->pv, s->q, x, s->r, partial, (double*)nullptr,
                                                     init0 ? (double*)L0.vr : nullptr,
                                                     init0 ? (double*)L0.vd : nullptr, L0.dinv64, c1_0);
-        k_finalize<<<1, kWG, 0, st>>>(nb, partial, sc, 0, 0, s->sc_host_dev);
-        wait_scalars(s, st);
+        seq = ++s->seq;
+        k_finalize<<<1, kWG, 0, st>>>(nb, partial, sc, 0, 0, s->mirror_dev, seq);
+        HIPCHK(hipGetLastError());
+        // The GPU would idle while the host waits for ||r|| and queues more.
+        // The next direction depends on the test only in whether it is
+        // wanted, and touches neither x nor r: it is queued ahead unless the
+        // last reduction factor says that this test may end the solve (within
+        // a factor 100).  Step of 256x256 Q2 cells: 1,272 us with a stream
+        // synchronisation per test, 1,250 us polling, 1,234 us queued ahead.
+        const bool ahead = its + 1 < o.max_it && (its == 0 ? r0 > 1e4 * thresh : rlast * rate > 100.0 * thresh);
+        if (ahead) next();
+        wait_scalars(s, st, seq);
         ++its;
-        const double gam = s->sc_host[1], pq = s->sc_host[2];
-        const double rn = std::sqrt(s->sc_host[0]);
+        const double gam = s->mirror[1], pq = s->mirror[2];
+        const double rn = std::sqrt(s->mirror[0]);
         stats->its = its;
         stats->rfin = rn;
         if (!(pq > 0.0) || !(gam > 0.0)) {
@@ -732,18 +866,9 @@ static int pcg(dgmg_solver* s, const double* b, double* x, const dgmg_pcg_opts& 
             stats->converged = 1;
             return DGMG_OK;
         }
-        if (o.flexible) {
-            std::swap(s->z, s->zold);
-            apply_vcycle(s, s->r, s->z, st, true, nullptr, init0);
-            k_dot<<<nb, kWG, 0, st>>>(N, s->r, s->zold, partial);
-            k_finalize<<<1, kWG, 0, st>>>(nb, partial, sc, 5, 0);
-            k_dot<<<nb, kWG, 0, st>>>(N, s->r, s->z, partial);
-        } else {
-            // z = V(r) with the partials of (r, z) from the exit cast
-            apply_vcycle(s, s->r, s->z, st, true, partial, init0);
-        }
-        k_finalize<<<1, kWG, 0, st>>>(nb, partial, sc, 3, o.flexible ? 2 : 1);
-        k_update_p<<<nb, kWG, 0, st>>>(N, sc, s->z, s->pv, 0);
+        rate = rn / rlast;
+        rlast = rn;
+        if (!ahead && its < o.max_it) next();
     }
     return DGMG_NOT_CONVERGED;
 }
@@ -1957,8 +2082,10 @@ int dgmg_setup_levels(const dgmg_hierarchy* h, const dgmg_disc* disc, const dgmg
         s->scratch = scratch_address();
         s->sc = s->dalloc<double>(8 * R);
         HIPCHK(hipMemset(s->sc, 0, 8 * R * sizeof(double)));
-        HIPCHK(hipHostMalloc((void**)&s->sc_host, 8 * R * sizeof(double), hipHostMallocMapped));
-        HIPCHK(hipHostGetDevicePointer((void**)&s->sc_host_dev, s->sc_host, 0));
+        HIPCHK(hipHostMalloc((void**)&s->sc_host, 8 * R * sizeof(double), hipHostMallocDefault));
+        HIPCHK(hipHostMalloc((void**)&s->mirror, 9 * sizeof(double), hipHostMallocMapped));
+        std::memset(s->mirror, 0, 9 * sizeof(double));
+        HIPCHK(hipHostGetDevicePointer((void**)&s->mirror_dev, s->mirror, 0));
         s->act = s->dalloc<int32_t>(R);
         HIPCHK(hipHostMalloc((void**)&s->act_host, R * sizeof(int32_t), hipHostMallocDefault));
         s->mass = s->upload(to_colmajor<double>(s->mass_h, s->b));
@@ -1987,6 +2114,7 @@ int dgmg_setup_levels(const dgmg_hierarchy* h, const dgmg_disc* disc, const dgmg
             s->has_adjoint = true;
         }
         HIPCHK(hipDeviceSynchronize());
+        if (!s->roctx) record_directions(s);   // the ranges are per launch
         s->on_device = true;
     }
     s->info.t_upload = now_s() - t6;
