@@ -17,7 +17,7 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-fopenmp", "-Wall", "-Wno-unused-functi
           "-Wno-unused-result"]
 HOST_SOURCES = ["setup_fem.cpp", "setup_mg.cpp"]
 HIP_SOURCES = ["solver.hip", "cell_box.hip", "cell_map.hip", "cell_blk.hip", "cell_hyb.hip",
-               "setup_dev.hip"]
+               "cell_row.hip", "setup_dev.hip"]
 
 
 def _run(cmd):

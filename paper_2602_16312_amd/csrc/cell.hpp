@@ -30,9 +30,11 @@ struct MfConst {
 };
 // How a level's cells are evaluated: identical boxes, bilinear / trilinear
 // cells with their metric data at the Gauss points, stored blocks of a nodal
-// level on a conforming grid of boxes, or stored cell blocks (with the cell's
-// own face terms) and metric data at the faces' Gauss points.
-enum { GEO_BOX = 0, GEO_MAP = 1, GEO_BLK = 2, GEO_HYB = 3 };
+// level on a conforming grid of boxes, stored cell blocks (with the cell's
+// own face terms) and metric data at the faces' Gauss points, whole stored
+// blocks (agglomerates in a grid whose boxes overlap), or whole blocks of 64
+// rows, a lane per row.
+enum { GEO_BOX = 0, GEO_MAP = 1, GEO_BLK = 2, GEO_HYB = 3, GEO_BLD = 4, GEO_ROW = 5 };
 
 // entry (i, j) of a nodal face block along axis a: node i on the lower cell's
 // upper face or node j on the upper cell's lower face
@@ -44,8 +46,9 @@ template <int B, int GEO>
 struct CellPack {
     static constexpr int D = dim_of<B>(), Q = ax_nodes_1d(B, D), QN = B / Q;
     static constexpr int NEC = GEO == GEO_MAP ? B * (D * (D + 1) / 2 + 1)
-                               : GEO == GEO_BLK || GEO == GEO_HYB ? B * (B + 1) / 2 : 0;
+                               : GEO != GEO_BOX ? B * (B + 1) / 2 : 0;
     static constexpr int NEF = GEO == GEO_MAP || GEO == GEO_HYB ? QN * (2 * D + 1)
+                               : GEO == GEO_BLD ? B * B
                                : GEO == GEO_BLK ? 2 * QN * B - QN * QN : 0;
     static constexpr int cell_groups(int w) { return (NEC + w - 1) / w; }
     static constexpr int face_groups(int w) { return (NEF + w - 1) / w; }
@@ -64,7 +67,7 @@ struct CellArgs {
 
 // Workgroups of the cell kernels on a level of n cells with b x b blocks (the
 // number of partial sums they write).
-unsigned cell_groups(int b, int n);
+unsigned cell_groups(int geo, int b, int n);
 
 // The cell forms of k_apply, k_residual and k_cheb_step (same arguments).
 template <typename T, int GEO>
@@ -84,7 +87,9 @@ void cell_step(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* d, 
         case GEO_BOX: { constexpr int GEO = GEO_BOX; __VA_ARGS__; } break;             \
         case GEO_MAP: { constexpr int GEO = GEO_MAP; __VA_ARGS__; } break;             \
         case GEO_BLK: { constexpr int GEO = GEO_BLK; __VA_ARGS__; } break;             \
-        default: { constexpr int GEO = GEO_HYB; __VA_ARGS__; } break;                  \
+        case GEO_HYB: { constexpr int GEO = GEO_HYB; __VA_ARGS__; } break;             \
+        case GEO_BLD: { constexpr int GEO = GEO_BLD; __VA_ARGS__; } break;             \
+        default: { constexpr int GEO = GEO_ROW; __VA_ARGS__; } break;                  \
     }
 
 }  // namespace dgmg

@@ -3,8 +3,8 @@
 
 namespace dgmg {
 
-unsigned cell_groups(int b, int n) {
-    const int nc = cells_per_group(b, n);
+unsigned cell_groups(int geo, int b, int n) {
+    const int nc = cells_per_group(geo, b, n);
     return (unsigned)((n + nc - 1) / nc);
 }
 

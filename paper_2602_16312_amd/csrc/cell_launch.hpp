@@ -10,35 +10,39 @@ namespace dgmg {
 // lane's scattered loads of its cell then share an address unit with fewer
 // others).  Measured per step, 16 / 64 cells: 1,728 3D Q2 boxes 5.1 / 5.8 us,
 // 8,000 6.8 / 6.0 us, 64,000 34 / 15 us.  3D Q3 cells take four lanes each.
-static int cells_per_group(int b, int n) { return b == 64 || n <= 16 * 256 ? 16 : 64; }
+static int cells_per_group(int geo, int b, int n) {
+    return geo == GEO_ROW ? 1 : b == 64 || n <= 16 * 256 ? 16 : 64;
+}
 
 // block size BV and cells per workgroup NC as constants
 #define DISPATCH_CELL(bval, nval, ...)                                                        \
-    if constexpr (GEO == GEO_BOX) {                                                           \
+    if constexpr (GEO == GEO_ROW) {                                                           \
+        if ((bval) == 64) { constexpr int BV = 64, NC = 1; __VA_ARGS__; return; }             \
+    } else if constexpr (GEO == GEO_BOX) {                                                    \
         if ((bval) == 64) { constexpr int BV = 64, NC = 16; __VA_ARGS__; return; }            \
     }                                                                                         \
-    if constexpr (GEO == GEO_BOX || GEO == GEO_HYB) {                                         \
+    if constexpr (GEO != GEO_MAP && GEO != GEO_ROW) {                                                         \
         if ((bval) == 4) { DISPATCH_NC(4, nval, __VA_ARGS__) return; }                        \
         if ((bval) == 8) { DISPATCH_NC(8, nval, __VA_ARGS__) return; }                        \
     }                                                                                         \
-    if constexpr (GEO != GEO_HYB) {                                                           \
-        switch (bval) {                                                                       \
-            case 9: { DISPATCH_NC(9, nval, __VA_ARGS__) } return;                             \
-            case 16: { DISPATCH_NC(16, nval, __VA_ARGS__) } return;                           \
-            case 25: { DISPATCH_NC(25, nval, __VA_ARGS__) } return;                           \
-            case 27: { DISPATCH_NC(27, nval, __VA_ARGS__) } return;                           \
-        }                                                                                     \
+    if constexpr (GEO != GEO_HYB && GEO != GEO_ROW) {                                                       \
+        if ((bval) == 9) { DISPATCH_NC(9, nval, __VA_ARGS__) return; }                        \
+        if ((bval) == 16) { DISPATCH_NC(16, nval, __VA_ARGS__) return; }                      \
+    }                                                                                         \
+    if constexpr (GEO != GEO_HYB && GEO != GEO_BLD && GEO != GEO_ROW) {                                         \
+        if ((bval) == 25) { DISPATCH_NC(25, nval, __VA_ARGS__) return; }                      \
+        if ((bval) == 27) { DISPATCH_NC(27, nval, __VA_ARGS__) return; }                      \
     }                                                                                         \
     fail(DGMG_EUNSUPPORTED, "unsupported block size");
 #define DISPATCH_NC(bval, nval, ...)                                                          \
     constexpr int BV = bval;                                                                  \
-    if (cells_per_group(BV, nval) == 16) { constexpr int NC = 16; __VA_ARGS__; }              \
+    if (cells_per_group(GEO, BV, nval) == 16) { constexpr int NC = 16; __VA_ARGS__; }              \
     else { constexpr int NC = 64; __VA_ARGS__; }
 
 template <typename T, int GEO>
 void cell_apply(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* va, T* y, const T* w, double* partial,
                 hipStream_t st) {
-    const int nc = cells_per_group(b, L.n);
+    const int nc = cells_per_group(GEO, b, L.n);
     const unsigned g = (unsigned)((L.n + nc - 1) / nc);
     DISPATCH_CELL(b, L.n, klaunch(ev, k_apply_cell<T, BV, NC, GEO>, g, cell_threads<BV, GEO>(), st, L, va, y, w, partial));
 }
@@ -47,7 +51,7 @@ template <typename T, int GEO>
 void cell_residual(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* va, const T* vb, const T* rhs, T* r,
                    T* d, T c1, T* xout, double* partial, const T* P, T* rp, const int32_t* ptype, const T* bj,
                    hipStream_t st) {
-    const int nc = cells_per_group(b, L.n);
+    const int nc = cells_per_group(GEO, b, L.n);
     const unsigned g = (unsigned)((L.n + nc - 1) / nc);
     auto go = [&](auto vbc, auto bjc) {
         constexpr bool VB = decltype(vbc)::value, BJ = decltype(bjc)::value;
@@ -65,7 +69,7 @@ void cell_residual(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T*
 template <typename T, int GEO>
 void cell_step(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* d, T* x, T* r, T* dn, T cd, T cr,
                int assign, int last, const T* bj, hipStream_t st) {
-    const int nc = cells_per_group(b, L.n);
+    const int nc = cells_per_group(GEO, b, L.n);
     const unsigned g = (unsigned)((L.n + nc - 1) / nc);
     auto go = [&](auto bjc) {
         constexpr bool BJ = decltype(bjc)::value;

@@ -55,7 +55,7 @@ constexpr int pk(int a, int b) {
 // face where the faces' blocks are streamed
 template <int B, int GEO>
 constexpr int cell_threads() {
-    return 64 * (1 + (GEO == GEO_BLK ? 2 : 1) * dim_of<B>());
+    return 64 * (1 + (GEO == GEO_BLK || GEO == GEO_BLD || GEO == GEO_ROW ? 2 : 1) * dim_of<B>());
 }
 template <typename T, int B, int NCELL, int GEO = GEO_BOX>
 struct CellTile {
@@ -63,7 +63,7 @@ struct CellTile {
     static constexpr int NC = NCELL;                  // cells per workgroup, one per lane
     static constexpr int NT = cell_threads<B, GEO>();
     static constexpr int NW = NT / 64;
-    static constexpr int SB = B | 1;                  // odd LDS stride of a cell's rows
+    static constexpr int SB = GEO == GEO_ROW ? B : B | 1;   // odd LDS stride of a cell's rows
 };
 
 // vector of 16 bytes at the alignment of its elements (a cell's values start
@@ -369,14 +369,14 @@ struct TriList {
             }
     }
 };
-template <int B, int A>
+template <int B, int A, int GEO>
 struct FaceList {
-    unsigned char i[CellPack<B, GEO_BLK>::NEF] = {}, j[CellPack<B, GEO_BLK>::NEF] = {};
+    unsigned char i[CellPack<B, GEO>::NEF] = {}, j[CellPack<B, GEO>::NEF] = {};
     constexpr FaceList() {
         int e = 0;
         for (int a = 0; a < B; ++a)
             for (int b = 0; b < B; ++b)
-                if (face_entry(a, b, A, CellPack<B, GEO_BLK>::Q)) {
+                if (GEO == GEO_BLD || face_entry(a, b, A, CellPack<B, GEO>::Q)) {
                     i[e] = (unsigned char)a;
                     j[e++] = (unsigned char)b;
                 }
@@ -527,7 +527,8 @@ __device__ __forceinline__ void map_face_terms(const CellArgs<T>& L, int c, cons
 
 // ---- stored blocks: the upper triangle of the cell block, and the face
 // block's entries (i, j) with node i on the upper face or node j on the
-// neighbour's lower face (the others vanish on a nodal level).  Every entry is
+// neighbour's lower face (the others vanish on a nodal level; GEO_BLD holds all
+// of them).  Every entry is
 // read coalesced, also by the cell above a face, whose transposed reads by a
 // thread per row touched a line per lane: level 1 of the 64^3 Q2 cube (32,768
 // boxes of 27 DoFs, 209 MB of entries), FP32 step 92 -> 42 us, FP64 260 -> 94.
@@ -547,12 +548,12 @@ __device__ __forceinline__ void blk_cell_terms(const CellArgs<T>& L, int c, cons
 #pragma unroll
     for (int i = 0; i < B; ++i) ys[i] = y[i];
 }
-template <typename T, int B, bool VB, int A, int S>
+template <typename T, int B, bool VB, int GEO, int A, int S>
 __device__ __forceinline__ void blk_face_terms(const CellArgs<T>& L, int c, const T* __restrict__ va,
                                                const T* __restrict__ vb, T* ys) {
     constexpr int W = 16 / sizeof(T);
-    using P = CellPack<B, GEO_BLK>;
-    constexpr FaceList<B, A> list;
+    using P = CellPack<B, GEO>;
+    constexpr FaceList<B, A, GEO> list;
     // no lower neighbour: the products are dropped with zero values (a missing
     // upper face has zero entries)
     const int v = (S ? L.up : L.lo)[(size_t)A * L.n + c], nb = v >= 0 ? v : c;
@@ -564,13 +565,86 @@ __device__ __forceinline__ void blk_face_terms(const CellArgs<T>& L, int c, cons
         y[i] = 0;
     }
     stream_entries<T, P::NEF, ring_groups<T>()>(
-        cell_data<T, B, GEO_BLK>(L, S ? c : nb, P::cell_groups(W) + A * P::face_groups(W)), [&](int e, T a) {
+        cell_data<T, B, GEO>(L, S ? c : nb, P::cell_groups(W) + A * P::face_groups(W)), [&](int e, T a) {
             const int i = list.i[e], j = list.j[e];
             if (S) y[i] += a * x[j];
             else y[j] += a * x[i];
         });
 #pragma unroll
     for (int i = 0; i < B; ++i) ys[i] = y[i];
+}
+
+// ---- 3D Q3 agglomerates: a workgroup per cell, a wave per block, a lane per
+// row.  Blocks are whole, W columns interleaved: entry (i, j) at
+// (j / W) 64 W + i W + j % W of a cell's own block and then its upper faces'.  A
+// wave with all seven blocks of its cell waited for a dozen memory round trips
+// one after the other (512 cells, FP64 step: 24.5 us, 14.8 us here; 64 cells 19.3,
+// 5.5 us).
+// sum over the wave's lanes l of P_l[i mod 16], at lane i
+template <typename T>
+__device__ __forceinline__ T reduce_columns16(T* P, int i) {
+#pragma unroll
+    for (int h = 8; h > 0; h >>= 1) {
+        const bool up = (i & h) != 0;
+#pragma unroll
+        for (int j = 0; j < h; ++j) {
+            // values, not elements: a choice of elements would index P dynamically
+            const T a = P[j], b = P[j + h], mine = up ? b : a, give = up ? a : b;
+            P[j] = mine + __shfl_xor(give, h, 64);
+        }
+    }
+    T s = P[0];
+    s += __shfl_xor(s, 16, 64);
+    return s + __shfl_xor(s, 32, 64);
+}
+template <typename T>
+__device__ __forceinline__ T lane_value(T v, int j);
+template <>
+__device__ __forceinline__ float lane_value<float>(float v, int j) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), j));
+}
+template <>
+__device__ __forceinline__ double lane_value<double>(double v, int j) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), j),
+                            __builtin_amdgcn_readlane(__double2loint(v), j));
+}
+// wave w of cell c: 0 its own block, 1 + 2 a + s the face on side s of axis a
+template <typename T, bool VB>
+__device__ __forceinline__ T row_terms(const CellArgs<T>& L, int c, int w, int lane, const T* __restrict__ va,
+                                       const T* __restrict__ vb) {
+    using V = typename Vec16a<T>::type;
+    constexpr int W = 16 / sizeof(T), NV = 64 / W, HV = NV / 2;
+    const int a = (w - 1) >> 1, side = (w - 1) & 1;
+    const int nb = w == 0 ? c : (side ? L.up : L.lo)[(size_t)a * L.n + c];
+    if (nb < 0 || (w > 0 && nb == c)) return T(0);        // no neighbour (uniform)
+    const bool low = w > 0 && !side;
+    const V* F = reinterpret_cast<const V*>(L.data + ((size_t)(low ? nb : c) * 4 + (w ? 1 + a : 0)) * 4096) + lane;
+    T x = va[(size_t)nb * 64 + lane];
+    if constexpr (VB) x += vb[(size_t)nb * 64 + lane];
+    T acc = 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {                          // half of the columns' loads in flight
+        V f[HV];
+#pragma unroll
+        for (int k = 0; k < HV; ++k) f[k] = F[(size_t)(h * HV + k) * 64];
+        if (!low) {
+#pragma unroll
+            for (int k = 0; k < HV; ++k)
+#pragma unroll
+                for (int q = 0; q < W; ++q) acc += f[k][q] * lane_value(x, (h * HV + k) * W + q);
+        } else {
+            // transposed: column j summed over the lanes' rows, 16 at a time
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                T P[16];
+#pragma unroll
+                for (int j = 0; j < 16; ++j) P[j] = f[(g * 16 + j) / W][j % W] * x;
+                const T r = reduce_columns16(P, lane);
+                acc += (lane >> 4) == h * 2 + g ? r : T(0);
+            }
+        }
+    }
+    return acc;
 }
 
 // ---- Q1 cells: the stored cell block holds the cell's own face terms, and
@@ -689,7 +763,9 @@ __device__ __forceinline__ T quad_dot(const T* c, T v) {
 }
 template <typename T>
 __device__ __forceinline__ T quad_pick(const T* a, int stride, int l) {
-    return l == 0 ? a[0] : l == 1 ? a[stride] : l == 2 ? a[2 * stride] : a[3 * stride];
+    // values, not elements: a choice of elements would become a choice of addresses
+    const T v0 = a[0], v1 = a[stride], v2 = a[2 * stride], v3 = a[3 * stride];
+    return l == 0 ? v0 : l == 1 ? v1 : l == 2 ? v2 : v3;
 }
 // row l of a 4 x 4 table, or column l
 template <typename T>
@@ -846,8 +922,12 @@ __device__ __forceinline__ void cell_product(const CellArgs<T>& L, int cell0, co
     using Ct = CellTile<T, B, NC, GEO>;
     static_assert(NC <= (B == 64 ? 16 : 64), "cells of a workgroup do not fit a wave");
     const int lane = (int)threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    if constexpr (B == 64) {
-        static_assert(GEO == GEO_BOX, "3D Q3 cells: boxes only");
+    if constexpr (GEO == GEO_ROW) {
+        static_assert(B == 64 && NC == 1, "a workgroup per cell of 64 rows");
+        sh[w * 64 + lane] = row_terms<T, VB>(L, cell0, w, lane, va, vb);
+        return;
+    } else if constexpr (B == 64) {
+        static_assert(GEO == GEO_BOX, "3D Q3 cells: boxes or agglomerates by rows");
         const int c = min(cell0 + lane / 4, L.n - 1), l = lane & 3;
         T* ys = sh + (w * Ct::NC + lane / 4) * Ct::SB;
         if (w == 0) cell_terms_quad<T, VB>(L, c, l, va, vb, ys);
@@ -859,15 +939,15 @@ __device__ __forceinline__ void cell_product(const CellArgs<T>& L, int cell0, co
     if (lane >= NC) return;
     const int c = min(cell0 + lane, L.n - 1);
     T* ys = sh + (w * Ct::NC + lane) * Ct::SB;
-    if constexpr (GEO == GEO_BLK) {
+    if constexpr (GEO == GEO_BLK || GEO == GEO_BLD) {
         if (w == 0) blk_cell_terms<T, B, NC, VB, GEO>(L, c, va, vb, ys);
-        else if (w == 1) blk_face_terms<T, B, VB, 0, 0>(L, c, va, vb, ys);
-        else if (w == 2) blk_face_terms<T, B, VB, 0, 1>(L, c, va, vb, ys);
-        else if (w == 3) blk_face_terms<T, B, VB, 1, 0>(L, c, va, vb, ys);
-        else if (Ct::D == 2 || w == 4) blk_face_terms<T, B, VB, 1, 1>(L, c, va, vb, ys);
+        else if (w == 1) blk_face_terms<T, B, VB, GEO, 0, 0>(L, c, va, vb, ys);
+        else if (w == 2) blk_face_terms<T, B, VB, GEO, 0, 1>(L, c, va, vb, ys);
+        else if (w == 3) blk_face_terms<T, B, VB, GEO, 1, 0>(L, c, va, vb, ys);
+        else if (Ct::D == 2 || w == 4) blk_face_terms<T, B, VB, GEO, 1, 1>(L, c, va, vb, ys);
         else if constexpr (Ct::D == 3) {
-            if (w == 5) blk_face_terms<T, B, VB, 2, 0>(L, c, va, vb, ys);
-            else blk_face_terms<T, B, VB, 2, 1>(L, c, va, vb, ys);
+            if (w == 5) blk_face_terms<T, B, VB, GEO, 2, 0>(L, c, va, vb, ys);
+            else blk_face_terms<T, B, VB, GEO, 2, 1>(L, c, va, vb, ys);
         }
         return;
     }

@@ -88,12 +88,14 @@ static inline unsigned blocks_for(int64_t threads) { return (unsigned)((threads 
 // against 12.0 us.  p = 1, 1,024 squares 2.7 against 3.7 us (FP64), boxes 2.6 us;
 // the shell of 1.0M hexahedra 148 against 214 us.
 constexpr int64_t kMinMappedCells = 256;
-// Agglomerated boxes whose blocks go to the cell kernels.  Their straight-line
-// products exceed the instruction cache from b = 25 on, which a small level
-// pays on every launch: a step at 1,024 cells of 25 DoFs (FP64) took 8.8 us
-// against 8.6 us by rows, at 1,000 of 27 DoFs 7.7 against 6.6 us, at 4,096 8.2
-// against 12.1 us; 1,600 cells of 9 DoFs 3.3 against 4.4 us.
-static int64_t min_stored_cells(int b) { return b <= 16 ? 1000 : 2000; }
+// Agglomerated levels in a grid whose blocks go to the cell kernels.  From
+// b = 25 on their straight-line products exceed the instruction cache, which a
+// small level pays on every launch: a step at 1,024 cells of 25 DoFs (FP64)
+// took 8.8 us against 8.6 us by rows, at 1,000 of 27 DoFs 7.7 against 6.6 us,
+// at 4,096 8.2 against 12.1 us.  b = 9: 1,024 cells 2.9 against 3.5 us, FP64
+// 4.0 against 4.5 us; b = 16 boxes 4.9 against 5.8 us (FP64), whole blocks of
+// 16 were slower (7.2 against 6.2 us at 4,096 cells) and stay by rows.
+static int64_t min_stored_cells(int b) { return b <= 16 ? 256 : b == 64 ? 1 : 2000; }
 // coarse problems above this size are factorised on the device at set-up
 constexpr int64_t kHostCholeskyMax = 4096;
 
@@ -340,7 +342,7 @@ static unsigned tiles_for(const DevLevel& L) {
 template <typename T>
 static unsigned level_tiles(const dgmg_solver* s, const DevLevel& L) {
     unsigned g = 0;
-    if (L.geo >= 0) return cell_groups(s->b, L.n);
+    if (L.geo >= 0) return cell_groups(L.geo, s->b, L.n);
     DISPATCH_B(s->b, g = tiles_for<T, BV>(L));
     return g;
 }
@@ -1417,20 +1419,37 @@ static std::vector<T> pack_hybrid(const BlockOp& A, const MetricData& M, const s
                          });
 }
 template <typename T>
-static std::vector<T> pack_blocks(const BlockOp& A, const std::vector<int64_t>& up, int d) {
-    const int b = A.b, q = ax_nodes_1d(b, d), nf = b / q;
+static std::vector<T> pack_blocks(const BlockOp& A, const std::vector<int64_t>& up, int d, bool nodal) {
+    const int b = A.b, q = ax_nodes_1d(b, d);
     const std::vector<int> tri = triangle(b);
     std::vector<int> fl[3];
     for (int i = 0; i < b; ++i)
         for (int j = 0; j < b; ++j)
             for (int a = 0; a < d; ++a)
-                if (face_entry(i, j, a, q)) fl[a].push_back(i * b + j);
-    return pack_cells<T>(A.n, d, (int)tri.size(), 2 * nf * b - nf * nf,
+                if (!nodal || face_entry(i, j, a, q)) fl[a].push_back(i * b + j);
+    return pack_cells<T>(A.n, d, (int)tri.size(), (int)fl[0].size(),
                          [&](int64_t c, int e) { return A.diag[(size_t)c * b * b + tri[e]]; },
                          [&](int64_t c, int a, int e) {
                              const int64_t f = up[(size_t)a * A.n + c];
                              return f < 0 ? 0.0 : A.fblk[(size_t)f * b * b + fl[a][e]];
                          });
+}
+// whole blocks of 64 rows for GEO_ROW (kernels_cell.hpp)
+template <typename T>
+static std::vector<T> pack_rows(const BlockOp& A, const std::vector<int64_t>& up, int d) {
+    const int b = A.b, W = 16 / sizeof(T);
+    std::vector<T> out((size_t)A.n * (1 + d) * b * b, (T)0);
+#pragma omp parallel for schedule(static)
+    for (int64_t c = 0; c < A.n; ++c)
+        for (int k = 0; k <= d; ++k) {
+            const int64_t f = k ? up[(size_t)(k - 1) * A.n + c] : -1;
+            if (k && f < 0) continue;
+            const double* F = k ? &A.fblk[(size_t)f * b * b] : &A.diag[(size_t)c * b * b];
+            T* o = &out[((size_t)c * (1 + d) + k) * b * b];
+            for (int i = 0; i < b; ++i)
+                for (int j = 0; j < b; ++j) o[(size_t)(j / W) * b * W + i * W + j % W] = (T)F[(size_t)i * b + j];
+        }
+    return out;
 }
 // block sizes of the cell kernels on mapped and stored cells
 static bool cell_block_size(int b) { return b == 4 || b == 8 || b == 9 || b == 16 || b == 25 || b == 27; }
@@ -1452,7 +1471,8 @@ static void upload_level(dgmg_solver* s, int l) {
     const bool ax = l == 0 && !mf && s->fine_layout != DGMG_LAYOUT_TILE_ELL && !s->axis0.empty();
     // agglomerated levels that form a conforming grid of boxes also store each
     // face block once (faces reoriented from the lower to the upper box)
-    bool axc = false, blk = false;
+    bool axc = false;
+    int blk = -1;   // GEO_* of an agglomerated level's blocks for the cell kernels
     AxisEll Ec;
     std::vector<int64_t> upf;
     if (l > 0 && !last && s->fine_layout != DGMG_LAYOUT_TILE_ELL && (size_t)l < s->axisl.size() &&
@@ -1473,16 +1493,22 @@ static void upload_level(dgmg_solver* s, int l) {
                     for (int j = i + 1; j < b; ++j) std::swap(blk[i * b + j], blk[j * b + i]);
             }
         try {
-            // above identical boxes the agglomerates are boxes with nodal
-            // bases: their blocks go to the cell kernels
-            if (s->fine_layout == DGMG_LAYOUT_MATRIX_FREE && b >= 9 && cell_block_size(b) && A.n >= min_stored_cells(b)) {
+            // above a fine level of the cell kernels: blocks of boxes with
+            // nodal bases without their zeros (b <= 27), others whole (b <= 9,
+            // and b = 64 by rows)
+            if ((s->fine_layout == DGMG_LAYOUT_MATRIX_FREE || s->mapped) && A.n >= min_stored_cells(b) &&
+                (b == 64 || cell_block_size(b))) {
                 Ec = build_axis_ell(Ao, s->axisl[l], s->dim, false);
                 upf = upper_faces(Ao, s->axisl[l], s->dim);
-                blk = faces_are_nodal(Ao, upf, s->dim);
+                blk = b == 64 ? GEO_ROW : faces_are_nodal(Ao, upf, s->dim) ? GEO_BLK : b <= 9 ? GEO_BLD : -1;
             }
-            if (blk) {
-                L.data64 = s->upload(pack_blocks<double>(Ao, upf, s->dim));
-                if (s->prec == DGMG_PREC_MIXED) L.data32 = s->upload(pack_blocks<float>(Ao, upf, s->dim));
+            if (blk >= 0) {
+                auto pack = [&](auto tag) {
+                    using T = decltype(tag);
+                    return b == 64 ? pack_rows<T>(Ao, upf, s->dim) : pack_blocks<T>(Ao, upf, s->dim, blk == GEO_BLK);
+                };
+                L.data64 = s->upload(pack(double{}));
+                if (s->prec == DGMG_PREC_MIXED) L.data32 = s->upload(pack(float{}));
             } else {
                 Ec = build_axis_ell(Ao, s->axisl[l], s->dim, true);
             }
@@ -1505,15 +1531,15 @@ static void upload_level(dgmg_solver* s, int l) {
             L.dinv32 = s->upload(convert<float>(dinv));
             L.mf32 = mf_constants<float>(s, re, s->upload(convert<float>(s->mf_D)));
         }
-    } else if (blk || (l == 0 && s->mapped)) {
-        AxisEll E = blk ? std::move(Ec) : build_axis_ell(A, s->axis0, s->dim, false);
-        const bool hyb = !blk && s->p == 1;
-        L.geo = blk ? GEO_BLK : hyb ? GEO_HYB : GEO_MAP;
+    } else if (blk >= 0 || (l == 0 && s->mapped)) {
+        AxisEll E = blk >= 0 ? std::move(Ec) : build_axis_ell(A, s->axis0, s->dim, false);
+        const bool hyb = blk < 0 && s->p == 1;
+        L.geo = blk >= 0 ? blk : hyb ? GEO_HYB : GEO_MAP;
         L.up = s->upload(E.up);
         L.lo = s->upload(E.lo);
         L.dinv64 = s->upload(dinv);
         if (s->prec == DGMG_PREC_MIXED) L.dinv32 = s->upload(convert<float>(dinv));
-        if (!blk) {
+        if (blk < 0) {
             RefElement re;
             re.init(s->dim, s->p);
             upf = upper_faces(A, s->axis0, s->dim);
@@ -2123,7 +2149,7 @@ int dgmg_setup_levels(const dgmg_hierarchy* h, const dgmg_disc* disc, const dgmg
         const DevLevel& Lv = s->lv[l];
         s->info.level_layout[l] = !s->on_device || (l == s->L - 1 && s->L > 1) ? 0
                                   : Lv.geo == GEO_BOX || Lv.geo == GEO_MAP ? DGMG_LAYOUT_MATRIX_FREE
-                                  : Lv.ax || Lv.geo == GEO_BLK || Lv.geo == GEO_HYB ? DGMG_LAYOUT_AXIS_ELL : DGMG_LAYOUT_TILE_ELL;
+                                  : Lv.ax || Lv.geo >= 0 ? DGMG_LAYOUT_AXIS_ELL : DGMG_LAYOUT_TILE_ELL;
     }
     s->info.fine_layout = s->info.level_layout[0];
     for (int l = 0; l < s->L; ++l) s->info.prolong_types[l] = s->on_device ? s->lv[l].ntypes : 0;

@@ -65,10 +65,13 @@ def test_mapped_vcycle_matches_blocks(name, kw, mg):
         assert rel(host(z[1]), host(z[0])) <= tol, prec
 
 
-# level 1: 1,024 boxes of 9 and 16 DoFs, 2,704 of 25, 2,197 of 27
+# level 1: 1,024 boxes of 9 and 16 DoFs, 2,704 of 25, 2,197 of 27, 64 and 27 of 64 (by rows),
+# 289 overlapping boxes of 9 and of 4 DoFs
 @pytest.mark.parametrize("name,kw", [
     ("e1", dict(n=64, p=2, group=[2, 8])), ("e1", dict(n=64, p=3, group=[2, 8])),
-    ("e1", dict(n=104, p=4, group=[2, 13])), ("c3", dict(n=26, group=[2, 13]))])
+    ("e1", dict(n=104, p=4, group=[2, 13])), ("c3", dict(n=26, group=[2, 13])),
+    ("c3", dict(n=8, p=3, group=[2, 2])), ("c3", dict(n=6, p=3, group=[2, 3])),
+    ("c2", dict(n=68, group=[4, 17])), ("c2", dict(n=68, p=1, group=[4, 17]))])
 def test_stored_boxes_match_rows(name, kw):
     pr = make_problem(name, **kw)
     out = {}
