@@ -50,6 +50,8 @@ struct LevelArgs {
     const int32_t* __restrict__ up;        // axis-ELL: [d][n] upper neighbour (itself if none)
     const int32_t* __restrict__ lo;        // axis-ELL: [d][n] lower neighbour (-1 if none)
     const int32_t* __restrict__ cmap;      // tile-ELL: tile position -> cell (null: identity)
+    const T* __restrict__ fvals;           // tile slots with faces held once: the face blocks
+    const int2* __restrict__ once;         // (slot, cell in tile) -> face << 1 | side (-1: none), column cell
 };
 
 // Axis-ELL storage of a cell's diagonal block, which is symmetric: plane k
@@ -323,10 +325,109 @@ __device__ __forceinline__ T ax_row_apply(const LevelArgs<T>& L, int tile, int c
     return acc;
 }
 
+// 16 bytes of row-major blocks
+template <typename T>
+struct RowVec;
+template <>
+struct RowVec<float> {
+    typedef float type __attribute__((ext_vector_type(4)));
+};
+template <>
+struct RowVec<double> {
+    typedef double type __attribute__((ext_vector_type(2)));
+};
+template <typename T, int B>
+__device__ __forceinline__ void load_row(const T* __restrict__ p, T* v) {
+    using V = typename RowVec<T>::type;
+    constexpr int W = 16 / sizeof(T);
+#pragma unroll
+    for (int k = 0; k < B; k += W) {
+        const V x = *reinterpret_cast<const V*>(p + k);
+#pragma unroll
+        for (int q = 0; q < W; ++q) v[k + q] = x[q];
+    }
+}
+// sum over the cell's B lanes l of P_l[i], at lane i (B a power of two)
+template <typename T, int B>
+__device__ __forceinline__ T reduce_columns(T* P, int i) {
+#pragma unroll
+    for (int h = B / 2; h > 0; h >>= 1) {
+        const bool up = (i & h) != 0;
+#pragma unroll
+        for (int j = 0; j < h; ++j) {
+            // values, not elements: a choice of elements would index P dynamically
+            const T a = P[j], b = P[j + h], mine = up ? b : a, give = up ? a : b;
+            P[j] = mine + __shfl_xor(give, h, 64);
+        }
+    }
+    return P[0];
+}
+// Row product on an irregular level whose face blocks are held once (row-major,
+// rows of the plus cell).  Lane i of a cell reads row i of every block: of a
+// face on its plus side that is the product's row; of a face on its minus
+// side the lane accumulates row i times x_plus[i] into the B columns, which
+// are summed over the cell's lanes at the end.  Level 1 of the 1.0M-hex shell
+// (125,229 cells of 8 DoFs, twelve neighbours each), FP32 step: 55 us, 94 us
+// with the tile slots' second copies; slots per group 1 / 2 / 3 / 4 / 6 / 8:
+// 67 / 59 / 55 / 67 / 59 / 62 us.  FP64 was slower (224 against 184 us).
+template <typename T, int B, bool VB>
+__device__ __forceinline__ T once_row_apply(const LevelArgs<T>& L, int tile, int lc, int cell, int i,
+                                            const T* __restrict__ va, const T* __restrict__ vb) {
+    constexpr int TC = Tile<T, B>::TC, G = 3;
+    const int s0 = L.slot_ptr[tile], ns = L.slot_ptr[tile + 1] - s0;
+    const int2* __restrict__ op = L.once + (size_t)s0 * TC + lc;
+    const int base = ((int)threadIdx.x & 63) - i;
+    T acc = 0, P[B];
+    const T xo = gather_own<T, B, VB>(va, vb, cell, i);
+    {
+        T a[B], x[B];
+        load_row<T, B>(L.vals + ((size_t)cell * B + i) * B, a);
+        share_segment<T, B>(xo, base, x);
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+            acc += a[j] * x[j];
+            P[j] = 0;
+        }
+    }
+    int2 en[G];
+#pragma unroll
+    for (int q = 0; q < G; ++q) en[q] = op[(size_t)min(q, ns - 1) * TC];
+    for (int g = 0; g < ns; g += G) {
+        int2 e[G];
+        T a[G][B], xi[G];
+#pragma unroll
+        for (int q = 0; q < G; ++q) e[q] = en[q];
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            // a padded slot reads the cell's own block and values, unused
+            const T* F = e[q].x < 0 ? L.vals + (size_t)cell * B * B : L.fvals + (size_t)(e[q].x >> 1) * B * B;
+            load_row<T, B>(F + i * B, a[q]);
+            xi[q] = gather_own<T, B, VB>(va, vb, e[q].y, i);
+        }
+        // the next group's references while this group's blocks arrive
+#pragma unroll
+        for (int q = 0; q < G; ++q) en[q] = op[(size_t)min(g + G + q, ns - 1) * TC];
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const bool on = g + q < ns && e[q].x >= 0, minus = (e[q].x & 1) != 0;
+            T x[B], r = 0;
+            share_segment<T, B>(xi[q], base, x);
+#pragma unroll
+            for (int j = 0; j < B; ++j) r += a[q][j] * x[j];
+            acc += on && !minus ? r : T(0);
+            const T w = on && minus ? xi[q] : T(0);
+#pragma unroll
+            for (int j = 0; j < B; ++j) P[j] += a[q][j] * w;
+        }
+    }
+    return acc + reduce_columns<T, B>(P, i);
+}
+
 // Operator layouts of a level: tile-ELL, axis-ELL, axis-ELL with sparse face
-// blocks (nodal fine levels, single column); LY_CELL levels evaluate the
+// blocks (nodal fine levels, single column), tile slots whose face blocks are
+// held once (irregular levels, single column); LY_CELL levels evaluate the
 // operator per cell and have kernels of their own (kernels_cell.hpp).
-enum { LY_TILE = 0, LY_AXIS = 1, LY_CELL = 2, LY_AXS = 3 };
+enum { LY_TILE = 0, LY_AXIS = 1, LY_CELL = 2, LY_AXS = 3, LY_ONCE = 4 };
 
 // (A (va + vb)) at the thread's row for layout LY; ri is the thread's row
 // within the tile (lc B + i), i its row of the cell.  A cell's lanes are all
@@ -338,6 +439,8 @@ __device__ __forceinline__ T row_apply(const LevelArgs<T>& L, int tile, int lc, 
     if (!active) return T(0);
     if constexpr (LY == LY_AXIS || LY == LY_AXS)
         return ax_row_apply<T, B, VB, whole_wave_cells<B>(), LY == LY_AXS>(L, tile, cell, ri, i, va, vb);
+    else if constexpr (LY == LY_ONCE)
+        return once_row_apply<T, B, VB>(L, tile, lc, cell, i, va, vb);
     else
         return ell_row_apply<T, B, VB, whole_wave_cells<B>()>(L, tile, lc, ri, i, va, vb);
 }
@@ -389,7 +492,7 @@ template <typename T, int B, int LY>
 __global__ __launch_bounds__(kWG) void k_apply(LevelArgs<T> L, const T* __restrict__ va,
                                                T* __restrict__ y,
                                                const T* __restrict__ w, double* __restrict__ partial) {
-    DGMG_TILE_THREAD_M(T, B, LY == LY_TILE, whole_wave_cells<B>())
+    DGMG_TILE_THREAD_M(T, B, LY == LY_TILE || LY == LY_ONCE, whole_wave_cells<B>())
     double contrib = 0.0;
     const T a = row_apply<T, B, false, LY>(L, tile, lc, cell, ri, ti, active, va, nullptr);
     if (active) {
@@ -412,7 +515,7 @@ __global__ __launch_bounds__(kWG) void k_residual(LevelArgs<T> L, const T* __res
                                                   const T* __restrict__ P, T* __restrict__ rp,
                                                   const int32_t* __restrict__ ptype,
                                                   const T* __restrict__ bj) {
-    DGMG_TILE_THREAD_M(T, B, LY == LY_TILE, whole_wave_cells<B>())
+    DGMG_TILE_THREAD_M(T, B, LY == LY_TILE || LY == LY_ONCE, whole_wave_cells<B>())
     double contrib = 0.0;
     T rr = 0;
     const T a = row_apply<T, B, VB, LY>(L, tile, lc, cell, ri, ti, active, va, vb);
@@ -462,7 +565,7 @@ __global__ __launch_bounds__(kWG) void k_cheb_step(LevelArgs<T> L, const T* __re
                                                    T* __restrict__ x, T* __restrict__ r,
                                                    T* __restrict__ dn, T cd, T cr, int assign,
                                                    int last, const T* __restrict__ bj) {
-    DGMG_TILE_THREAD_M(T, B, LY == LY_TILE, whole_wave_cells<B>())
+    DGMG_TILE_THREAD_M(T, B, LY == LY_TILE || LY == LY_ONCE, whole_wave_cells<B>())
     // FP32: the row's own operands are requested before the product, so that
     // their loads overlap its memory chain (FP64 keeps its register count;
     // for 3D Q1 blocks the three registers would cost a wave per SIMD)

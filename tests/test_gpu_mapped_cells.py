@@ -86,3 +86,26 @@ def test_stored_boxes_match_rows(name, kw):
             out[layout, prec] = host(y)
     assert rel(out["auto", "fp64"], out["axis_ell", "fp64"]) <= 1e-13
     assert rel(out["auto", "mixed"], out["axis_ell", "fp64"]) <= 3e-6
+
+
+@pytest.mark.parametrize("mg", [dict(), dict(cheb_degree=1), dict(jacobi="cell_block"),
+                                dict(cheb_degree=1, jacobi="cell_block")])
+def test_faces_held_once_match_tile_slots(mg):
+    pr = make_problem("c4", h=0.042, agglo=("rtree_str", 8, 4))
+    r = dev(np.random.default_rng(2).standard_normal(pr["N"]))
+    z = [torch.empty_like(r) for _ in range(2)]
+    y, lam = {}, None
+    for k, layout in enumerate(("tile_ell", "auto")):
+        h, s = problem.build(pr, precision="mixed", fine_layout=layout, lam_override=lam, **mg)
+        i = s.info()
+        assert i["n_cells"][1] >= 4000 and i["level_layout"][1] == "tile_ell"
+        lam = np.stack([i["lam_lo"][:-1], i["lam_hi"][:-1]], axis=1)
+        x = dev(np.random.default_rng(5).standard_normal(i["n_cells"][1] * 8))
+        for prec in ("fp64", "mixed"):
+            y[layout, prec] = torch.empty_like(x)
+            say("faces once", mg, layout, prec)
+            api.apply(s, 1, x, y[layout, prec], prec)
+        api.vcycle(s, r, z[k])
+    assert np.array_equal(host(y["auto", "fp64"]), host(y["tile_ell", "fp64"]))
+    assert rel(host(y["auto", "mixed"]), host(y["tile_ell", "fp64"])) <= 3e-6
+    assert rel(host(z[1]), host(z[0])) <= 2e-5
