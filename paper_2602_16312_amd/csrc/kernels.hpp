@@ -505,8 +505,8 @@ __global__ __launch_bounds__(kWG) void k_apply(LevelArgs<T> L, const T* __restri
 // Residual r = rhs - A (va + vb), with optional epilogues: d = dinv * r * c1
 // (with bj: d = c1 D_K^-1 r per cell, the cell-block Jacobi term),
 // xout = va + vb, partial of ||r||^2, and restriction partials
-// rp[cell, j] = sum_i P_cell(i, j) r[cell, i] (P in tile-interleaved layout)
-// for the coarse correction.  r may be null when only rp is wanted.
+// rp[cell, j] = sum_i P_cell(i, j) r[cell, i] (P row by row in tile-interleaved
+// layout, so that a cell's lanes read a row together) for the coarse correction.  r may be null when only rp is wanted.
 template <typename T, int B, bool VB, int LY, bool BJ = false>
 __global__ __launch_bounds__(kWG) void k_residual(LevelArgs<T> L, const T* __restrict__ va,
                                                   const T* __restrict__ vb, const T* __restrict__ rhs,
@@ -536,14 +536,14 @@ __global__ __launch_bounds__(kWG) void k_residual(LevelArgs<T> L, const T* __res
         if (ri < Tile<T, B>::TR) rs[ri] = rr;
         __syncthreads();
         if (active) {
-            // thread (lc, j): column j of P_cell, contiguous in i (tile
-            // layout, at the cell's own tile position) or strided by B
-            // (row-major block of the cell's type)
+            // thread (lc, j): column j of P_cell, whose lanes read consecutive
+            // words of a row (restriction layout, at the cell's own tile
+            // position, or row-major block of the cell's type)
             constexpr int TC = Tile<T, B>::TC, TR = Tile<T, B>::TR;
             const int j = ti;
             const int ht = cell / TC, hl = cell - ht * TC;
-            const T* Pc = ptype ? P + (size_t)ptype[cell] * B * B + j : P + ((size_t)ht * B + j) * TR + hl * B;
-            const int ks = ptype ? B : 1;
+            const T* Pc = ptype ? P + (size_t)ptype[cell] * B * B + j : P + (size_t)ht * B * TR + hl * B + j;
+            const int ks = ptype ? B : TR;
             const T* rc = rs + lc * B;
             T s = 0;
 #pragma unroll

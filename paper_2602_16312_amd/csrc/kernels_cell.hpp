@@ -1056,30 +1056,37 @@ __global__ __launch_bounds__((cell_threads<B, GEO>())) void k_residual_cell(
     }
     if ((BJ && d) || P) {
         __syncthreads();
-        for (int e = threadIdx.x; e < rows; e += Ct::NT) {
-            const size_t t = t0 + e;
-            const int lc = e / B, j = e - lc * B, cell = cell0 + lc;
-            const T* rc = sh + lc * Ct::SB;
-            if constexpr (BJ) {
-                if (d) {
-                    const T* Dc = bj + (size_t)cell * B * B + j;
-                    T z = 0;
+        // two rows of a thread at a time, their loads requested together
+        for (int e0 = threadIdx.x; e0 < rows; e0 += 2 * Ct::NT) {
+            T z[2] = {0, 0}, s[2] = {0, 0};
 #pragma unroll
-                    for (int i = 0; i < B; ++i) z += Dc[(size_t)i * B] * rc[i];
-                    d[t] = c1 * z;
+            for (int u = 0; u < 2; ++u) {
+                const int e = min(e0 + u * Ct::NT, rows - 1), lc = e / B, j = e - lc * B, cell = cell0 + lc;
+                const T* rc = sh + lc * Ct::SB;
+                if constexpr (BJ) {
+                    if (d) {
+                        const T* Dc = bj + (size_t)cell * B * B + j;
+#pragma unroll
+                        for (int i = 0; i < B; ++i) z[u] += Dc[(size_t)i * B] * rc[i];
+                    }
+                }
+                if (P) {
+                    // column j of P_cell: a block of the type table or of the
+                    // tile-interleaved restriction layout
+                    constexpr int TC = Tile<T, B>::TC, TR = Tile<T, B>::TR;
+                    const int ht = cell / TC, hl = cell - ht * TC;
+                    const T* Pc = ptype ? P + (size_t)ptype[cell] * B * B + j : P + (size_t)ht * B * TR + hl * B + j;
+                    const int ks = ptype ? B : TR;
+#pragma unroll
+                    for (int i = 0; i < B; ++i) s[u] += Pc[i * ks] * rc[i];
                 }
             }
-            if (P) {
-                // column j of P_cell: a block of the type table (stride B) or
-                // the tile-interleaved block (contiguous)
-                constexpr int TC = Tile<T, B>::TC, TR = Tile<T, B>::TR;
-                const int ht = cell / TC, hl = cell - ht * TC;
-                const T* Pc = ptype ? P + (size_t)ptype[cell] * B * B + j : P + ((size_t)ht * B + j) * TR + hl * B;
-                const int ks = ptype ? B : 1;
-                T s = 0;
 #pragma unroll
-                for (int i = 0; i < B; ++i) s += Pc[i * ks] * rc[i];
-                rp[t] = s;
+            for (int u = 0; u < 2; ++u) {
+                const int e = e0 + u * Ct::NT;
+                if (e >= rows) continue;
+                if (BJ && d) d[t0 + e] = c1 * z[u];
+                if (P) rp[t0 + e] = s[u];
             }
         }
     }

@@ -288,8 +288,8 @@ __global__ __launch_bounds__(kWG) void k_residual_m(LevelArgs<T> L, const T* __r
         if (active) {
             constexpr int TR = Tile<T, B>::TR;
             const int j = threadIdx.x - lc * B;
-            const T* Pc = ptype ? P + (size_t)ptype[cell] * B * B + j : P + ((size_t)tile * B + j) * TR + lc * B;
-            const int ks = ptype ? B : 1;
+            const T* Pc = ptype ? P + (size_t)ptype[cell] * B * B + j : P + (size_t)tile * B * TR + lc * B + j;
+            const int ks = ptype ? B : TR;
             T s[R];
 #pragma unroll
             for (int q = 0; q < R; ++q) s[q] = 0;

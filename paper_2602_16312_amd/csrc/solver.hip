@@ -119,8 +119,8 @@ struct DevLevel {
     int32_t* ptype = nullptr;                              // P_e = table[ptype[e]] when set
     int32_t* cmap = nullptr;                               // tile-ELL: tile position -> cell
     int32_t ntypes = 0;                                    // distinct blocks in that table
-    double *vals64 = nullptr, *dinv64 = nullptr, *P64 = nullptr;
-    float *vals32 = nullptr, *dinv32 = nullptr, *P32 = nullptr;
+    double *vals64 = nullptr, *dinv64 = nullptr, *P64 = nullptr, *R64 = nullptr;
+    float *vals32 = nullptr, *dinv32 = nullptr, *P32 = nullptr, *R32 = nullptr;
     double* bj64 = nullptr;                                // cell-block Jacobi: D_K^-1 (symmetric)
     float* bj32 = nullptr;
     void *vb = nullptr, *vx = nullptr, *vx2 = nullptr, *vr = nullptr, *vd = nullptr, *vd2 = nullptr;
@@ -301,6 +301,13 @@ template <>
 const double* BJof<double>(const DevLevel& L) { return L.bj64; }
 template <>
 const float* BJof<float>(const DevLevel& L) { return L.bj32; }
+// the restriction's blocks: the type table, or the row-by-row layout
+template <typename T>
+static const T* Rof(const DevLevel& L) {
+    if (L.ptype) return Pof<T>(L);
+    if constexpr (sizeof(T) == 4) return L.R32;
+    else return L.R64;
+}
 // the prolongation's blocks: with a type table, its transposed half
 template <typename T>
 static const T* PofT(const DevLevel& L, int b) {
@@ -610,7 +617,7 @@ static void vcycle(dgmg_solver* s, int l, hipStream_t st, T** xres, T** dres, bo
     T* rp = d2;   // free: no step result or pending correction lives there
     if (pending) {
         launch_residual<T, R>(s, L, xzero ? d : x, xzero ? nullptr : d, b, (T*)nullptr, (T*)nullptr, c1, x2,
-                              nullptr, st, Pof<T>(L), rp, L.ptype);
+                              nullptr, st, Rof<T>(L), rp, L.ptype);
         std::swap(x, x2);
         xzero = false;
         pending = false;
@@ -621,7 +628,7 @@ static void vcycle(dgmg_solver* s, int l, hipStream_t st, T** xres, T** dres, bo
             xzero = false;
         }
         launch_residual<T, R>(s, L, x, (const T*)nullptr, b, (T*)nullptr, (T*)nullptr, c1, (T*)nullptr,
-                              nullptr, st, Pof<T>(L), rp, L.ptype);
+                              nullptr, st, Rof<T>(L), rp, L.ptype);
     }
     // the coarse level's first sweep (point Jacobi, single column) starts in
     // the restriction kernel
@@ -1255,9 +1262,10 @@ static void coarse_face_axes(const BlockOp& A, const std::vector<double>& lo, co
     }
 }
 
-// prolongation blocks (row-major per fine entity) in tile-interleaved layout
+// prolongation blocks (row-major per fine entity) in tile-interleaved layout,
+// planes of columns or of rows
 template <typename T>
-static std::vector<T> interleave_P(const std::vector<double>& P, int b, int64_t n) {
+static std::vector<T> interleave_P(const std::vector<double>& P, int b, int64_t n, bool by_rows) {
     const int TC = kWG / b, TR = TC * b;
     const int64_t ntiles = (n + TC - 1) / TC;
     std::vector<T> out((size_t)ntiles * b * TR, (T)0);
@@ -1267,7 +1275,8 @@ static std::vector<T> interleave_P(const std::vector<double>& P, int b, int64_t 
         const int lc = (int)(e - t * TC);
         for (int i = 0; i < b; ++i)
             for (int j = 0; j < b; ++j)
-                out[((size_t)t * b + j) * TR + (size_t)lc * b + i] = (T)P[((size_t)e * b + i) * b + j];
+                out[((size_t)t * b + (by_rows ? i : j)) * TR + (size_t)lc * b + (by_rows ? j : i)] =
+                    (T)P[((size_t)e * b + i) * b + j];
     }
     return out;
 }
@@ -1672,8 +1681,16 @@ static void upload_level(dgmg_solver* s, int l) {
             L.P64 = s->upload(ptab);
             if (s->prec == DGMG_PREC_MIXED) L.P32 = s->upload(convert<float>(ptab));
         } else {
-            L.P64 = s->upload(interleave_P<double>(s->Ph[l], b, A.n));
-            if (s->prec == DGMG_PREC_MIXED) L.P32 = s->upload(interleave_P<float>(s->Ph[l], b, A.n));
+            // column by column for the prolongation and row by row for the
+            // restriction: either way the lanes of a cell read consecutive words
+            // (the precision of the V-cycle)
+            if (s->prec == DGMG_PREC_MIXED) {
+                L.P32 = s->upload(interleave_P<float>(s->Ph[l], b, A.n, false));
+                L.R32 = s->upload(interleave_P<float>(s->Ph[l], b, A.n, true));
+            } else {
+                L.P64 = s->upload(interleave_P<double>(s->Ph[l], b, A.n, false));
+                L.R64 = s->upload(interleave_P<double>(s->Ph[l], b, A.n, true));
+            }
         }
     }
     if (l > 0) {
