@@ -81,6 +81,12 @@ template <typename T, int GEO>
 void cell_step(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* d, T* x, T* r, T* dn, T cd, T cr,
                int assign, int last, const T* bj, hipStream_t st);
 
+// The load vector (k_rhs) on boxes and mapped cells; false where the block size
+// has no such kernel.  cM: mass coefficient of the level's operator.
+template <int GEO>
+bool cell_rhs(int b, const CellArgs<double>& L, int bdf, double chi, double cU, double cM, const double* U,
+              const double* Up, const double* iapp, const double* g, double* out, double* xout, hipStream_t st);
+
 // geometry GEO of a level as a constant
 #define DISPATCH_GEO(gval, ...)                                                        \
     switch (gval) {                                                                    \

@@ -10,5 +10,6 @@ unsigned cell_groups(int geo, int b, int n) {
 
 DGMG_CELL_LAUNCHERS(float, GEO_BOX)
 DGMG_CELL_LAUNCHERS(double, GEO_BOX)
+DGMG_CELL_RHS(GEO_BOX)
 
 }  // namespace dgmg

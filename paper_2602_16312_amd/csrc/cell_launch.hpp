@@ -80,6 +80,27 @@ void cell_step(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* d, 
     else go(std::false_type{});
 }
 
+template <int GEO>
+bool cell_rhs(int b, const CellArgs<double>& L, int bdf, double chi, double cU, double cM, const double* U,
+              const double* Up, const double* iapp, const double* g, double* out, double* xout, hipStream_t st) {
+    const unsigned n = (unsigned)((L.n + 63) / 64);
+    auto go = [&](auto bc) {
+        hipLaunchKernelGGL((k_rhs_cell<decltype(bc)::value, GEO>), dim3(n), dim3(256), 0, st, L, bdf, chi, cU, 1.0 / cM, U, Up,
+                           iapp, g, out, xout);
+        return true;
+    };
+    switch (b) {
+        case 9: return go(std::integral_constant<int, 9>{});
+        case 16: return go(std::integral_constant<int, 16>{});
+        case 25: return go(std::integral_constant<int, 25>{});
+        case 27: return go(std::integral_constant<int, 27>{});
+    }
+    return false;
+}
+#define DGMG_CELL_RHS(GEO)                                                                                          \
+    template bool cell_rhs<GEO>(int, const CellArgs<double>&, int, double, double, double, const double*,           \
+                                const double*, const double*, const double*, double*, double*, hipStream_t);
+
 #define DGMG_CELL_LAUNCHERS(T, GEO)                                                                                              \
     template void cell_apply<T, GEO>(const LaunchEvents&, int, const CellArgs<T>&, const T*, T*, const T*, double*,      \
                                 hipStream_t);                                                                       \

@@ -5,5 +5,6 @@ namespace dgmg {
 
 DGMG_CELL_LAUNCHERS(float, GEO_MAP)
 DGMG_CELL_LAUNCHERS(double, GEO_MAP)
+DGMG_CELL_RHS(GEO_MAP)
 
 }  // namespace dgmg

@@ -1160,4 +1160,66 @@ __global__ __launch_bounds__((cell_threads<B, GEO>())) void k_cheb_step_cell(Cel
     }
 }
 
+// Load vector of the step (k_rhs) on boxes and mapped cells: the mass block is
+// evaluated at the Gauss points, M f = I^T (w (I f)), instead of read (b^2
+// values per cell: 1.5 GB on the 64^3 Q2 cube).  The workgroup forms f row by
+// row, its first wave takes a cell per lane, and the rows are written
+// together.  Step of 64^3 Q2: 349 us, RHSRES here.
+template <int B, int GEO>
+__global__ __launch_bounds__(256) void k_rhs_cell(CellArgs<double> L, int bdf, double chi, double cU, double inv_cM,
+                                                  const double* U, const double* Up, const double* __restrict__ iapp,
+                                                  const double* __restrict__ g, double* __restrict__ b, double* xout) {
+    using Ct = CellTile<double, B, 64, GEO>;
+    constexpr int D = Ct::D, Q = Ct::Q, R = (64 * B + 255) / 256;
+    __shared__ double sh[64 * Ct::SB];
+    const int cell0 = xcd_tile(blockIdx.x, gridDim.x) * 64;
+    const int rows = min(64, L.n - cell0) * B;
+    const size_t t0 = (size_t)cell0 * B;
+    auto at = [&](int e) { return e + (Ct::SB - B) * (e / B); };
+    double u[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int e = min((int)threadIdx.x + k * 256, rows - 1);
+        u[k] = U[t0 + e];
+        const double hist = bdf == 2 ? 4.0 * u[k] - Up[t0 + e] : u[k];
+        const double f = cU * hist + (iapp ? iapp[t0 + e] : 0.0) - chi * g[t0 + e];
+        if ((int)threadIdx.x + k * 256 < rows) sh[at(e)] = f;
+    }
+    __syncthreads();
+    if (threadIdx.x < 64 && (int)threadIdx.x * B < rows) {
+        const MfConst<double>& C = L.mf;
+        double* fc = sh + threadIdx.x * Ct::SB;
+        double v[B];
+#pragma unroll
+        for (int i = 0; i < B; ++i) v[i] = fc[i];
+        if constexpr (GEO == GEO_BOX) {
+            line_pass<double, Q, D, 0, false>(v, C.M1);
+            line_pass<double, Q, D, 1, false>(v, C.M1);
+            if constexpr (D == 3) line_pass<double, Q, D, 2, false>(v, C.M1);
+#pragma unroll
+            for (int i = 0; i < B; ++i) v[i] *= C.vol;
+        } else {
+            constexpr int NE = npack<D>() + 1;             // the last entry of a point is cM w
+            all_passes<double, Q, D, false>(v, C.Ig);
+            const double* K = cell_data<double, B, GEO>(L, cell0 + (int)threadIdx.x, 0);
+#pragma unroll
+            for (int q = 0; q < B; ++q) {
+                const int e = q * NE + NE - 1;
+                v[q] *= K[(size_t)(e / 2) * 128 + e % 2] * inv_cM;
+            }
+            all_passes<double, Q, D, true>(v, C.Ig);
+        }
+#pragma unroll
+        for (int i = 0; i < B; ++i) fc[i] = v[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int e = (int)threadIdx.x + k * 256;
+        if (e >= rows) continue;
+        b[t0 + e] = sh[at(e)];
+        if (xout) xout[t0 + e] = u[k];
+    }
+}
+
 }  // namespace dgmg

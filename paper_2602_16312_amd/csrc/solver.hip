@@ -186,7 +186,7 @@ struct dgmg_solver {
     int64_t* scell = nullptr;
     double* sw = nullptr;
     IonicParams ip{};
-    double cU = 0.0;
+    double cU = 0.0, cM = 0.0;        // history and mass coefficients of the step
     std::vector<void*> allocs;
     int64_t dev_bytes = 0;
     // host copies
@@ -2019,6 +2019,7 @@ int dgmg_setup_levels(const dgmg_hierarchy* h, const dgmg_disc* disc, const dgmg
     s->S = ph->model == DGMG_MODEL_BO ? 3 : 1;
     s->parents = h->parent;
     const double cM = (ph->bdf == 2 ? 1.5 : 1.0) * ph->chi * ph->Cm / ph->dt;
+    s->cM = cM;
     s->cU = ph->bdf == 2 ? ph->chi * ph->Cm / (2.0 * ph->dt) : ph->chi * ph->Cm / ph->dt;
     s->ip.model = ph->model;
     s->ip.S = s->S;
@@ -2313,10 +2314,20 @@ int dgmg_time_step(dgmg_solver* s, dgmg_state* z, double t_next, const double* i
     k_ionic<<<blocks_for(s->N), 256, 0, hs>>>(s->N, s->ip, z->U, z->Uprev, z->W, z->Wprev, z->Wprev, z->g);
     mark(1);
     // load vector; the warm start U_n is written into the U_{n-1} buffer
-    const int cells_per = 256 / s->b;
-    const unsigned nblk = (unsigned)((s->lv[0].n + cells_per - 1) / cells_per);
-    DISPATCH_B(s->b, k_rhs<BV><<<nblk, cells_per * BV, 0, hs>>>(s->lv[0].n, s->ip, s->cU, s->mass, z->U,
-                                                                 z->Uprev, iapp, z->g, s->bwork, z->Uprev));
+    const DevLevel& L0 = s->lv[0];
+    bool done = false;
+    if (L0.geo == GEO_BOX)
+        done = cell_rhs<GEO_BOX>(s->b, cargs<double>(L0), s->bdf, s->ip.chi, s->cU, s->cM, z->U, z->Uprev, iapp, z->g,
+                                 s->bwork, z->Uprev, hs);
+    else if (L0.geo == GEO_MAP)
+        done = cell_rhs<GEO_MAP>(s->b, cargs<double>(L0), s->bdf, s->ip.chi, s->cU, s->cM, z->U, z->Uprev, iapp, z->g,
+                                 s->bwork, z->Uprev, hs);
+    if (!done) {
+        const int cells_per = 256 / s->b;
+        const unsigned nblk = (unsigned)((L0.n + cells_per - 1) / cells_per);
+        DISPATCH_B(s->b, k_rhs<BV><<<nblk, cells_per * BV, 0, hs>>>(L0.n, s->ip, s->cU, s->mass, z->U, z->Uprev, iapp,
+                                                                     z->g, s->bwork, z->Uprev));
+    }
     HIPCHK(hipGetLastError());
     mark(2);
     int rc = pcg(s, s->bwork, z->Uprev, *o, st, hs, s->partial, s->sc);

@@ -109,3 +109,22 @@ def test_faces_held_once_match_tile_slots(mg):
     assert np.array_equal(host(y["auto", "fp64"]), host(y["tile_ell", "fp64"]))
     assert rel(host(y["auto", "mixed"]), host(y["tile_ell", "fp64"])) <= 3e-6
     assert rel(host(z[1]), host(z[0])) <= 2e-5
+
+
+@pytest.mark.parametrize("name,kw", [("c2", dict(n=17, p=3, jitter=0.1, group=[17])), ("c2", dict(n=17, p=4, jitter=0.1, group=[17])),
+                                     ("c3", dict(n=7, group=[7], **CUBE)), ("c3", dict(n=9, group=[3]))])
+def test_step_on_gauss_point_mass(name, kw):
+    """The load vector formed at the Gauss points, in a time step, against the stored mass blocks'."""
+    pr = make_problem(name, **kw)
+    rng = np.random.default_rng(6)
+    U = [rng.uniform(0.0, 1.0, pr["N"]) for _ in range(2)]
+    W = [rng.uniform(0.2, 0.8, pr["S"] * pr["N"]) for _ in range(2)]
+    out = []
+    for layout in ("axis_ell", "auto"):
+        h, s = problem.build(pr, precision="fp64", fine_layout=layout)
+        st = api.State(dev(U[0]), dev(U[1]), dev(W[0]), dev(W[1]), torch.empty(pr["N"], dtype=torch.float64, device="cuda"))
+        say("mass step", name, kw, layout)
+        assert api.time_step(s, st, pr["dt"], iapp=dev(np.full(pr["N"], 0.1)), tol=1e-13)["converged"]
+        out.append((host(st.U), host(st.W)))
+    assert rel(out[1][0], out[0][0]) <= 1e-10              # the time series' bound
+    assert np.array_equal(out[1][1], out[0][1])
