@@ -60,13 +60,32 @@ def cheb_step_bytes(info, prec_bytes, nrhs=1):
     b = info["b"]
     n, nf = info["n_cells"][0], info["n_faces"][0]
     N = n * b
-    if info.get("fine_layout") == "matrix_free":
-        d = info["dim"]
-        return n * (d * (d + 1) // 2) * prec_bytes + 2 * d * 4 * n + (6 * nrhs + 1) * prec_bytes * N
+    if info.get("form", "blocks") != "blocks":
+        return cell_form_values(info) * prec_bytes + 2 * info["dim"] * 4 * n + (6 * nrhs + 1) * prec_bytes * N
     blocks = (n * cell_block_values(info) + nf * face_block_values(info)) * prec_bytes
     adjacency = 4 * (n + 1) + 2 * 2 * 4 * nf
     vectors = (6 * nrhs + 1) * prec_bytes * N
     return blocks + adjacency + vectors
+
+
+def level0_form(info, pr, fine_layout, nrhs):
+    """How the level-0 operator is held: "box" (conductivities of identical
+    boxes), "mapped" (metric data at the Gauss points), "hybrid" (Q1: cell
+    blocks and the faces' metric data) or "blocks"."""
+    if info["fine_layout"] == "matrix_free":
+        return "mapped" if pr.get("jitter") else "box"
+    if fine_layout == "auto" and nrhs == 1 and info["p"] == 1 and info["n_cells"][0] >= 256 and info["n_levels"] > 1:
+        return "hybrid"
+    return "blocks"
+
+
+def cell_form_values(info):
+    """Level-0 operator values of the forms evaluated per cell."""
+    b, d = info["b"], info["dim"]
+    n, nf = info["n_cells"][0], info["n_faces"][0]
+    sym = d * (d + 1) // 2
+    face = nf * (b // round(b ** (1.0 / d))) * (2 * d + 1)
+    return {"box": n * sym, "mapped": n * b * (sym + 1) + face, "hybrid": n * b * (b + 1) // 2 + face}[info["form"]]
 
 
 def cell_block_values(info):
@@ -99,9 +118,8 @@ def level0_working_set(info, prec_bytes, nrhs=1):
     b = info["b"]
     n, nf = info["n_cells"][0], info["n_faces"][0]
     N = n * b
-    if info.get("fine_layout") == "matrix_free":
-        d = info["dim"]
-        ops = n * (d * (d + 1) // 2) * prec_bytes + 2 * d * 4 * n
+    if info.get("form", "blocks") != "blocks":
+        ops = cell_form_values(info) * prec_bytes + 2 * info["dim"] * 4 * n
     else:
         ops = (n * cell_block_values(info) + nf * face_block_values(info)) * prec_bytes + 4 * (n + 1) + 2 * 2 * 4 * nf
     return ops + (6 * nrhs + 1) * prec_bytes * N
@@ -145,9 +163,9 @@ def cheb_step_flops(info, nrhs):
 
 
 COUNTER_FILES = {
-    "c2": "k_cheb_step_f32_b9_c2_counters.md",
-    "c3": "k_cheb_step_mf_f32_b27_c3_counters.md",
-    "c4": "k_cheb_step_f32_b8_c4_counters.md",
+    "c2": "k_cheb_step_cell_f32_b9_c2_counters.md",
+    "c3": "k_cheb_step_cell_f32_b27_c3_counters.md",
+    "c4": "k_cheb_step_cell_f32_b8_c4_counters.md",
     "c4x8": "k_cheb_step_mfma8_c4x8_counters.md",
 }
 
@@ -251,7 +269,9 @@ def run_gpu(pr, precision, steps, warmup, tol, profile_kind=None, nrhs=1, mfma=F
         prof = dict(launches=n, in_run_ms=ms / max(1, n), back_to_back_ms=b2b)
     if step_log is not None:
         write_step_log(step_log, workload, precision, s, st, step, pr, k, steps, tol, nrhs, setup_s, dev)
-    return dict(wall=wall, its=its, setup_s=setup_s, info=s.info(), prof=prof, U=U)
+    info = s.info()
+    info["form"] = level0_form(info, pr, fine_layout, nrhs)
+    return dict(wall=wall, its=its, setup_s=setup_s, info=info, prof=prof, U=U)
 
 
 def write_step_log(f, workload, precision, s, st, step, pr, k, steps, tol, nrhs, setup_s, dev):
@@ -482,7 +502,9 @@ def measure(workload, pr, args, steps, warmup, nrhs):
     ws = level0_working_set(info, 4, nrhs)
     b_ = info["b"]
     achieved = alg / in_run_s / 1e9
-    if nrhs == 1:
+    if nrhs == 1 and info["form"] != "blocks":
+        kname = f"k_cheb_step_cell<float,{b_},{info['form']}> (level 0)"
+    elif nrhs == 1:
         kname = f"k_cheb_step<float,{b_},{info['fine_layout']}{', sparse faces' if info.get('sparse_faces') else ''}> (level 0)"
     elif mfma:
         kname = f"k_cheb_step_mfma8<{info['fine_layout']}> (level 0, 8 columns, v_mfma_f32_4x4x1f32)"
