@@ -26,8 +26,10 @@
  *    A solver is not thread-safe; calls that share a solver must be
  *    serialised by the caller.
  *  - `stream` is a hipStream_t (NULL = default stream).  Work is enqueued on
- *    it; dgmg_pcg_solve and dgmg_time_step synchronise it once per PCG
- *    iteration to read the residual norm for the stopping test.
+ *    it; dgmg_pcg_solve and dgmg_time_step wait once per PCG iteration for the
+ *    residual norm of the stopping test (polled in mapped host memory), may
+ *    queue work on internal buffers ahead of it, and return with the stream
+ *    idle.
  */
 #ifndef DGMG_H
 #define DGMG_H

@@ -97,7 +97,7 @@ struct MetricData {
     std::vector<double> cell, face;
 };
 void metric_data(const Hierarchy& h, const Faces& F, const RefElement& re, const dgmg_disc& disc,
-                 const dgmg_physics& ph, double cM, MetricData& M);
+                 const dgmg_physics& ph, double cM, bool cells, MetricData& M);   // cells: the cells' part too
 
 // Prolongation blocks P_e (n_l x b x b, row-major: fine node i, coarse basis j)
 // from level l+1 to level l, with per-level bounding boxes.

@@ -1164,7 +1164,7 @@ __global__ __launch_bounds__((cell_threads<B, GEO>())) void k_cheb_step_cell(Cel
 // evaluated at the Gauss points, M f = I^T (w (I f)), instead of read (b^2
 // values per cell: 1.5 GB on the 64^3 Q2 cube).  The workgroup forms f row by
 // row, its first wave takes a cell per lane, and the rows are written
-// together.  Step of 64^3 Q2: 349 us, RHSRES here.
+// together.  Step of 64^3 Q2: 349 us, 79 us here.
 template <int B, int GEO>
 __global__ __launch_bounds__(256) void k_rhs_cell(CellArgs<double> L, int bdf, double chi, double cU, double inv_cM,
                                                   const double* U, const double* Up, const double* __restrict__ iapp,

@@ -511,7 +511,7 @@ void assemble_fine(const Hierarchy& h, const Faces& F, const RefElement& re,
 // Metric data of the sum-factorised operator at the Gauss points (the same
 // geometry, weights and penalty as assemble_fine).
 void metric_data(const Hierarchy& h, const Faces& F, const RefElement& re, const dgmg_disc& disc,
-                 const dgmg_physics& ph, double cM, MetricData& M) {
+                 const dgmg_physics& ph, double cM, bool cells, MetricData& M) {
     const int d = re.d, symn = d * (d + 1) / 2;
     const int64_t n = h.n_cells, nf = (int64_t)F.plus.size();
     FaceRef fr;
@@ -519,7 +519,7 @@ void metric_data(const Hierarchy& h, const Faces& F, const RefElement& re, const
     const int qf = fr.qf;
     M.nec = re.qc * (symn + 1);
     M.nef = qf * (2 * d + 1);
-    M.cell.assign((size_t)n * M.nec, 0.0);
+    if (cells) M.cell.assign((size_t)n * M.nec, 0.0);
     M.face.assign((size_t)nf * M.nef, 0.0);
     std::vector<double> vol(n, 0.0);
     auto tensor = [&](int64_t c, double* D) {
@@ -534,6 +534,7 @@ void metric_data(const Hierarchy& h, const Faces& F, const RefElement& re, const
             cell_map(d, X, &re.cq_xi[(size_t)iq * d], nullptr, J, &det, JiT);
             const double w = re.cq_w[iq] * std::fabs(det);
             vol[c] += w;
+            if (!cells) continue;
             double* e = &M.cell[((size_t)c * re.qc + iq) * (symn + 1)];
             for (int k = 0; k < d; ++k)
                 for (int l = k; l < d; ++l) {

@@ -2062,7 +2062,7 @@ int dgmg_setup_levels(const dgmg_hierarchy* h, const dgmg_disc* disc, const dgmg
         s->fine_layout = DGMG_LAYOUT_MATRIX_FREE;
     s->mapped = s->fine_layout == DGMG_LAYOUT_AUTO && s->max_rhs == 1 && cell_block_size(s->b) && s->L > 1 &&
                 h->n_cells >= kMinMappedCells && mg->device_setup;
-    if (s->mapped) metric_data(*h, F, re, *disc, *ph, cM, s->metric);
+    if (s->mapped) metric_data(*h, F, re, *disc, *ph, cM, s->p >= 2, s->metric);
     if (s->fine_layout == DGMG_LAYOUT_MATRIX_FREE) {
         if (!uniform_boxes(*h, s->mf_h))
             fail(DGMG_EUNSUPPORTED, "the matrix-free fine level needs identical axis-aligned box cells");
@@ -2223,7 +2223,17 @@ int dgmg_setup_levels(const dgmg_hierarchy* h, const dgmg_disc* disc, const dgmg
             s->has_adjoint = true;
         }
         HIPCHK(hipDeviceSynchronize());
-        if (!s->roctx) record_directions(s);   // the ranges are per launch
+        // (roctx ranges are per launch; where recording fails the solver launches
+        // one by one)
+        if (!s->roctx) {
+            try {
+                record_directions(s);
+            } catch (const Error&) {
+                (void)hipGetLastError();
+                if (s->g_first) (void)hipGraphExecDestroy(s->g_first);
+                s->g_first = s->g_next = nullptr;
+            }
+        }
         s->on_device = true;
     }
     s->info.t_upload = now_s() - t6;
