@@ -306,14 +306,14 @@ int dgmg_pcg_solve(dgmg_solver* s, const double* b, double* x,
  * call (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc): the same solve, bit-identical results, with the
  * reduction scratch (block partials and the 8 CG scalar slots) in a static
- * per-GPU device array of 1 MiB instead of the solver's buffers.  It calls
+ * per-GPU device array of 1.25 MiB instead of the solver's buffers.  It calls
  * no hipMalloc, hipFree or allocating library routine; the solver's set-up
  * resolved the array's device address.  Every call on one GPU shares that
  * array and its contents persist between calls (the scalar slots are
  * cleared by a fill kernel on `stream` at entry), so calls that overlap on
  * one GPU, from any solver or stream, race and must be serialised by the
- * caller.  Limit: the solve needs 48 + max(ceil(N / 256), level-0
- * workgroups) doubles of the array's 131,072 (N up to about 31M DoFs);
+ * caller.  Limit: 48 + max(ceil(N / 256), level-0 workgroups of up to
+ * 256 / b cells) at most 131,072 (N up to about 31M DoFs);
  * larger solvers get DGMG_EINVAL and must use dgmg_pcg_solve.  Other
  * errors as for dgmg_pcg_solve. */
 int dgmg_pcg_solve_noalloc(dgmg_solver* s, const double* b, double* x,

@@ -2,8 +2,8 @@
 //
 // Layout on the device (one level, scalar type T = double or float):
 //  * vectors: cell-major, DoF (K, i) at K*B + i;
-//  * operator: "tile-ELL".  Cells are grouped in tiles of TC = 256/B cells
-//    (one workgroup, thread = (cell in tile, row i)).  Tile t owns ns_t slots
+//  * operator: "tile-ELL".  Cells are grouped in tiles of TC = tile_cells(B)
+//    cells (one workgroup, thread = (cell in tile, row i)).  Tile t owns ns_t slots
 //    (its cell blocks, then one slot per neighbour entry, ns_t = 1 + largest
 //    neighbour count in the tile); slot s holds, for every cell of the tile,
 //    the B x B block coupling that cell to its s-th column cell, already
@@ -92,14 +92,24 @@ constexpr int slot_group() {
 
 // Block sizes whose cells the block layouts keep inside one wave: lane l of
 // wave w holds row l % B of tile cell w (64/B) + l / B, the lanes past
-// (64/B) B stay idle, and the tile keeps its 256/B cells.  A cell's B lanes
+// (64/B) B stay idle, and a tile holds 4 (64/B) cells.  That is 256/B, but for
+// b = 25: 8 cells instead of 10.  A cell's B lanes
 // then share gathered vector values by lane shuffles (ds_bpermute, the LDS
 // crossbar) instead of each loading all B values through the address unit.
 template <int B>
 constexpr bool whole_wave_cells() {
-    return B == 4 || B == 8 || B == 9 || B == 16 || B == 64;
+    return B == 4 || B == 8 || B == 9 || B == 16 || B == 25 || B == 64;
 }
-static_assert(4 * (64 / 9) == 256 / 9 && 4 * (64 / 8) == 256 / 8, "wave-aligned tiles keep 256/B cells");
+static_assert(4 * (64 / 9) == tile_cells(9) && 4 * (64 / 25) == tile_cells(25), "wave-aligned tiles");
+// Tile slots of b = 25 with FP32 values of one vector gather directly: B
+// contiguous values per cell, mostly broadcast, cost less than B shuffles (150^2
+// jittered Q4 cells, 1296-cell level, one step: 6.4 us direct, 7.3 us shared, 6.7
+// us with the tiles of 10 cells).  Two vectors or FP64 values are shared:
+// residual 7.5 -> 6.4 us, FP64 step 15.9 -> 12.4 us and residual 16.9 -> 15.3 us.
+template <typename T, int B, bool VB>
+constexpr bool share_gathers() {
+    return B != 25 || VB || sizeof(T) == 8;
+}
 
 // (A v) at row (tile*TC + lc, i) of the tile's thread (lc, i), v = va (+ vb
 // when VB).  Loads of a group of G slots -- block values and the gathered
@@ -158,7 +168,7 @@ __device__ __forceinline__ T ell_row_apply(const LevelArgs<T>& L, int tile, int 
 #pragma unroll
             for (int j = 0; j < B; ++j) a[q][j] = As[(size_t)j * TR];
         }
-        if constexpr (WW) {
+        if constexpr (WW && share_gathers<T, B, VB>()) {
             T xq[G];
 #pragma unroll
             for (int q = 0; q < G; ++q) xq[q] = gather_own<T, B, VB>(va, vb, nbq[q], i);
@@ -605,7 +615,7 @@ template <typename T, int B>
 __global__ __launch_bounds__(kWG) void k_block_jacobi(int32_t n, const T* __restrict__ Dinv,
                                                       const T* __restrict__ v, T* __restrict__ y, T alpha,
                                                       T beta, T* __restrict__ x, T* __restrict__ vcopy) {
-    constexpr int TC = Tile<T, B>::TC;
+    constexpr int TC = kWG / B;
     const int lc = threadIdx.x / B;
     const int cell = blockIdx.x * TC + lc;
     if (lc >= TC || cell >= n) return;

@@ -22,10 +22,19 @@ constexpr int dim_of() {
     return (B == 8 || B == 27 || B == 64) ? 3 : 2;
 }
 
+// Cells per tile: 256 / b, but 8 (two whole cells per wave) for b = 25.  The
+// values that a cell gathers are then shared by lane shuffles, which is worth
+// the idle lanes: axis-ELL level of 1024 cells, FP64 step 8.7 -> 7.1 us and
+// residual 10.8 -> 6.2 us, FP32 5.6 -> 4.9 and 6.5 -> 4.6 us.  b = 27 keeps 9
+// cells that straddle waves: with 8 its FP64 level products gain as much (slots,
+// 1728 cells, step 38.4 -> 28.5 us), but in mixed precision the narrower
+// workgroups cost a time step of 64^3 Q2 boxes 9.93 ms instead of 9.89.
+__host__ __device__ constexpr int tile_cells(int b) { return b == 25 ? 8 : kWG / b; }
+
 template <typename T, int B>
 struct Tile {
-    static constexpr int TC = kWG / B;   // cells per tile / workgroup
-    static constexpr int TR = TC * B;    // rows per tile
+    static constexpr int TC = tile_cells(B);  // cells per tile / workgroup
+    static constexpr int TR = TC * B;         // rows per tile
 };
 
 // Nodes per axis of a block size.

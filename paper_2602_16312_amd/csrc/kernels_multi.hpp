@@ -22,6 +22,22 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Cells per workgroup of the multi-column kernels, whatever the tile holds: they
+// share no gathered values between lanes of b = 25, so that the idle lanes of
+// its 8-cell tiles buy them nothing (128^2 cells, 8 columns, FP32
+// residual: 128 us with 10 cells, 138 us with 8).
+constexpr int column_cells(int b) { return kWG / b; }
+// Thread x of workgroup g holds row x % B of cell g column_cells(B) + x / B; the
+// cell's blocks lie at slot lc of storage tile `tile`.
+#define DGMG_GROUP_THREAD(T, B)                                                                \
+    const int lg_ = (int)threadIdx.x / B, ti = (int)threadIdx.x - lg_ * B;                     \
+    const int grp_ = xcd_tile(blockIdx.x, gridDim.x), cell = grp_ * column_cells(B) + lg_;     \
+    const bool active = lg_ < column_cells(B) && cell < L.n;                                   \
+    [[maybe_unused]] const int tile = column_cells(B) == Tile<T, B>::TC ? grp_ : cell / Tile<T, B>::TC; \
+    [[maybe_unused]] const int lc = cell - tile * Tile<T, B>::TC;                              \
+    [[maybe_unused]] const int ri = lc * B + ti;                                               \
+    const int t = cell * B + ti;
+
 // acc[r] += (A (va + vb))[row, r] for the tile thread (lc, i), slot by slot:
 // one coalesced block column value per (slot, j) and the R contiguous
 // gathered values of the column cell.
@@ -69,13 +85,12 @@ __device__ __forceinline__ void segment_accumulate(const T* __restrict__ va, con
 }
 
 template <typename T, int B, int R, bool VB>
-__device__ __forceinline__ void ell_row_apply_m(const LevelArgs<T>& L, int tile, int lc,
+__device__ __forceinline__ void ell_row_apply_m(const LevelArgs<T>& L, int tile, int lc, int i,
                                                 const T* __restrict__ va, const T* __restrict__ vb,
                                                 T* acc) {
     constexpr int TC = Tile<T, B>::TC, TR = Tile<T, B>::TR;
-    const int i = threadIdx.x - lc * B;
     const int s0 = L.slot_ptr[tile], ns = L.slot_ptr[tile + 1] - s0;
-    const T* __restrict__ A = L.vals + (size_t)s0 * B * TR + threadIdx.x;
+    const T* __restrict__ A = L.vals + (size_t)s0 * B * TR + lc * B + i;
     const int32_t* __restrict__ nbp = L.snb + (size_t)s0 * TC + lc;
     T* cs = segment_buffer<T, B, R>();
     for (int s = 0; s < ns; ++s) {
@@ -91,13 +106,12 @@ __device__ __forceinline__ void ell_row_apply_m(const LevelArgs<T>& L, int tile,
 // planes (plane k: A[i][i+k] and, at row i-k, A[i][i-k]), then the lower
 // faces read transposed.
 template <typename T, int B, int R, bool VB>
-__device__ __forceinline__ void ax_row_apply_m(const LevelArgs<T>& L, int tile, int lc, int cell,
+__device__ __forceinline__ void ax_row_apply_m(const LevelArgs<T>& L, int tile, int lc, int i, int cell,
                                                const T* __restrict__ va, const T* __restrict__ vb,
                                                T* acc) {
     constexpr int TC = Tile<T, B>::TC, TR = Tile<T, B>::TR, D = dim_of<B>();
     constexpr int P0 = ax_cell_planes(B), TP = ax_tile_planes(B, D);
-    const int i = threadIdx.x - lc * B;
-    const T* __restrict__ A = L.vals + (size_t)tile * TP * TR + threadIdx.x;
+    const T* __restrict__ A = L.vals + (size_t)tile * TP * TR + lc * B + i;
     auto column = [&](int nb, int j, int r) -> T {
         const size_t k = ((size_t)nb * B + j) * R + r;
         return VB ? va[k] + vb[k] : va[k];
@@ -164,12 +178,12 @@ __device__ __forceinline__ void ax_row_apply_m(const LevelArgs<T>& L, int tile, 
 }
 
 template <typename T, int B, int R, bool VB, bool AX>
-__device__ __forceinline__ void row_apply_m(const LevelArgs<T>& L, int tile, int lc, int cell,
+__device__ __forceinline__ void row_apply_m(const LevelArgs<T>& L, int tile, int lc, int i, int cell,
                                             const T* __restrict__ va, const T* __restrict__ vb, T* acc) {
     if constexpr (AX)
-        ax_row_apply_m<T, B, R, VB>(L, tile, lc, cell, va, vb, acc);
+        ax_row_apply_m<T, B, R, VB>(L, tile, lc, i, cell, va, vb, acc);
     else
-        ell_row_apply_m<T, B, R, VB>(L, tile, lc, va, vb, acc);
+        ell_row_apply_m<T, B, R, VB>(L, tile, lc, i, va, vb, acc);
 }
 
 template <bool AX, bool VB>
@@ -204,7 +218,7 @@ template <typename T, int B, int R, bool AX>
 __global__ __launch_bounds__(kWG) void k_apply_m(LevelArgs<T> L, const T* __restrict__ va,
                                                  T* __restrict__ y, const T* __restrict__ w,
                                                  double* __restrict__ partial) {
-    DGMG_TILE_THREAD(T, B)
+    DGMG_GROUP_THREAD(T, B)
     double contrib[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) contrib[r] = 0.0;
@@ -212,7 +226,7 @@ __global__ __launch_bounds__(kWG) void k_apply_m(LevelArgs<T> L, const T* __rest
         T acc[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) acc[r] = 0;
-        row_apply_m<T, B, R, false, AX>(L, tile, lc, cell, va, nullptr, acc);
+        row_apply_m<T, B, R, false, AX>(L, tile, lc, ti, cell, va, nullptr, acc);
         T* yp = y + (size_t)t * R;
 #pragma unroll
         for (int r = 0; r < R; ++r) yp[r] = acc[r];
@@ -238,7 +252,7 @@ __global__ __launch_bounds__(kWG) void k_residual_m(LevelArgs<T> L, const T* __r
                                                     T* __restrict__ xout, double* __restrict__ partial,
                                                     const T* __restrict__ P, T* __restrict__ rp,
                                                     const int32_t* __restrict__ ptype) {
-    DGMG_TILE_THREAD(T, B)
+    DGMG_GROUP_THREAD(T, B)
     double contrib[R];
     T rr[R];
 #pragma unroll
@@ -260,7 +274,7 @@ __global__ __launch_bounds__(kWG) void k_residual_m(LevelArgs<T> L, const T* __r
 #pragma unroll
             for (int q = 0; q < R; ++q) xs[q] = VB ? va[k0 + q] + vb[k0 + q] : va[k0 + q];
         }
-        if constexpr (!MF) row_apply_m<T, B, R, VB, AX>(L, tile, lc, cell, va, vb, acc);
+        if constexpr (!MF) row_apply_m<T, B, R, VB, AX>(L, tile, lc, ti, cell, va, vb, acc);
         const T di = L.dinv[t];
 #pragma unroll
         for (int q = 0; q < R; ++q) {
@@ -287,8 +301,8 @@ __global__ __launch_bounds__(kWG) void k_residual_m(LevelArgs<T> L, const T* __r
         __syncthreads();
         if (active) {
             constexpr int TR = Tile<T, B>::TR;
-            const int j = threadIdx.x - lc * B;
-            const T* Pc = ptype ? P + (size_t)ptype[cell] * B * B + j : P + (size_t)tile * B * TR + lc * B + j;
+            const T* Pc = ptype ? P + (size_t)ptype[cell] * B * B + ti : P + (size_t)tile * B * TR + ri;
+            const int l0 = (int)threadIdx.x - ti;   // the cell's row 0
             const int ks = ptype ? B : TR;
             T s[R];
 #pragma unroll
@@ -297,7 +311,7 @@ __global__ __launch_bounds__(kWG) void k_residual_m(LevelArgs<T> L, const T* __r
             for (int k = 0; k < B; ++k) {
                 const T pk = Pc[k * ks];
 #pragma unroll
-                for (int q = 0; q < R; ++q) s[q] += pk * rs[(lc * B + k) * R + q];
+                for (int q = 0; q < R; ++q) s[q] += pk * rs[(l0 + k) * R + q];
             }
 #pragma unroll
             for (int q = 0; q < R; ++q) rp[(size_t)t * R + q] = s[q];
@@ -353,12 +367,12 @@ __global__ __launch_bounds__(kWG) void k_cheb_step_m(LevelArgs<T> L, const T* __
                                                      T* __restrict__ x, T* __restrict__ r,
                                                      T* __restrict__ dn, T cd, T cr, int assign,
                                                      int last) {
-    DGMG_TILE_THREAD(T, B)
+    DGMG_GROUP_THREAD(T, B)
     if (!active) return;
     T acc[R];
 #pragma unroll
     for (int q = 0; q < R; ++q) acc[q] = 0;
-    row_apply_m<T, B, R, false, AX>(L, tile, lc, cell, d, nullptr, acc);
+    row_apply_m<T, B, R, false, AX>(L, tile, lc, ti, cell, d, nullptr, acc);
     cheb_epilogue_m<T, R>(L, t, acc, d, x, r, dn, cd, cr, assign, last);
 }
 

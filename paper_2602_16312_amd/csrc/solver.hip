@@ -350,6 +350,8 @@ template <typename T, int B>
 static unsigned tiles_for(const DevLevel& L) {
     return (unsigned)((L.n + Tile<T, B>::TC - 1) / Tile<T, B>::TC);
 }
+// workgroups of the kernels that take cells across storage tiles: cw cells each
+static unsigned groups_for(const DevLevel& L, int cw) { return (unsigned)((L.n + cw - 1) / cw); }
 // number of workgroups (tiles) of the block kernels on a level; also the
 // number of partial sums they write
 template <typename T>
@@ -381,7 +383,7 @@ static void launch_apply(dgmg_solver* s, const DevLevel& L, const T* va, T* y, c
         } else if constexpr (LYV == LY_AXS) {
             fail(DGMG_EUNSUPPORTED, "sparse face blocks have no multi-column kernels");
         } else {
-            DISPATCH_B(s->b, klaunch(ps, k_apply_m<T, BV, R, AXV>, tiles_for<T, BV>(L), kWG, st, largs<T>(L), va, y,
+            DISPATCH_B(s->b, klaunch(ps, k_apply_m<T, BV, R, AXV>, groups_for(L, column_cells(BV)), kWG, st, largs<T>(L), va, y,
                                                                                             w, partial));
         }
     });
@@ -449,10 +451,10 @@ static void launch_residual(dgmg_solver* s, const DevLevel& L, const T* va, cons
             }
             if (!done) {
                 if (vb) {
-                    DISPATCH_B(s->b, klaunch(ps, k_residual_m<T, BV, R, true, AXV>, tiles_for<T, BV>(L), kWG, st,
+                    DISPATCH_B(s->b, klaunch(ps, k_residual_m<T, BV, R, true, AXV>, groups_for(L, column_cells(BV)), kWG, st,
                                          largs<T>(L), va, vb, rhs, r, d, c1, xout, partial, P, rp, ptype));
                 } else {
-                    DISPATCH_B(s->b, klaunch(ps, k_residual_m<T, BV, R, false, AXV>, tiles_for<T, BV>(L), kWG, st,
+                    DISPATCH_B(s->b, klaunch(ps, k_residual_m<T, BV, R, false, AXV>, groups_for(L, column_cells(BV)), kWG, st,
                                          largs<T>(L), va, vb, rhs, r, d, c1, xout, partial, P, rp, ptype));
                 }
             }
@@ -502,7 +504,7 @@ static void launch_step(dgmg_solver* s, const DevLevel& L, const T* d, T* x, T* 
                 }
             }
             if (!done) {
-                DISPATCH_B(s->b, klaunch(ps, k_cheb_step_m<T, BV, R, AXV>, tiles_for<T, BV>(L), kWG, st,
+                DISPATCH_B(s->b, klaunch(ps, k_cheb_step_m<T, BV, R, AXV>, groups_for(L, column_cells(BV)), kWG, st,
                                      largs<T>(L), d, x, r, dn, cd, cr, assign, last));
             }
         }
@@ -575,7 +577,7 @@ static void vcycle(dgmg_solver* s, int l, hipStream_t st, T** xres, T** dres, bo
         } else if (xzero && !pending) {
             if constexpr (R == 1) {
                 if (bjp) {   // r = b and d = c1 D^-1 b in one pass
-                    DISPATCH_B(s->b, k_block_jacobi<T, BV><<<tiles_for<T, BV>(L), kWG, 0, st>>>(
+                    DISPATCH_B(s->b, k_block_jacobi<T, BV><<<groups_for(L, kWG / BV), kWG, 0, st>>>(
                                          L.n, bjp, b, d, T(0), c1, (T*)nullptr, r));
                 } else {
                     k_cheb_init0<T><<<blocks_for(L.N), kWG, 0, st>>>(L.N, b, dinv, r, d, c1);
@@ -930,7 +932,7 @@ static int pcg_multi(dgmg_solver* s, const double* b, double* x, const dgmg_pcg_
     const int64_t N = s->N, NR = N * R;
     const unsigned nb = blocks_for(N);
     DevLevel& L0 = s->lv[0];
-    const unsigned nt = level_tiles<double>(s, L0);
+    const unsigned nt = groups_for(L0, column_cells(s->b));   // partials of the block kernels
     launch_residual<double, R>(s, L0, x, nullptr, b, s->r, nullptr, 1.0, nullptr, s->partial, st);
     k_finalize_m<R><<<1, kWG, 0, st>>>(nt, s->partial, s->sc, 0, 0);
     if (o.tol_mode == DGMG_TOL_REL_B) {
@@ -1031,7 +1033,7 @@ static void build_nbr(const BlockOp& A, std::vector<int32_t>& ptr, std::vector<i
 }
 
 // Tile-ELL layout of a level operator (see kernels.hpp): per tile of
-// TC = 256/b cells, slot 0 holds the cell blocks and slot r >= 1 the r-th
+// TC = tile_cells(b) cells, slot 0 holds the cell blocks and slot r >= 1 the r-th
 // neighbour block of every cell, oriented for the row cell and interleaved
 // so that the tile's rows are contiguous for each (slot, column).
 struct TileEll {
@@ -1047,7 +1049,7 @@ struct TileEll {
 // it saves at least 3% of the slots.  once: only the neighbours' slots, as
 // references to the face blocks (at least one slot per tile).
 static TileEll build_tile_ell(const BlockOp& A, int window = 0, bool once = false) {
-    const int b = A.b, TC = kWG / b, TR = TC * b;
+    const int b = A.b, TC = tile_cells(b), TR = TC * b;
     const int64_t n = A.n, ntiles = (n + TC - 1) / TC;
     std::vector<int32_t> ptr, cell, code;
     build_nbr(A, ptr, cell, code);
@@ -1158,7 +1160,7 @@ static bool faces_are_nodal(const BlockOp& A, const std::vector<int64_t>& upface
 // sparse: store the face blocks in the sparse-face form when they are nodal
 static AxisEll build_axis_ell(const BlockOp& A, const std::vector<int>& axis, int d, bool with_vals,
                               bool sparse = false) {
-    const int b = A.b, TC = kWG / b, TR = TC * b, P0 = ax_cell_planes(b), TP = ax_tile_planes(b, d);
+    const int b = A.b, TC = tile_cells(b), TR = TC * b, P0 = ax_cell_planes(b), TP = ax_tile_planes(b, d);
     const int64_t n = A.n, ntiles = (n + TC - 1) / TC;
     if ((int64_t)axis.size() != A.nf) fail(DGMG_EINVAL, "face axis list does not match the operator");
     AxisEll E;
@@ -1266,7 +1268,7 @@ static void coarse_face_axes(const BlockOp& A, const std::vector<double>& lo, co
 // planes of columns or of rows
 template <typename T>
 static std::vector<T> interleave_P(const std::vector<double>& P, int b, int64_t n, bool by_rows) {
-    const int TC = kWG / b, TR = TC * b;
+    const int TC = tile_cells(b), TR = TC * b;
     const int64_t ntiles = (n + TC - 1) / TC;
     std::vector<T> out((size_t)ntiles * b * TR, (T)0);
 #pragma omp parallel for schedule(static)
@@ -1717,6 +1719,11 @@ static int64_t pcg_partials(const dgmg_solver* s) {
     return (int64_t)std::max(blocks_for(s->N), level_tiles<double>(s, s->lv[0])) + 16;
 }
 
+// The same with 256/b level-0 cells per partial, whatever the storage tile.
+static int64_t limit_partials(const dgmg_solver* s) {
+    return (int64_t)std::max(blocks_for(s->N), (unsigned)((s->lv[0].n + kWG / s->b - 1) / (kWG / s->b))) + 16;
+}
+
 // ------------------------------------------------- static PCG scratch
 // Reduction scratch of dgmg_pcg_solve_noalloc: the 8 scalar slots of pcg()
 // at offset 0 and its block partials from kScratchPartial on.  A file-scope
@@ -1725,7 +1732,10 @@ static int64_t pcg_partials(const dgmg_solver* s) {
 // (in host code the name is a stand-in, not a device address); it uses the
 // address hipGetSymbolAddress returns for the device, resolved once per
 // device at set-up.
-constexpr int64_t kScratchDoubles = 131072;   // 1 MiB per GPU
+// A solver is accepted when 256/b level-0 cells per partial fit kScratchLimit;
+// the array also holds the 10/8 as many partials of the 8-cell tiles (b = 25).
+constexpr int64_t kScratchLimit = 131072;
+constexpr int64_t kScratchDoubles = kScratchLimit / 8 * 10;   // 1.25 MiB per GPU
 constexpr int64_t kScratchPartial = 32;       // partials start 256 bytes in
 static __device__ __align__(256) double scratch[kScratchDoubles];
 constexpr int kMaxScratchDevices = 64;
@@ -2282,11 +2292,11 @@ int dgmg_pcg_solve_noalloc(dgmg_solver* s, const double* b, double* x, const dgm
     API_BEGIN
     need_device(s);
     if (!b || !x || !o || !st) fail(DGMG_EINVAL, "null argument");
-    const int64_t need = kScratchPartial + pcg_partials(s);
-    if (need > kScratchDoubles)
+    const int64_t need = kScratchPartial + std::min(pcg_partials(s), limit_partials(s));
+    if (need > kScratchLimit || kScratchPartial + pcg_partials(s) > kScratchDoubles)
         fail(DGMG_EINVAL, "dgmg_pcg_solve_noalloc: this solver needs " + std::to_string(need) +
                               " doubles of reduction scratch; the static array holds " +
-                              std::to_string(kScratchDoubles) + " (use dgmg_pcg_solve)");
+                              std::to_string(kScratchLimit) + " (use dgmg_pcg_solve)");
     if (!s->scratch) fail(DGMG_EINVAL, "the static PCG scratch was not resolved at set-up");
     hipStream_t hs = (hipStream_t)stream;
     // the array keeps the previous call's contents: clear the scalar slots
