@@ -1014,7 +1014,7 @@ __global__ __launch_bounds__((cell_threads<B, GEO>())) void k_apply_cell(CellArg
             contrib += (double)wv[u] * (double)a;
         }
     }
-    if (partial) wg_sum_store(contrib, partial);
+    if (partial) wg_sum_store<Ct::NT>(contrib, partial);
 }
 
 // Residual with the epilogues of k_residual.
@@ -1090,7 +1090,7 @@ __global__ __launch_bounds__((cell_threads<B, GEO>())) void k_residual_cell(
             }
         }
     }
-    if (partial) wg_sum_store(contrib, partial);
+    if (partial) wg_sum_store<Ct::NT>(contrib, partial);
 }
 
 // One inner Chebyshev step, as k_cheb_step.

@@ -46,8 +46,12 @@ __host__ __device__ constexpr int node_tan(int j, int a, int q) {
 }
 
 // Workgroup sum of a double into partial[blockIdx.x] (deterministic order).
+// NT: threads of the workgroup; one slot per wave (the cell kernels run three
+// to seven).
+template <int NT = kWG>
 __device__ __forceinline__ void wg_sum_store(double v, double* partial) {
-    __shared__ double red[kWG / 64];
+    constexpr int NW = NT / 64;
+    __shared__ double red[NW];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -55,7 +59,7 @@ __device__ __forceinline__ void wg_sum_store(double v, double* partial) {
     __syncthreads();
     if (threadIdx.x == 0) {
         double s = 0.0;
-        for (int k = 0; k < (int)(blockDim.x >> 6); ++k) s += red[k];
+        for (int k = 0; k < NW; ++k) s += red[k];
         partial[blockIdx.x] = s;
     }
 }
