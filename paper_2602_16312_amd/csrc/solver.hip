@@ -831,10 +831,18 @@ static int pcg(dgmg_solver* s, const double* b, double* x, const dgmg_pcg_opts& 
                hipStream_t st, double* partial, double* sc) {
     RangeScope range(s, "dgmg PCG");
     // the call returns, or fails, with the stream idle (also when work was
-    // queued ahead of a test that ended it)
+    // queued ahead of a test that ended it); a return reports what that work met
     struct StreamIdle {
         hipStream_t st;
-        ~StreamIdle() { (void)hipStreamSynchronize(st); }
+        bool waited = false;
+        int returning(int rc) {
+            waited = true;
+            HIPCHK(hipStreamSynchronize(st));
+            return rc;
+        }
+        ~StreamIdle() {
+            if (!waited) (void)hipStreamSynchronize(st);
+        }
     } idle{st};
     const int64_t N = s->N;
     const unsigned nb = blocks_for(N);
@@ -862,7 +870,7 @@ static int pcg(dgmg_solver* s, const double* b, double* x, const dgmg_pcg_opts& 
     stats->converged = 0;
     if (r0 == 0.0 || r0 <= thresh) {
         stats->converged = 1;
-        return DGMG_OK;
+        return idle.returning(DGMG_OK);
     }
     const bool graphs = s->g_next && !o.flexible && partial == s->partial && s->prof_kind < 0 && !s->roctx;
     auto first = [&]() {
@@ -914,13 +922,13 @@ static int pcg(dgmg_solver* s, const double* b, double* x, const dgmg_pcg_opts& 
         if (!std::isfinite(rn)) fail(DGMG_ENAN, "non-finite residual");
         if (rn <= thresh) {
             stats->converged = 1;
-            return DGMG_OK;
+            return idle.returning(DGMG_OK);
         }
         rate = rn / rlast;
         rlast = rn;
         if (!ahead && its < o.max_it) next();
     }
-    return DGMG_NOT_CONVERGED;
+    return idle.returning(DGMG_NOT_CONVERGED);
 }
 
 // PCG on R columns at once: every A_0 apply, V-cycle and reduction serves all

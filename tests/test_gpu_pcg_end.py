@@ -1,0 +1,40 @@
+"""How a PCG call ends: an error of the work that was still queued is reported."""
+import pytest
+
+from gpu_util import need_gpu, say
+from stream_shim import run_child
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    need_gpu()
+
+
+def test_an_error_of_the_last_wait_is_reported(tmp_path):
+    say("error of the last wait (child process)")
+    out = run_child(tmp_path, r"""
+pr = make_problem("c2", n=16, group=[4])
+h, s = problem.build(pr, precision="mixed")
+b = torch.from_numpy(np.random.default_rng(1).standard_normal(pr["N"])).cuda()
+zero = torch.zeros_like(b)
+x = torch.zeros_like(b)
+for solve in (api.pcg_solve, api.pcg_solve_noalloc):
+    # converged, cut off, nothing to do
+    for rhs, opts in ((b, dict(tol=1e-8)), (b, dict(tol=1e-8, max_it=2)), (zero, dict())):
+        x.zero_()
+        rc = solve(s, rhs, x, **opts)["rc"]
+        shim.shim_fail(1)
+        try:
+            x.zero_()
+            solve(s, rhs, x, **opts)
+            print("missed", solve.__name__, opts, flush=True)
+        except F.DGMGError as e:
+            print("reported", e.code, flush=True)
+        shim.shim_fail(0)
+        x.zero_()
+        assert solve(s, rhs, x, **opts)["rc"] == rc
+""")
+    assert out.count("reported -4") == 6, out
+    assert "missed" not in out
