@@ -887,7 +887,7 @@ static int pcg(dgmg_solver* s, const double* b, double* x, const dgmg_pcg_opts& 
     float* rb = s->prec == DGMG_PREC_MIXED ? (float*)L0.vb : nullptr;
     const bool init0 = update_starts_sweep(s);
     const double c1_0 = 1.0 / (0.5 * (L0.lam_hi + L0.lam_lo));
-    first();
+    if (o.max_it > 0) first();
     double rlast = r0, rate = 0.0;   // residual norm and its last reduction factor
     while (its < o.max_it) {
         if (s->prec == DGMG_PREC_MIXED)

@@ -38,3 +38,33 @@ for solve in (api.pcg_solve, api.pcg_solve_noalloc):
 """)
     assert out.count("reported -4") == 6, out
     assert "missed" not in out
+
+
+def coarse_solves(s, b, **opts):
+    """(V-cycles that a solve from zero ran, its iterations)"""
+    from gpu_util import torch
+    from paper_2602_16312_amd import api
+    x = torch.zeros_like(b)
+    api.profile_begin(s, "coarse", s.info()["n_levels"] - 1)
+    its = api.pcg_solve(s, b, x, **opts)["its"]
+    n, _ = api.profile_end(s)
+    return n, its
+
+
+def small_solver(name, mg, **kw):
+    import numpy as np
+    from gpu_util import dev
+    from paper_2602_16312_amd import problem
+    from workloads import make_problem
+    pr = make_problem(name, **kw)
+    h, s = problem.build(pr, precision="fp64", **mg)
+    return s, dev(np.random.default_rng(1).standard_normal(pr["N"]))
+
+
+def test_no_direction_for_no_iterations():
+    s, b = small_solver("c2", {}, n=16, group=[4])
+    say("max_it 0")
+    assert coarse_solves(s, b, max_it=0) == (0, 0)
+    say("max_it 1 and 2")
+    assert coarse_solves(s, b, max_it=1) == (1, 1)
+    assert coarse_solves(s, b, max_it=2) == (2, 2)
