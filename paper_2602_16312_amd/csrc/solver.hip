@@ -903,11 +903,17 @@ static int pcg(dgmg_solver* s, const double* b, double* x, const dgmg_pcg_opts& 
         HIPCHK(hipGetLastError());
         // The GPU would idle while the host waits for ||r|| and queues more.
         // The next direction depends on the test only in whether it is
-        // wanted, and touches neither x nor r: it is queued ahead unless the
-        // last reduction factor says that this test may end the solve (within
-        // a factor 100).  Step of 256x256 Q2 cells: 1,272 us with a stream
-        // synchronisation per test, 1,250 us polling, 1,234 us queued ahead.
-        const bool ahead = its + 1 < o.max_it && (its == 0 ? r0 > 1e4 * thresh : rlast * rate > 100.0 * thresh);
+        // wanted, and touches neither x nor r: it is queued ahead unless this
+        // test may end the solve, when a whole V-cycle would be thrown away: with
+        // one level (an exact inverse: one iteration), when the last reduction
+        // factor comes within 100 of the threshold, or its cube under it (CG
+        // converges faster than linearly: on 4x4 Q1 cells with the cell-block
+        // smoother by 2e-3, then by 1e-7).  Step of 256x256 Q2 cells: 1,272 us
+        // with a stream synchronisation per test, 1,250 us polling, 1,234 us
+        // queued ahead.
+        const bool ends = its == 0 ? s->L == 1 || r0 <= 1e4 * thresh
+                                   : rlast * rate <= 100.0 * thresh || rlast * rate * rate * rate <= thresh;
+        const bool ahead = its + 1 < o.max_it && !ends;
         if (ahead) next();
         wait_scalars(s, st, seq);
         ++its;

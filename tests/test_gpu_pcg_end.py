@@ -68,3 +68,15 @@ def test_no_direction_for_no_iterations():
     say("max_it 1 and 2")
     assert coarse_solves(s, b, max_it=1) == (1, 1)
     assert coarse_solves(s, b, max_it=2) == (2, 2)
+
+
+# one level (an exact inverse); a spectrum so small that the second reduction is the square of the first
+@pytest.mark.parametrize("name,kw,mg", [("c1", dict(n=8, group=[]), dict()), ("c2", dict(n=6, group=[], jitter=0.1), dict()),
+                                        ("e1", dict(n=4, group=[2]), dict(jacobi="cell_block")),
+                                        ("c1", dict(n=16), dict()), ("c2", dict(n=16, group=[4]), dict())])
+@pytest.mark.parametrize("tol", [1e-4, 1e-8, 1e-10])
+def test_no_direction_is_thrown_away(name, kw, mg, tol):
+    s, b = small_solver(name, mg, **kw)
+    say("directions", name, kw, tol)
+    n, its = coarse_solves(s, b, tol=tol)
+    assert its > 0 and n == its
