@@ -27,9 +27,12 @@
  *    serialised by the caller.
  *  - `stream` is a hipStream_t (NULL = default stream).  Work is enqueued on
  *    it; dgmg_pcg_solve and dgmg_time_step wait once per PCG iteration for the
- *    residual norm of the stopping test (polled in mapped host memory), may
- *    queue work on internal buffers ahead of it, and return with the stream
- *    idle.
+ *    residual norm of the stopping test, may queue work on internal buffers
+ *    ahead of it, and return with the stream idle.  The wait polls mapped host
+ *    memory and keeps the calling thread's core busy for the whole solve; where
+ *    the process chose hipDeviceScheduleBlockingSync for the device, it is a
+ *    stream synchronisation per iteration with nothing queued ahead, and with
+ *    hipDeviceScheduleYield every poll yields.
  */
 #ifndef DGMG_H
 #define DGMG_H

@@ -28,6 +28,7 @@
 #include <mutex>
 #include <new>
 #include <stdexcept>
+#include <thread>
 #include <type_traits>
 #include <vector>
 
@@ -704,15 +705,30 @@ static double read_scalars(dgmg_solver* s, hipStream_t st, int R = 1, const doub
     HIPCHK(hipStreamSynchronize(st));
     return s->sc_host[0];
 }
+// How the host waits, as the process chose it for the device (hipSetDeviceFlags):
+// a blocking wait leaves the core to others.
+enum class HostWait { Spin, Yield, Block };
+static HostWait host_wait() {
+    unsigned f = 0;
+    if (hipGetDeviceFlags(&f) != hipSuccess) return HostWait::Spin;
+    f &= hipDeviceScheduleMask;
+    return f == hipDeviceScheduleBlockingSync ? HostWait::Block
+           : f == hipDeviceScheduleYield      ? HostWait::Yield : HostWait::Spin;
+}
 // Waits for the finalize kernel launched with `seq`, which writes the 8 scalars
 // and then seq into the mapped pinned buffer.  Polling that word sees the
 // scalars before a stream synchronisation returns; every 20 ms or so the stream is
 // queried (which queues a marker behind the work), so that a failed launch or
 // kernel ends the wait.
-static void wait_scalars(dgmg_solver* s, hipStream_t st, uint64_t seq) {
+static void wait_scalars(dgmg_solver* s, hipStream_t st, uint64_t seq, HostWait how) {
+    if (how == HostWait::Block) {
+        HIPCHK(hipStreamSynchronize(st));
+        return;
+    }
     const auto* word = reinterpret_cast<const std::atomic<uint64_t>*>(s->mirror + 8);
     for (unsigned spin = 1; word->load(std::memory_order_acquire) != seq; ++spin) {
-        __builtin_ia32_pause();
+        if (how == HostWait::Yield) std::this_thread::yield();
+        else __builtin_ia32_pause();
         if (spin % (1 << 20) != 0) continue;
         const hipError_t e = hipStreamQuery(st);
         if (e == hipErrorNotReady) continue;
@@ -851,6 +867,7 @@ static int pcg(dgmg_solver* s, const double* b, double* x, const dgmg_pcg_opts& 
     // r = b - A x, ||r||^2
     launch_residual<double>(s, L0, x, nullptr, b, s->r, nullptr, 1.0, nullptr, partial, st);
     const bool relb = o.tol_mode == DGMG_TOL_REL_B;
+    const HostWait how = host_wait();
     uint64_t seq = ++s->seq;
     k_finalize<<<1, kWG, 0, st>>>(nt, partial, sc, 0, 0, relb ? nullptr : s->mirror_dev, seq);
     double bnorm = 0.0;
@@ -859,7 +876,7 @@ static int pcg(dgmg_solver* s, const double* b, double* x, const dgmg_pcg_opts& 
         k_finalize<<<1, kWG, 0, st>>>(nb, partial, sc, 6, 0, s->mirror_dev, seq);
     }
     HIPCHK(hipGetLastError());
-    wait_scalars(s, st, seq);
+    wait_scalars(s, st, seq, how);
     const double r0 = std::sqrt(s->mirror[0]);
     if (o.tol_mode == DGMG_TOL_REL_B) bnorm = std::sqrt(s->mirror[6]);
     if (!std::isfinite(r0)) fail(DGMG_ENAN, "non-finite initial residual");
@@ -913,9 +930,9 @@ static int pcg(dgmg_solver* s, const double* b, double* x, const dgmg_pcg_opts& 
         // queued ahead.
         const bool ends = its == 0 ? s->L == 1 || r0 <= 1e4 * thresh
                                    : rlast * rate <= 100.0 * thresh || rlast * rate * rate * rate <= thresh;
-        const bool ahead = its + 1 < o.max_it && !ends;
+        const bool ahead = its + 1 < o.max_it && !ends && how != HostWait::Block;   // a blocking wait is for all of it
         if (ahead) next();
-        wait_scalars(s, st, seq);
+        wait_scalars(s, st, seq, how);
         ++its;
         const double gam = s->mirror[1], pq = s->mirror[2];
         const double rn = std::sqrt(s->mirror[0]);
@@ -2216,7 +2233,7 @@ int dgmg_setup_levels(const dgmg_hierarchy* h, const dgmg_disc* disc, const dgmg
         s->sc = s->dalloc<double>(8 * R);
         HIPCHK(hipMemset(s->sc, 0, 8 * R * sizeof(double)));
         HIPCHK(hipHostMalloc((void**)&s->sc_host, 8 * R * sizeof(double), hipHostMallocDefault));
-        HIPCHK(hipHostMalloc((void**)&s->mirror, 9 * sizeof(double), hipHostMallocMapped));
+        HIPCHK(hipHostMalloc((void**)&s->mirror, 9 * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent));
         std::memset(s->mirror, 0, 9 * sizeof(double));
         HIPCHK(hipHostGetDevicePointer((void**)&s->mirror_dev, s->mirror, 0));
         s->act = s->dalloc<int32_t>(R);

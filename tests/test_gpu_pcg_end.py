@@ -80,3 +80,32 @@ def test_no_direction_is_thrown_away(name, kw, mg, tol):
     say("directions", name, kw, tol)
     n, its = coarse_solves(s, b, tol=tol)
     assert its > 0 and n == its
+
+
+def test_the_wait_follows_the_devices_scheduling_mode(tmp_path):
+    """A process that chose blocking waits gets a synchronisation per stopping test,
+    one that did not a poll (one synchronisation, at the end); the same solution."""
+    body = r"""
+mode = MODE
+if mode:
+    assert hip.hipSetDeviceFlags(ctypes.c_uint(mode)) == 0
+pr = make_problem("c2", n=16, group=[4])
+h, s = problem.build(pr, precision="mixed")
+b = torch.from_numpy(np.random.default_rng(1).standard_normal(pr["N"])).cuda()
+for k, solve in enumerate((api.pcg_solve, api.pcg_solve_noalloc)):
+    x = torch.zeros_like(b)
+    torch.cuda.synchronize()
+    before = shim.shim_calls()
+    its = solve(s, b, x, tol=1e-9)["its"]
+    print("calls", shim.shim_calls() - before, its, repr(float(x.norm())), flush=True)
+"""
+    got = {}
+    for mode in (0, 2, 4):   # automatic, yield, blocking
+        say("scheduling mode (child process)", mode)
+        out = run_child(tmp_path, body.replace("MODE", str(mode)))
+        got[mode] = [l.split()[1:] for l in out.splitlines() if l.startswith("calls")]
+        assert len(got[mode]) == 2, out
+    for k in range(2):
+        calls, its = {m: int(v[k][0]) for m, v in got.items()}, int(got[0][k][1])
+        assert calls[0] == 1 and calls[2] == 1 and calls[4] == its + 2   # the first residual's and the end's
+        assert got[0][k][1:] == got[2][k][1:] == got[4][k][1:]
