@@ -68,15 +68,12 @@ def cheb_step_bytes(info, prec_bytes, nrhs=1):
     return blocks + adjacency + vectors
 
 
-def level0_form(info, pr, fine_layout, nrhs):
+def level0_form(solver):
     """How the level-0 operator is held: "box" (conductivities of identical
     boxes), "mapped" (metric data at the Gauss points), "hybrid" (Q1: cell
     blocks and the faces' metric data) or "blocks"."""
-    if info["fine_layout"] == "matrix_free":
-        return "mapped" if pr.get("jitter") else "box"
-    if fine_layout == "auto" and nrhs == 1 and info["p"] == 1 and info["n_cells"][0] >= 256 and info["n_levels"] > 1:
-        return "hybrid"
-    return "blocks"
+    form = solver.forms()["level_form"][0]
+    return form if form in ("box", "mapped", "hybrid") else "blocks"
 
 
 def cell_form_values(info):
@@ -270,7 +267,7 @@ def run_gpu(pr, precision, steps, warmup, tol, profile_kind=None, nrhs=1, mfma=F
     if step_log is not None:
         write_step_log(step_log, workload, precision, s, st, step, pr, k, steps, tol, nrhs, setup_s, dev)
     info = s.info()
-    info["form"] = level0_form(info, pr, fine_layout, nrhs)
+    info["form"] = level0_form(s)
     return dict(wall=wall, its=its, setup_s=setup_s, info=info, prof=prof, U=U)
 
 

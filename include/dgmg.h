@@ -281,6 +281,26 @@ typedef struct {
 } dgmg_solver_info;
 int dgmg_get_info(const dgmg_solver* s, dgmg_solver_info* info);
 
+/* The form in which a level's operator is evaluated.  TILE_ELL, AXIS_ELL and
+ * AXIS_ELL_SPARSE: the stored blocks of those layouts, a thread per row.
+ * FACES_ONCE: as TILE_ELL, with an FP32 copy that holds every face block once.
+ * The others take cells per lane: BOX from the conductivities of identical
+ * boxes, MAPPED from metric data at the Gauss points, HYBRID from the cell
+ * blocks and the faces' metric data (Q1); on agglomerated levels NODAL_BLOCKS
+ * and WHOLE_BLOCKS from stored blocks without and with the entries that vanish
+ * on nested boxes, ROW_BLOCKS from blocks of 64 rows, a wave per block.
+ * dgmg_solver_info.level_layout names the layout that a form stands in for. */
+enum { DGMG_FORM_NONE = 0, DGMG_FORM_TILE_ELL = 1, DGMG_FORM_AXIS_ELL = 2, DGMG_FORM_AXIS_ELL_SPARSE = 3,
+       DGMG_FORM_FACES_ONCE = 4, DGMG_FORM_BOX = 5, DGMG_FORM_MAPPED = 6, DGMG_FORM_HYBRID = 7,
+       DGMG_FORM_NODAL_BLOCKS = 8, DGMG_FORM_WHOLE_BLOCKS = 9, DGMG_FORM_ROW_BLOCKS = 10 };
+/* Forms of the levels (host out, DGMG_MAX_LEVELS; NONE for the coarsest level
+ * and without device data) and whether the PCG replays its search directions as
+ * graphs: 1 yes; 0 no (smoothers of degree 1 rename their buffers, roctx
+ * ranges are per launch); -1 recording them failed at set-up, for the reason
+ * that dgmg_last_error() then gives, and the directions are launched kernel by
+ * kernel. */
+int dgmg_get_forms(const dgmg_solver* s, int32_t* level_form, int32_t* pcg_graphs);
+
 enum { DGMG_TOL_REL_R0 = 0, DGMG_TOL_REL_B = 1, DGMG_TOL_ABS = 2 };
 typedef struct {
     double tol;

@@ -21,7 +21,7 @@ EXPORTS = [
     "dgmg_apply", "dgmg_vcycle", "dgmg_mass_apply", "dgmg_export_level",
     "dgmg_profile_begin", "dgmg_profile_end", "dgmg_kernel_bench", "dgmg_last_error",
     "dgmg_set_sensors", "dgmg_sensor_misfit", "dgmg_adjoint_step", "dgmg_grad_accumulate",
-    "dgmg_pcg_solve_noalloc", "dgmg_set_phase_timing", "dgmg_step_phase_ms",
+    "dgmg_pcg_solve_noalloc", "dgmg_set_phase_timing", "dgmg_step_phase_ms", "dgmg_get_forms",
 ]
 
 dp = C.POINTER(C.c_double)
@@ -128,6 +128,7 @@ def lib():
         L.dgmg_destroy_solver.argtypes = [vp]
         L.dgmg_destroy_solver.restype = None
         L.dgmg_get_info.argtypes = [vp, C.POINTER(SolverInfo)]
+        L.dgmg_get_forms.argtypes = [vp, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
         L.dgmg_pcg_solve.argtypes = [vp, vp, vp, C.POINTER(PCGOpts), C.POINTER(PCGStats), vp]
         L.dgmg_pcg_solve_noalloc.argtypes = [vp, vp, vp, C.POINTER(PCGOpts), C.POINTER(PCGStats), vp]
         L.dgmg_ionic_step.argtypes = [vp] * 7 + [vp]

@@ -168,6 +168,16 @@ class Solver:
                     level_grouped=[bool(v) for v in i.level_grouped[:L]],
                     sparse_faces=bool(i.sparse_faces))
 
+    def forms(self):
+        """dgmg_get_forms: the form in which each level's operator is evaluated, and
+        whether the PCG replays its directions as graphs ("held", "unused", or
+        "failed: " and the reason that recording them failed)."""
+        form, graphs = (C.c_int32 * F.MAX_LEVELS)(), C.c_int32()
+        F.check(F.lib().dgmg_get_forms(self._s, form, C.byref(graphs)))
+        why = "failed: " + F.lib().dgmg_last_error().decode() if graphs.value < 0 else None
+        return dict(level_form=[_FORM_NAMES[v] for v in form[:self.info()["n_levels"]]],
+                    pcg_graphs=why or ("held" if graphs.value else "unused"))
+
     def export_level(self, level, blocks=True):
         """Host copies of a level's FP64 operator and transfer blocks
         (blocks=False: the prolongation, parents and face list only)."""
@@ -195,6 +205,8 @@ class Solver:
 
 
 _LAYOUT_NAMES = {1: "tile_ell", 2: "axis_ell", 3: "matrix_free"}
+_FORM_NAMES = ["none", "tile_ell", "axis_ell", "axis_ell_sparse", "faces_once", "box", "mapped", "hybrid",
+               "nodal_blocks", "whole_blocks", "row_blocks"]
 
 
 def setup_levels(hier, p, D_cell, chi, Cm, dt, model, params, penalty=("paper",),

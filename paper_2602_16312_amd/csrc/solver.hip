@@ -172,6 +172,7 @@ struct dgmg_solver {
     uint64_t seq = 0;                // stopping tests launched
     // the PCG's search directions as graphs (null: launched one by one)
     hipGraphExec_t g_first = nullptr, g_next = nullptr;
+    std::string graph_error;         // why recording them failed
     double* scratch = nullptr;     // this device's static PCG scratch (dgmg_pcg_solve_noalloc)
     int32_t* act = nullptr;        // per-column active mask of multi-column PCG
     int32_t* act_host = nullptr;   // pinned staging of that mask
@@ -2269,10 +2270,11 @@ int dgmg_setup_levels(const dgmg_hierarchy* h, const dgmg_disc* disc, const dgmg
         if (!s->roctx) {
             try {
                 record_directions(s);
-            } catch (const Error&) {
+            } catch (const Error& e) {
                 (void)hipGetLastError();
                 if (s->g_first) (void)hipGraphExecDestroy(s->g_first);
                 s->g_first = s->g_next = nullptr;
+                s->graph_error = e.msg;
             }
         }
         s->on_device = true;
@@ -2300,6 +2302,24 @@ int dgmg_get_info(const dgmg_solver* s, dgmg_solver_info* info) {
     API_BEGIN
     if (!s || !info) fail(DGMG_EINVAL, "null argument");
     *info = s->info;
+    return DGMG_OK;
+    API_END
+}
+
+int dgmg_get_forms(const dgmg_solver* s, int32_t* level_form, int32_t* pcg_graphs) {
+    API_BEGIN
+    if (!s || !level_form || !pcg_graphs) fail(DGMG_EINVAL, "null argument");
+    static const int32_t cell_form[] = {DGMG_FORM_BOX, DGMG_FORM_MAPPED, DGMG_FORM_NODAL_BLOCKS,
+                                        DGMG_FORM_HYBRID, DGMG_FORM_WHOLE_BLOCKS, DGMG_FORM_ROW_BLOCKS};   // by GEO_*
+    for (int l = 0; l < s->L; ++l) {
+        const DevLevel& L = s->lv[l];
+        level_form[l] = !s->on_device || (l == s->L - 1 && s->L > 1) ? DGMG_FORM_NONE
+                        : L.geo >= 0                                 ? cell_form[L.geo]
+                        : L.ax   ? (L.sf ? DGMG_FORM_AXIS_ELL_SPARSE : DGMG_FORM_AXIS_ELL)
+                        : L.once ? DGMG_FORM_FACES_ONCE : DGMG_FORM_TILE_ELL;
+    }
+    *pcg_graphs = s->g_next ? 1 : s->graph_error.empty() ? 0 : -1;
+    if (*pcg_graphs < 0) set_last_error(s->graph_error);
     return DGMG_OK;
     API_END
 }

@@ -1,6 +1,7 @@
 """Child processes whose hipStreamSynchronize is counted, and made to report an
 error on request, by a small library loaded before the HIP runtime (the call
-itself is always passed on, so that the GPU runs as it would)."""
+itself is always passed on, so that the GPU runs as it would).  The library can
+also refuse hipStreamBeginCapture."""
 import os
 import subprocess
 import sys
@@ -9,8 +10,11 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 SHIM = r"""
 static int (*real)(void*);
-static int calls, failing;
-void shim_init(void* f) { real = (int (*)(void*))f; }
+static int (*begin)(void*, int);
+static int calls, failing, refusing;
+void shim_init(void* f, void* g) { real = (int (*)(void*))f; begin = (int (*)(void*, int))g; }
+void shim_refuse(int on) { refusing = on; }
+int hipStreamBeginCapture(void* stream, int mode) { return refusing ? 999 : begin(stream, mode); }
 int shim_calls(void) { return calls; }
 void shim_fail(int on) { failing = on; }
 int hipStreamSynchronize(void* stream) {
@@ -32,7 +36,7 @@ from workloads import make_problem
 F.lib()
 path = next(l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l)
 hip = ctypes.CDLL(path)
-shim.shim_init(ctypes.cast(hip.hipStreamSynchronize, ctypes.c_void_p))
+shim.shim_init(*(ctypes.cast(f, ctypes.c_void_p) for f in (hip.hipStreamSynchronize, hip.hipStreamBeginCapture)))
 """
 
 
