@@ -1170,8 +1170,9 @@ struct AxisEll {
     bool sparse = false;   // face blocks in the sparse-face form (kernels.hpp)
 };
 // Whether every face block vanishes outside the rows of the lower cell's
-// upper face and the columns of the upper cell's lower face (exact zeros).
-static bool faces_are_nodal(const BlockOp& A, const std::vector<int64_t>& upface, int d) {
+// upper face and the columns of the upper cell's lower face: exactly, or up
+// to rtol of the block's largest entry.
+static bool faces_are_nodal(const BlockOp& A, const std::vector<int64_t>& upface, int d, double rtol = 0.0) {
     const int b = A.b, q = ax_nodes_1d(b, d);
     if (q < 2 || std::pow(q, d) != b) return false;
     const int64_t n = A.n;
@@ -1182,13 +1183,23 @@ static bool faces_are_nodal(const BlockOp& A, const std::vector<int64_t>& upface
             const int64_t f = upface[(size_t)a * n + c];
             if (f < 0) continue;
             const double* F = &A.fblk[(size_t)f * b * b];
+            double top = 0.0, off = 0.0;
             for (int i = 0; i < b; ++i)
-                for (int j = 0; j < b; ++j)
-                    if (node_coord(i, a, q) != q - 1 && node_coord(j, a, q) != 0 && F[(size_t)i * b + j] != 0.0)
-                        ok = false;
+                for (int j = 0; j < b; ++j) {
+                    const double v = std::fabs(F[(size_t)i * b + j]);
+                    double& m = node_coord(i, a, q) != q - 1 && node_coord(j, a, q) != 0 ? off : top;
+                    m = v > m || std::isnan(v) ? v : m;
+                }
+            if (!(off <= rtol * top)) ok = false;
         }
     return ok;
 }
+// On boxes nested in boxes the other entries are zero and the Galerkin products
+// leave their roundoff: at most 1.4e-16 of the block's largest entry on Q3 and
+// Q4 squares of 60 to 104 cells a side (none on most other sizes).  Boxes that
+// overlap have 2e-3 to 2e-1 there (cells jittered by a tenth; by a thousandth
+// 2e-5 to 3e-4).
+constexpr double kNodalRoundoff = 16 * 2.2204460492503131e-16;
 // sparse: store the face blocks in the sparse-face form when they are nodal
 static AxisEll build_axis_ell(const BlockOp& A, const std::vector<int>& axis, int d, bool with_vals,
                               bool sparse = false) {
@@ -1597,7 +1608,7 @@ static void upload_level(dgmg_solver* s, int l) {
                 (b == 64 || cell_block_size(b))) {
                 Ec = build_axis_ell(Ao, s->axisl[l], s->dim, false);
                 upf = upper_faces(Ao, s->axisl[l], s->dim);
-                blk = b == 64 ? GEO_ROW : faces_are_nodal(Ao, upf, s->dim) ? GEO_BLK : b <= 9 ? GEO_BLD : -1;
+                blk = b == 64 ? GEO_ROW : faces_are_nodal(Ao, upf, s->dim, kNodalRoundoff) ? GEO_BLK : b <= 9 ? GEO_BLD : -1;
             }
             if (blk >= 0) {
                 auto pack = [&](auto tag) {

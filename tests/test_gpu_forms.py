@@ -22,6 +22,10 @@ def _gpu():
     ("e1", dict(n=64, p=3, group=[2, 8]), {}, ["box", "nodal_blocks", "none"]),
     ("e1", dict(n=128, p=4, group=[2, 16]), {}, ["box", "nodal_blocks", "none"]),
     ("e1", dict(n=64, p=4, group=[2, 8]), {}, ["box", "axis_ell", "none"]),
+    # nested boxes whose face blocks hold roundoff where others of the degree hold zeros
+    ("e1", dict(n=60, p=3, group=[2, 10]), {}, ["box", "nodal_blocks", "none"]),
+    ("e1", dict(n=104, p=3, group=[2, 13]), {}, ["box", "nodal_blocks", "none"]),
+    ("e1", dict(n=104, p=4, group=[2, 13]), {}, ["box", "nodal_blocks", "none"]),
     ("c3", dict(n=32, group=[2, 8]), {}, ["box", "nodal_blocks", "none"]),
     ("c3", dict(n=8, p=3, group=[2, 2]), {}, ["box", "row_blocks", "none"]),
     ("c2", dict(n=68, group=[2, 17]), {}, ["mapped", "whole_blocks", "none"]),
