@@ -17,6 +17,16 @@ struct Error {
 [[noreturn]] void fail(int code, const std::string& msg);
 void set_last_error(const std::string& msg);
 
+// Doubles of static scratch that dgmg_pcg_solve_noalloc counts for a solver, of
+// which it accepts kScratchLimit: 48 and the larger of the vector kernels'
+// workgroups and the level-0 workgroups of 256 / b cells, in whatever form and
+// tiles the level is held.
+constexpr int64_t kScratchLimit = 131072;
+constexpr int64_t noalloc_doubles(int64_t dofs, int64_t cells, int b) {
+    const int64_t v = (dofs + 255) / 256, g = (cells + 256 / b - 1) / (256 / b);
+    return 48 + (v > g ? v : g);
+}
+
 // ---------------------------------------------------------------- reference
 constexpr int kMaxQ = 5;                      // points per direction, p <= 4
 struct RefElement {

@@ -1762,11 +1762,6 @@ static int64_t pcg_partials(const dgmg_solver* s) {
     return (int64_t)std::max(blocks_for(s->N), level_tiles<double>(s, s->lv[0])) + 16;
 }
 
-// The same with 256/b level-0 cells per partial, whatever the storage tile.
-static int64_t limit_partials(const dgmg_solver* s) {
-    return (int64_t)std::max(blocks_for(s->N), (unsigned)((s->lv[0].n + kWG / s->b - 1) / (kWG / s->b))) + 16;
-}
-
 // ------------------------------------------------- static PCG scratch
 // Reduction scratch of dgmg_pcg_solve_noalloc: the 8 scalar slots of pcg()
 // at offset 0 and its block partials from kScratchPartial on.  A file-scope
@@ -1775,9 +1770,8 @@ static int64_t limit_partials(const dgmg_solver* s) {
 // (in host code the name is a stand-in, not a device address); it uses the
 // address hipGetSymbolAddress returns for the device, resolved once per
 // device at set-up.
-// A solver is accepted when 256/b level-0 cells per partial fit kScratchLimit;
+// What is accepted depends on the mesh and the degree alone (noalloc_doubles);
 // the array also holds the 10/8 as many partials of the 8-cell tiles (b = 25).
-constexpr int64_t kScratchLimit = 131072;
 constexpr int64_t kScratchDoubles = kScratchLimit / 8 * 10;   // 1.25 MiB per GPU
 constexpr int64_t kScratchPartial = 32;       // partials start 256 bytes in
 static __device__ __align__(256) double scratch[kScratchDoubles];
@@ -2354,7 +2348,7 @@ int dgmg_pcg_solve_noalloc(dgmg_solver* s, const double* b, double* x, const dgm
     API_BEGIN
     need_device(s);
     if (!b || !x || !o || !st) fail(DGMG_EINVAL, "null argument");
-    const int64_t need = kScratchPartial + std::min(pcg_partials(s), limit_partials(s));
+    const int64_t need = noalloc_doubles(s->N, s->lv[0].n, s->b);
     if (need > kScratchLimit || kScratchPartial + pcg_partials(s) > kScratchDoubles)
         fail(DGMG_EINVAL, "dgmg_pcg_solve_noalloc: this solver needs " + std::to_string(need) +
                               " doubles of reduction scratch; the static array holds " +
