@@ -1411,9 +1411,9 @@ static double* device_spd_inverse(dgmg_solver* s, const std::vector<double>& a, 
 }
 
 // Identical axis-aligned boxes: every cell's corners are X_0 + sum_k bit_k h_k e_k
-// with the same h.  Tolerance: 1e-12 of the largest coordinate (at least 1), or
-// with of_extent > 0 that fraction of the smallest h_k.  Returns false otherwise.
-static bool uniform_boxes(const Hierarchy& h, double* ext, double of_extent = 0.0) {
+// with the same h.  Tolerance: 1e-12 of the largest coordinate (at least 1), and
+// at most of_extent of the smallest h_k.  Returns false otherwise.
+static bool uniform_boxes(const Hierarchy& h, double* ext, double of_extent = 1e-8) {
     const int d = h.dim, nc = 1 << d;
     double scale = 0.0;
     for (double v : h.xyz) scale = std::max(scale, std::fabs(v));
@@ -1423,7 +1423,7 @@ static bool uniform_boxes(const Hierarchy& h, double* ext, double of_extent = 0.
         ext[k] = h.xyz[(size_t)v1 * d + k] - h.xyz[(size_t)v0 * d + k];
         if (!(ext[k] > 0)) return false;
     }
-    if (of_extent > 0) tol = of_extent * *std::min_element(ext, ext + d);
+    tol = std::min(tol, of_extent * *std::min_element(ext, ext + d));
     for (int64_t c = 0; c < h.n_cells; ++c) {
         const int64_t* cv = &h.cells[(size_t)c * nc];
         const double* x0 = &h.xyz[(size_t)cv[0] * d];
@@ -2106,9 +2106,9 @@ int dgmg_setup_levels(const dgmg_hierarchy* h, const dgmg_disc* disc, const dgmg
     // AUTO (single column): matrix-free on meshes of identical boxes for p >= 2,
     // and for p = 1 from kMinMappedCells on; metric data on other meshes from
     // that size on (p = 1: beside the cell blocks); else the axis-ELL blocks.
-    // p = 1 asks for boxes to 1e-12 of their extents: the tolerance in absolute
-    // coordinates takes any mesh smaller than 1e-12 for boxes, and one in
-    // metres with cells of 0.1 mm if they are distorted by less than 1e-8
+    // p = 1, whose other forms are as exact, asks for boxes to 1e-12 of their
+    // extents: 1e-12 in absolute coordinates are 1e-8 of a cell of 0.1 mm in a
+    // mesh in metres
     if (s->fine_layout == DGMG_LAYOUT_AUTO && s->max_rhs == 1 &&
         (s->p >= 2 ? uniform_boxes(*h, s->mf_h)
                    : s->L > 1 && h->n_cells >= kMinMappedCells && uniform_boxes(*h, s->mf_h, 1e-12)))

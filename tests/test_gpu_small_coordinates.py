@@ -1,4 +1,4 @@
-"""Q1 meshes in units in which an absolute tolerance on coordinates says nothing: the
+"""Meshes in units in which an absolute tolerance on coordinates says nothing: the
 operator of slightly distorted cells against the oracle's rows."""
 import numpy as np
 import pytest
@@ -6,6 +6,7 @@ import pytest
 from gpu_util import dev, host, need_gpu, rel, say, torch
 from oracle.assemble import assemble
 from paper_2602_16312_amd import api, problem
+from paper_2602_16312_amd._ffi import DGMGError
 from workloads import make_problem
 
 pytestmark = pytest.mark.gpu
@@ -30,3 +31,25 @@ def test_q1_rows_match_oracle(scale, jitter, form):
         say("small coordinates", scale, jitter, prec)
         api.apply(s, 0, dev(x), y, prec)
         assert rel(host(y), ref) <= tol, prec
+
+
+@pytest.mark.parametrize("p", [2, 3])
+def test_distorted_cells_of_any_unit_are_no_boxes(p):
+    def tiny(name, **kw):   # the time step shrinks with the area, so that the mass term stays
+        pr = make_problem(name, n=17, p=p, group=[17], **kw)
+        return {**pr, "xyz": pr["xyz"] * 1e-13, "dt": pr["dt"] * 1e-26}
+
+    pr = tiny("c2", jitter=0.1)
+    with pytest.raises(DGMGError) as e:
+        problem.build(pr, precision="mixed", fine_layout="matrix_free")
+    assert e.value.code == -6
+    h, s = problem.build(pr, precision="mixed")
+    M, A = assemble(pr, None)
+    ref = ((1.5 * pr["chi"] * pr["Cm"] / pr["dt"]) * M + A) @ (x := np.random.default_rng(4).standard_normal(pr["N"]))
+    y = torch.empty(pr["N"], dtype=torch.float64, device="cuda")
+    for prec, tol in (("fp64", 1e-13), ("mixed", 3e-6)):
+        say("small coordinates", p, prec)
+        api.apply(s, 0, dev(x), y, prec)
+        assert rel(host(y), ref) <= tol, prec
+    h, s = problem.build(tiny("e1"), precision="mixed", fine_layout="matrix_free")   # real boxes still are
+    assert s.info()["fine_layout"] == "matrix_free"
