@@ -89,14 +89,18 @@ static inline unsigned blocks_for(int64_t threads) { return (unsigned)((threads 
 // against 12.0 us.  p = 1, 1,024 squares 2.7 against 3.7 us (FP64), boxes 2.6 us;
 // the shell of 1.0M hexahedra 148 against 214 us.
 constexpr int64_t kMinMappedCells = 256;
-// Agglomerated levels in a grid whose blocks go to the cell kernels.  From
-// b = 25 on their straight-line products exceed the instruction cache, which a
-// small level pays on every launch: a step at 1,024 cells of 25 DoFs (FP64)
-// took 8.8 us against 8.6 us by rows, at 1,000 of 27 DoFs 7.7 against 6.6 us,
-// at 4,096 8.2 against 12.1 us.  b = 9: 1,024 cells 2.9 against 3.5 us, FP64
-// 4.0 against 4.5 us; b = 16 boxes 4.9 against 5.8 us (FP64), whole blocks of
-// 16 were slower (7.2 against 6.2 us at 4,096 cells) and stay by rows.
-static int64_t min_stored_cells(int b) { return b <= 16 ? 256 : b == 64 ? 1 : 2000; }
+// Agglomerated levels in a grid whose blocks go to the cell kernels.  Sweeps of a
+// V-cycle (12 steps, 6 residuals) by rows and by cells, us:
+//   b = 4: 256 cells FP32 46.5 / 47.0, FP64 54.7 / 47.6; 324 cells 49.6 / 45.8, 57.4 / 47.0
+//   b = 9, 1,024 cells: a step 3.5 / 2.9, FP64 4.5 / 4.0; b = 8, 343 cells 67.9 / 51.5, 83.9 / 69.8
+//   b = 16 boxes, 256 cells 72.5 / 59.5, FP64 101 / 95.7 (whole blocks of 16 were slower,
+//   a step 7.2 against 6.2 at 4,096 cells, and stay by rows)
+// From b = 25 on the cells' straight-line products exceed the instruction cache,
+// which a small level pays on every launch, and by rows a level of one
+// workgroup per CU is done in one round:
+//   b = 25: 2,025 cells 88.3 / 93.5, FP64 131 / 150; 2,116 cells 104 / 93.7, 198 / 150
+//   b = 27: 2,197 cells 136 / 138, FP64 311 / 348; 2,744 cells 222 / 138, 530 / 357
+static int64_t min_stored_cells(int b) { return b <= 16 ? 256 : b == 64 ? 1 : 256 * tile_cells(b) + 1; }
 // coarse problems above this size are factorised on the device at set-up
 constexpr int64_t kHostCholeskyMax = 4096;
 

@@ -27,6 +27,11 @@ def _gpu():
     ("e1", dict(n=104, p=3, group=[2, 13]), {}, ["box", "nodal_blocks", "none"]),
     ("e1", dict(n=104, p=4, group=[2, 13]), {}, ["box", "nodal_blocks", "none"]),
     ("c3", dict(n=32, group=[2, 8]), {}, ["box", "nodal_blocks", "none"]),
+    # on either side of the sizes where rows and slots are as fast
+    ("e1", dict(n=90, p=4, group=[2, 9]), {}, ["box", "axis_ell", "none"]),
+    ("e1", dict(n=92, p=4, group=[2, 23]), {}, ["box", "nodal_blocks", "none"]),
+    ("c3", dict(n=26, group=[2, 13]), {}, ["box", "axis_ell", "none"]),
+    ("c3", dict(n=28, group=[2, 14]), {}, ["box", "nodal_blocks", "none"]),
     ("c3", dict(n=8, p=3, group=[2, 2]), {}, ["box", "row_blocks", "none"]),
     ("c2", dict(n=68, group=[2, 17]), {}, ["mapped", "whole_blocks", "none"]),
     ("c2", dict(n=68, p=1, group=[2, 17]), {}, ["hybrid", "whole_blocks", "none"]),
