@@ -101,6 +101,10 @@ constexpr int64_t kMinMappedCells = 256;
 //   b = 25: 2,025 cells 88.3 / 93.5, FP64 131 / 150; 2,116 cells 104 / 93.7, 198 / 150
 //   b = 27: 2,197 cells 136 / 138, FP64 311 / 348; 2,744 cells 222 / 138, 530 / 357
 static int64_t min_stored_cells(int b) { return b <= 16 ? 256 : b == 64 ? 1 : 256 * tile_cells(b) + 1; }
+// Irregular levels of 3D Q1 agglomerates with their face blocks held once.  Sweeps
+// of a V-cycle in FP32 by slots and with faces once: 5,426 cells 127 / 134 us, 8,828
+// 141 / 144, 9,220 155 / 151, 10,212 171 / 142, 14,659 214 / 184.
+constexpr int64_t kMinFacesOnce = 9000;
 // coarse problems above this size are factorised on the device at set-up
 constexpr int64_t kHostCholeskyMax = 4096;
 
@@ -1692,9 +1696,8 @@ static void upload_level(dgmg_solver* s, int l) {
         L.dinv64 = s->upload(dinv);
         if (s->prec == DGMG_PREC_MIXED) {
             // Q1 hexahedra's irregular levels hold each face block once in
-            // FP32 from this size on: a step at 14,659 cells 10.0 against 12.2
-            // us, at 1,957 8.4 against 7.9 us
-            if (b == 8 && l > 0 && s->max_rhs == 1 && s->fine_layout != DGMG_LAYOUT_TILE_ELL && A.n >= 4000 && A.nf > 0) {
+            // FP32 from kMinFacesOnce cells on
+            if (b == 8 && l > 0 && s->max_rhs == 1 && s->fine_layout != DGMG_LAYOUT_TILE_ELL && A.n >= kMinFacesOnce && A.nf > 0) {
                 TileEll O = build_tile_ell(A, 16, true);
                 L.slot_once = s->upload(O.slot_ptr);
                 L.once = s->upload(O.once);

@@ -32,6 +32,8 @@ def _gpu():
     ("e1", dict(n=92, p=4, group=[2, 23]), {}, ["box", "nodal_blocks", "none"]),
     ("c3", dict(n=26, group=[2, 13]), {}, ["box", "axis_ell", "none"]),
     ("c3", dict(n=28, group=[2, 14]), {}, ["box", "nodal_blocks", "none"]),
+    ("c4", dict(h=0.036, agglo=("rtree_str", 8, 4)), {}, ["hybrid", "tile_ell", "tile_ell", "none"]),
+    ("c4", dict(h=0.034, agglo=("rtree_str", 8, 4)), {}, ["hybrid", "faces_once", "tile_ell", "none"]),
     ("c3", dict(n=8, p=3, group=[2, 2]), {}, ["box", "row_blocks", "none"]),
     ("c2", dict(n=68, group=[2, 17]), {}, ["mapped", "whole_blocks", "none"]),
     ("c2", dict(n=68, p=1, group=[2, 17]), {}, ["hybrid", "whole_blocks", "none"]),
