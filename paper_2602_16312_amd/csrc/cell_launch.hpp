@@ -9,53 +9,62 @@ namespace dgmg {
 // such workgroup per CU, smaller groups spread the cells over more CUs (a
 // lane's scattered loads of its cell then share an address unit with fewer
 // others).  Measured per step, 16 / 64 cells: 1,728 3D Q2 boxes 5.1 / 5.8 us,
-// 8,000 6.8 / 6.0 us, 64,000 34 / 15 us.  3D Q3 cells take four lanes each.
-static int cells_per_group(int geo, int b, int n) {
-    return geo == GEO_ROW ? 1 : b == 64 || n <= 16 * 256 ? 16 : 64;
+// 8,000 6.8 / 6.0 us, 64,000 34 / 15 us.  3D Q3 cells take four lanes each, and
+// with the cell-block smoother (bj), whose epilogue reads 64 values per row,
+// groups of 4 on small levels: 512 cells, 4 / 16 cells: FP64 8.7 / 14.5 us, FP32
+// 6.3 / 8.7 us; 1,728 cells 15.2 / 15.3, 7.5 / 8.9; 4,096 cells 28.7 / 25.1, 17.1 / 14.9.
+static int cells_per_group(int geo, int b, int n, bool bj) {
+    return geo == GEO_ROW ? 1 : b == 64 ? (bj && n <= 8 * 256 ? 4 : 16) : n <= 16 * 256 ? 16 : 64;
 }
 
-// block size BV and cells per workgroup NC as constants
-#define DISPATCH_CELL(bval, nval, ...)                                                        \
+// block size BV and cells per workgroup NC as constants (BJ: of the kernels with
+// the cell-block term)
+#define DISPATCH_CELL(bval, nc, ...)                                                          \
     if constexpr (GEO == GEO_ROW) {                                                           \
         if ((bval) == 64) { constexpr int BV = 64, NC = 1; __VA_ARGS__; return; }             \
     } else if constexpr (GEO == GEO_BOX) {                                                    \
+        if constexpr (BJ) {                                                                   \
+            if ((bval) == 64 && (nc) == 4) { constexpr int BV = 64, NC = 4; __VA_ARGS__; return; } \
+        }                                                                                     \
         if ((bval) == 64) { constexpr int BV = 64, NC = 16; __VA_ARGS__; return; }            \
     }                                                                                         \
-    if constexpr (GEO != GEO_MAP && GEO != GEO_ROW) {                                                         \
-        if ((bval) == 4) { DISPATCH_NC(4, nval, __VA_ARGS__) return; }                        \
-        if ((bval) == 8) { DISPATCH_NC(8, nval, __VA_ARGS__) return; }                        \
+    if constexpr (GEO != GEO_MAP && GEO != GEO_ROW) {                                         \
+        if ((bval) == 4) { DISPATCH_NC(4, nc, __VA_ARGS__) return; }                          \
+        if ((bval) == 8) { DISPATCH_NC(8, nc, __VA_ARGS__) return; }                          \
     }                                                                                         \
-    if constexpr (GEO != GEO_HYB && GEO != GEO_ROW) {                                                       \
-        if ((bval) == 9) { DISPATCH_NC(9, nval, __VA_ARGS__) return; }                        \
-        if ((bval) == 16) { DISPATCH_NC(16, nval, __VA_ARGS__) return; }                      \
+    if constexpr (GEO != GEO_HYB && GEO != GEO_ROW) {                                         \
+        if ((bval) == 9) { DISPATCH_NC(9, nc, __VA_ARGS__) return; }                          \
+        if ((bval) == 16) { DISPATCH_NC(16, nc, __VA_ARGS__) return; }                        \
     }                                                                                         \
-    if constexpr (GEO != GEO_HYB && GEO != GEO_BLD && GEO != GEO_ROW) {                                         \
-        if ((bval) == 25) { DISPATCH_NC(25, nval, __VA_ARGS__) return; }                      \
-        if ((bval) == 27) { DISPATCH_NC(27, nval, __VA_ARGS__) return; }                      \
+    if constexpr (GEO != GEO_HYB && GEO != GEO_BLD && GEO != GEO_ROW) {                       \
+        if ((bval) == 25) { DISPATCH_NC(25, nc, __VA_ARGS__) return; }                        \
+        if ((bval) == 27) { DISPATCH_NC(27, nc, __VA_ARGS__) return; }                        \
     }                                                                                         \
     fail(DGMG_EUNSUPPORTED, "unsupported block size");
-#define DISPATCH_NC(bval, nval, ...)                                                          \
+#define DISPATCH_NC(bval, nc, ...)                                                            \
     constexpr int BV = bval;                                                                  \
-    if (cells_per_group(GEO, BV, nval) == 16) { constexpr int NC = 16; __VA_ARGS__; }              \
+    if ((nc) == 16) { constexpr int NC = 16; __VA_ARGS__; }                                   \
     else { constexpr int NC = 64; __VA_ARGS__; }
 
 template <typename T, int GEO>
 void cell_apply(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* va, T* y, const T* w, double* partial,
                 hipStream_t st) {
-    const int nc = cells_per_group(GEO, b, L.n);
+    constexpr bool BJ = false;
+    const int nc = cells_per_group(GEO, b, L.n, BJ);
     const unsigned g = (unsigned)((L.n + nc - 1) / nc);
-    DISPATCH_CELL(b, L.n, klaunch(ev, k_apply_cell<T, BV, NC, GEO>, g, cell_threads<BV, GEO>(), st, L, va, y, w, partial));
+    DISPATCH_CELL(b, nc, klaunch(ev, k_apply_cell<T, BV, NC, GEO>, g, cell_threads<BV, GEO>(), st, L, va, y, w, partial));
 }
 
 template <typename T, int GEO>
 void cell_residual(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* va, const T* vb, const T* rhs, T* r,
                    T* d, T c1, T* xout, double* partial, const T* P, T* rp, const int32_t* ptype, const T* bj,
                    hipStream_t st) {
-    const int nc = cells_per_group(GEO, b, L.n);
+    // as many partials as cell_groups says
+    const int nc = cells_per_group(GEO, b, L.n, bj && !partial);
     const unsigned g = (unsigned)((L.n + nc - 1) / nc);
     auto go = [&](auto vbc, auto bjc) {
         constexpr bool VB = decltype(vbc)::value, BJ = decltype(bjc)::value;
-        DISPATCH_CELL(b, L.n, klaunch(ev, k_residual_cell<T, BV, NC, GEO, VB, BJ>, g, cell_threads<BV, GEO>(), st, L, va, vb, rhs,
+        DISPATCH_CELL(b, nc, klaunch(ev, k_residual_cell<T, BV, NC, GEO, VB, BJ>, g, cell_threads<BV, GEO>(), st, L, va, vb, rhs,
                                       r, d, c1, xout, partial, P, rp, ptype, bj));
     };
     using Y = std::true_type;
@@ -69,11 +78,11 @@ void cell_residual(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T*
 template <typename T, int GEO>
 void cell_step(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* d, T* x, T* r, T* dn, T cd, T cr,
                int assign, int last, const T* bj, hipStream_t st) {
-    const int nc = cells_per_group(GEO, b, L.n);
+    const int nc = cells_per_group(GEO, b, L.n, bj != nullptr);
     const unsigned g = (unsigned)((L.n + nc - 1) / nc);
     auto go = [&](auto bjc) {
         constexpr bool BJ = decltype(bjc)::value;
-        DISPATCH_CELL(b, L.n, klaunch(ev, k_cheb_step_cell<T, BV, NC, GEO, BJ>, g, cell_threads<BV, GEO>(), st, L, d, x, r, dn, cd,
+        DISPATCH_CELL(b, nc, klaunch(ev, k_cheb_step_cell<T, BV, NC, GEO, BJ>, g, cell_threads<BV, GEO>(), st, L, d, x, r, dn, cd,
                                       cr, assign, last, bj));
     };
     if (bj) go(std::true_type{});

@@ -928,6 +928,7 @@ __device__ __forceinline__ void cell_product(const CellArgs<T>& L, int cell0, co
         return;
     } else if constexpr (B == 64) {
         static_assert(GEO == GEO_BOX, "3D Q3 cells: boxes or agglomerates by rows");
+        if (lane >= 4 * NC) return;   // whole quads
         const int c = min(cell0 + lane / 4, L.n - 1), l = lane & 3;
         T* ys = sh + (w * Ct::NC + lane / 4) * Ct::SB;
         if (w == 0) cell_terms_quad<T, VB>(L, c, l, va, vb, ys);
