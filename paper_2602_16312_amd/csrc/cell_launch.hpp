@@ -34,9 +34,9 @@ static int cells_per_group(int geo, int b, int n, bool bj) {
     }                                                                                         \
     if constexpr (GEO != GEO_HYB && GEO != GEO_ROW) {                                         \
         if ((bval) == 9) { DISPATCH_NC(9, nc, __VA_ARGS__) return; }                          \
-        if ((bval) == 16) { DISPATCH_NC(16, nc, __VA_ARGS__) return; }                        \
     }                                                                                         \
     if constexpr (GEO != GEO_HYB && GEO != GEO_BLD && GEO != GEO_ROW) {                       \
+        if ((bval) == 16) { DISPATCH_NC(16, nc, __VA_ARGS__) return; }                        \
         if ((bval) == 25) { DISPATCH_NC(25, nc, __VA_ARGS__) return; }                        \
         if ((bval) == 27) { DISPATCH_NC(27, nc, __VA_ARGS__) return; }                        \
     }                                                                                         \

@@ -973,18 +973,17 @@ __device__ __forceinline__ T cell_row(const T* sh, int k) {
     const int cell0 = xcd_tile(blockIdx.x, gridDim.x) * Ct::NC;                      \
     const int rows = min(Ct::NC, L.n - cell0) * B;                                   \
     const size_t t0 = (size_t)cell0 * B;
-// The epilogue takes a row per lane, U rows of a thread at a time, whose
-// vector operands are requested together (the first ones before the barrier):
-// a loop that loaded row by row cost a memory latency per row, 7 of them on
-// 3D Q2 cells.
+// The epilogue takes a row per lane, all U rows of a thread at once, whose
+// vector operands are requested together before the barrier: a loop that
+// loaded row by row cost a memory latency per row, 7 of them on 3D Q2 cells.
 template <int B, int NC, int GEO>
-constexpr int cell_rows_at_once() {
-    constexpr int n = (NC * B + cell_threads<B, GEO>() - 1) / cell_threads<B, GEO>();
-    return n > 9 ? 8 : n;
+constexpr int cell_rows() {
+    return (NC * B + cell_threads<B, GEO>() - 1) / cell_threads<B, GEO>();
 }
 #define DGMG_CELL_ROWS(B)                                                            \
-    constexpr int U = cell_rows_at_once<B, NC, GEO>(), NCH = (Ct::NC * B + U * Ct::NT - 1) / (U * Ct::NT); \
-    auto row = [&](int ch, int u) { return (int)threadIdx.x + (ch * U + u) * Ct::NT; };           \
+    constexpr int U = cell_rows<B, NC, GEO>();                                       \
+    static_assert(U <= 9, "rows of a thread held in registers");                     \
+    auto row = [&](int u) { return (int)threadIdx.x + u * Ct::NT; };                 \
     auto at = [&](int e) { return e + (Ct::SB - B) * (e / B); };   // LDS index of row e
 
 // y = A va; optional partial of dot(w, y).
@@ -996,24 +995,17 @@ __global__ __launch_bounds__((cell_threads<B, GEO>())) void k_apply_cell(CellArg
     DGMG_CELL_ROWS(B)
     cell_product<T, B, NC, false, GEO>(L, cell0, va, nullptr, sh);
     T wv[U];
-    auto fetch = [&](int ch) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) wv[u] = w ? w[t0 + min(row(ch, u), rows - 1)] : T(0);
-    };
-    fetch(0);
+    for (int u = 0; u < U; ++u) wv[u] = w ? w[t0 + min(row(u), rows - 1)] : T(0);
     __syncthreads();
     double contrib = 0.0;
 #pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-        if (ch) fetch(ch);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int e = row(ch, u);
-            if (e >= rows) continue;
-            const T a = cell_row<T, B, NC, GEO>(sh, at(e));
-            y[t0 + e] = a;
-            contrib += (double)wv[u] * (double)a;
-        }
+    for (int u = 0; u < U; ++u) {
+        const int e = row(u);
+        if (e >= rows) continue;
+        const T a = cell_row<T, B, NC, GEO>(sh, at(e));
+        y[t0 + e] = a;
+        contrib += (double)wv[u] * (double)a;
     }
     if (partial) wg_sum_store<Ct::NT>(contrib, partial);
 }
@@ -1028,32 +1020,25 @@ __global__ __launch_bounds__((cell_threads<B, GEO>())) void k_residual_cell(
     DGMG_CELL_ROWS(B)
     cell_product<T, B, NC, VB, GEO>(L, cell0, va, vb, sh);
     T bv[U], di[U];
-    auto fetch = [&](int ch) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const size_t t = t0 + min(row(ch, u), rows - 1);
-            bv[u] = rhs[t];
-            di[u] = d && !BJ ? L.dinv[t] : T(0);
-        }
-    };
-    fetch(0);
+    for (int u = 0; u < U; ++u) {
+        const size_t t = t0 + min(row(u), rows - 1);
+        bv[u] = rhs[t];
+        di[u] = d && !BJ ? L.dinv[t] : T(0);
+    }
     __syncthreads();
     double contrib = 0.0;
 #pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-        if (ch) fetch(ch);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int e = row(ch, u);
-            if (e >= rows) continue;
-            const size_t t = t0 + e;
-            const T rr = bv[u] - cell_row<T, B, NC, GEO>(sh, at(e));
-            if (r) r[t] = rr;
-            if (!BJ && d) d[t] = di[u] * rr * c1;
-            if (xout) xout[t] = VB ? va[t] + vb[t] : va[t];
-            contrib += (double)rr * (double)rr;
-            sh[at(e)] = rr;                           // a row's first share is read by its own thread only
-        }
+    for (int u = 0; u < U; ++u) {
+        const int e = row(u);
+        if (e >= rows) continue;
+        const size_t t = t0 + e;
+        const T rr = bv[u] - cell_row<T, B, NC, GEO>(sh, at(e));
+        if (r) r[t] = rr;
+        if (!BJ && d) d[t] = di[u] * rr * c1;
+        if (xout) xout[t] = VB ? va[t] + vb[t] : va[t];
+        contrib += (double)rr * (double)rr;
+        sh[at(e)] = rr;                               // a row's first share is read by its own thread only
     }
     if ((BJ && d) || P) {
         __syncthreads();
@@ -1104,60 +1089,48 @@ __global__ __launch_bounds__((cell_threads<B, GEO>())) void k_cheb_step_cell(Cel
     DGMG_CELL_ROWS(B)
     cell_product<T, B, NC, false, GEO>(L, cell0, d, nullptr, sh);
     T rv[U], dv[U], xv[U], di[U];
-    auto fetch = [&](int ch) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const size_t t = t0 + min(row(ch, u), rows - 1);   // padded rows reread the last one
-            rv[u] = r[t];
-            dv[u] = d[t];
-            xv[u] = assign ? T(0) : x[t];
-            di[u] = BJ ? T(0) : L.dinv[t];
-        }
-    };
-    fetch(0);
+    for (int u = 0; u < U; ++u) {
+        const size_t t = t0 + min(row(u), rows - 1);   // padded rows reread the last one
+        rv[u] = r[t];
+        dv[u] = d[t];
+        xv[u] = assign ? T(0) : x[t];
+        di[u] = BJ ? T(0) : L.dinv[t];
+    }
     __syncthreads();
     if constexpr (BJ) {
 #pragma unroll
-        for (int ch = 0; ch < NCH; ++ch) {
-            if (ch) fetch(ch);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int e = row(ch, u);
-                if (e >= rows) continue;
-                const T rr = rv[u] - cell_row<T, B, NC, GEO>(sh, at(e));
-                if (!last) r[t0 + e] = rr;
-                sh[at(e)] = rr;                       // a row's first share is read by its own thread only
-            }
+        for (int u = 0; u < U; ++u) {
+            const int e = row(u);
+            if (e >= rows) continue;
+            const T rr = rv[u] - cell_row<T, B, NC, GEO>(sh, at(e));
+            if (!last) r[t0 + e] = rr;
+            sh[at(e)] = rr;                           // a row's first share is read by its own thread only
         }
         __syncthreads();
-        if (NCH > 1) fetch(0);
     }
 #pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-        if (ch) fetch(ch);
+    for (int u = 0; u < U; ++u) {
+        const int e = row(u);
+        if (e >= rows) continue;
+        const size_t t = t0 + e;
+        T z;
+        if constexpr (BJ) {
+            const int lc = e / B;
+            const T* Dc = bj + (size_t)(cell0 + lc) * B * B + (e - lc * B);
+            const T* rc = sh + lc * Ct::SB;
+            z = 0;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int e = row(ch, u);
-            if (e >= rows) continue;
-            const size_t t = t0 + e;
-            T z;
-            if constexpr (BJ) {
-                const int lc = e / B;
-                const T* Dc = bj + (size_t)(cell0 + lc) * B * B + (e - lc * B);
-                const T* rc = sh + lc * Ct::SB;
-                z = 0;
-#pragma unroll
-                for (int i = 0; i < B; ++i) z += Dc[(size_t)i * B] * rc[i];
-            } else {
-                const T rr = rv[u] - cell_row<T, B, NC, GEO>(sh, at(e));
-                if (!last) r[t] = rr;
-                z = di[u] * rr;
-            }
-            const T x1 = assign ? dv[u] : xv[u] + dv[u];
-            const T dnew = cd * dv[u] + cr * z;
-            x[t] = last ? x1 + dnew : x1;
-            if (!last) dn[t] = dnew;
+            for (int i = 0; i < B; ++i) z += Dc[(size_t)i * B] * rc[i];
+        } else {
+            const T rr = rv[u] - cell_row<T, B, NC, GEO>(sh, at(e));
+            if (!last) r[t] = rr;
+            z = di[u] * rr;
         }
+        const T x1 = assign ? dv[u] : xv[u] + dv[u];
+        const T dnew = cd * dv[u] + cr * z;
+        x[t] = last ? x1 + dnew : x1;
+        if (!last) dn[t] = dnew;
     }
 }
 
