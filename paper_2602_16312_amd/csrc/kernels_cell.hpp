@@ -986,6 +986,26 @@ constexpr int cell_rows() {
     auto row = [&](int u) { return (int)threadIdx.x + u * Ct::NT; };                 \
     auto at = [&](int e) { return e + (Ct::SB - B) * (e / B); };   // LDS index of row e
 
+// The cell-block term's columns of the thread's U rows (row-major symmetric
+// blocks: the lanes of a cell read consecutive words of a row), requested before
+// the barrier where they fit in registers.  Boxes of 25 DoFs, 576 cells, step: FP64
+// 9.9 -> 8.4 us, FP32 6.7 -> 6.0; of 64, 512 cells: 8.7 -> 8.1, 6.3 -> 6.0.  Boxes of 27
+// (7.5 -> 7.7 us) and mapped cells (25 DoFs FP64 7.5 -> 8.6) were slower with it.
+template <typename T, int B, int NC, int GEO>
+constexpr bool block_columns_early() {
+    return GEO == GEO_BOX && (B == 25 || B == 64) && cell_rows<B, NC, GEO>() * B * sizeof(T) <= 640;
+}
+template <typename T, int B, int NT, int U>
+__device__ __forceinline__ void load_block_columns(const T* __restrict__ bj, int cell0, int rows, T (*dk)[B]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int e = min((int)threadIdx.x + u * NT, rows - 1), lc = e / B;
+        const T* Dc = bj + (size_t)(cell0 + lc) * B * B + (e - lc * B);
+#pragma unroll
+        for (int i = 0; i < B; ++i) dk[u][i] = Dc[(size_t)i * B];
+    }
+}
+
 // y = A va; optional partial of dot(w, y).
 template <typename T, int B, int NC, int GEO>
 __global__ __launch_bounds__((cell_threads<B, GEO>())) void k_apply_cell(CellArgs<T> L, const T* __restrict__ va,
@@ -1026,6 +1046,11 @@ __global__ __launch_bounds__((cell_threads<B, GEO>())) void k_residual_cell(
         bv[u] = rhs[t];
         di[u] = d && !BJ ? L.dinv[t] : T(0);
     }
+    constexpr bool EARLY = BJ && block_columns_early<T, B, NC, GEO>();
+    T dk[EARLY ? U : 1][B];
+    if constexpr (EARLY) {
+        if (d) load_block_columns<T, B, Ct::NT, U>(bj, cell0, rows, dk);
+    }
     __syncthreads();
     double contrib = 0.0;
 #pragma unroll
@@ -1042,6 +1067,24 @@ __global__ __launch_bounds__((cell_threads<B, GEO>())) void k_residual_cell(
     }
     if ((BJ && d) || P) {
         __syncthreads();
+        if constexpr (EARLY) {
+            if (d) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int e = row(u);
+                    if (e >= rows) continue;
+                    const T* rc = sh + e / B * Ct::SB;
+                    T z = 0;
+#pragma unroll
+                    for (int i = 0; i < B; ++i) z += dk[u][i] * rc[i];
+                    d[t0 + e] = c1 * z;
+                }
+            }
+            if (!P) {
+                if (partial) wg_sum_store<Ct::NT>(contrib, partial);
+                return;
+            }
+        }
         // two rows of a thread at a time, their loads requested together
         for (int e0 = threadIdx.x; e0 < rows; e0 += 2 * Ct::NT) {
             T z[2] = {0, 0}, s[2] = {0, 0};
@@ -1049,7 +1092,7 @@ __global__ __launch_bounds__((cell_threads<B, GEO>())) void k_residual_cell(
             for (int u = 0; u < 2; ++u) {
                 const int e = min(e0 + u * Ct::NT, rows - 1), lc = e / B, j = e - lc * B, cell = cell0 + lc;
                 const T* rc = sh + lc * Ct::SB;
-                if constexpr (BJ) {
+                if constexpr (BJ && !EARLY) {
                     if (d) {
                         const T* Dc = bj + (size_t)cell * B * B + j;
 #pragma unroll
@@ -1071,7 +1114,7 @@ __global__ __launch_bounds__((cell_threads<B, GEO>())) void k_residual_cell(
             for (int u = 0; u < 2; ++u) {
                 const int e = e0 + u * Ct::NT;
                 if (e >= rows) continue;
-                if (BJ && d) d[t0 + e] = c1 * z[u];
+                if (BJ && !EARLY && d) d[t0 + e] = c1 * z[u];
                 if (P) rp[t0 + e] = s[u];
             }
         }
@@ -1097,6 +1140,9 @@ __global__ __launch_bounds__((cell_threads<B, GEO>())) void k_cheb_step_cell(Cel
         xv[u] = assign ? T(0) : x[t];
         di[u] = BJ ? T(0) : L.dinv[t];
     }
+    constexpr bool EARLY = BJ && block_columns_early<T, B, NC, GEO>();
+    T dk[EARLY ? U : 1][B];
+    if constexpr (EARLY) load_block_columns<T, B, Ct::NT, U>(bj, cell0, rows, dk);
     __syncthreads();
     if constexpr (BJ) {
 #pragma unroll
@@ -1121,7 +1167,7 @@ __global__ __launch_bounds__((cell_threads<B, GEO>())) void k_cheb_step_cell(Cel
             const T* rc = sh + lc * Ct::SB;
             z = 0;
 #pragma unroll
-            for (int i = 0; i < B; ++i) z += Dc[(size_t)i * B] * rc[i];
+            for (int i = 0; i < B; ++i) z += (EARLY ? dk[EARLY ? u : 0][i] : Dc[(size_t)i * B]) * rc[i];
         } else {
             const T rr = rv[u] - cell_row<T, B, NC, GEO>(sh, at(e));
             if (!last) r[t] = rr;
