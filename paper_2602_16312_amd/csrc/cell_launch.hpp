@@ -9,12 +9,18 @@ namespace dgmg {
 // such workgroup per CU, smaller groups spread the cells over more CUs (a
 // lane's scattered loads of its cell then share an address unit with fewer
 // others).  Measured per step, 16 / 64 cells: 1,728 3D Q2 boxes 5.1 / 5.8 us,
-// 8,000 6.8 / 6.0 us, 64,000 34 / 15 us.  3D Q3 cells take four lanes each, and
-// with the cell-block smoother (bj), whose epilogue reads 64 values per row,
-// groups of 4 on small levels: 512 cells, 4 / 16 cells: FP64 8.7 / 14.5 us, FP32
-// 6.3 / 8.7 us; 1,728 cells 15.2 / 15.3, 7.5 / 8.9; 4,096 cells 28.7 / 25.1, 17.1 / 14.9.
-static int cells_per_group(int geo, int b, int n, bool bj) {
-    return geo == GEO_ROW ? 1 : b == 64 ? (bj && n <= 8 * 256 ? 4 : 16) : n <= 16 * 256 ? 16 : 64;
+// 8,000 6.8 / 6.0 us, 64,000 34 / 15 us.  3D Q3 cells take four lanes each.
+// bj, elem: the kernel has the cell-block term, whose epilogue reads b values per
+// row, in elements of that size.  b = 64: groups of 4 on small levels; 512 cells, 4 / 16
+// cells: FP64 8.7 / 14.5 us, FP32 6.3 / 8.7 us; 1,728 cells 15.2 / 15.3, 7.5 / 8.9;
+// 4,096 cells 28.7 / 25.1, 17.1 / 14.9.  b = 25 in FP32, not from stored blocks: groups of
+// 16 up to 64 per CU; boxes, 9,216 cells, 16 / 64 cells: 9.2 / 10.9 us (FP64 21.1 / 15.9),
+// 16,384 12.4 / 13.2, 36,864 22.7 / 23.2 with the residual 29.6 / 29.5.
+static int cells_per_group(int geo, int b, int n, bool bj, size_t elem) {
+    if (geo == GEO_ROW) return 1;
+    if (b == 64) return bj && n <= 8 * 256 ? 4 : 16;
+    const bool spread = bj && b == 25 && elem == 4 && (geo == GEO_BOX || geo == GEO_MAP);
+    return n <= (spread ? 64 : 16) * 256 ? 16 : 64;
 }
 
 // block size BV and cells per workgroup NC as constants (BJ: of the kernels with
@@ -50,7 +56,7 @@ template <typename T, int GEO>
 void cell_apply(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* va, T* y, const T* w, double* partial,
                 hipStream_t st) {
     constexpr bool BJ = false;
-    const int nc = cells_per_group(GEO, b, L.n, BJ);
+    const int nc = cells_per_group(GEO, b, L.n, BJ, sizeof(T));
     const unsigned g = (unsigned)((L.n + nc - 1) / nc);
     DISPATCH_CELL(b, nc, klaunch(ev, k_apply_cell<T, BV, NC, GEO>, g, cell_threads<BV, GEO>(), st, L, va, y, w, partial));
 }
@@ -60,7 +66,7 @@ void cell_residual(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T*
                    T* d, T c1, T* xout, double* partial, const T* P, T* rp, const int32_t* ptype, const T* bj,
                    hipStream_t st) {
     // as many partials as cell_groups says
-    const int nc = cells_per_group(GEO, b, L.n, bj && !partial);
+    const int nc = cells_per_group(GEO, b, L.n, bj && !partial, sizeof(T));
     const unsigned g = (unsigned)((L.n + nc - 1) / nc);
     auto go = [&](auto vbc, auto bjc) {
         constexpr bool VB = decltype(vbc)::value, BJ = decltype(bjc)::value;
@@ -78,7 +84,7 @@ void cell_residual(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T*
 template <typename T, int GEO>
 void cell_step(const LaunchEvents& ev, int b, const CellArgs<T>& L, const T* d, T* x, T* r, T* dn, T cd, T cr,
                int assign, int last, const T* bj, hipStream_t st) {
-    const int nc = cells_per_group(GEO, b, L.n, bj != nullptr);
+    const int nc = cells_per_group(GEO, b, L.n, bj != nullptr, sizeof(T));
     const unsigned g = (unsigned)((L.n + nc - 1) / nc);
     auto go = [&](auto bjc) {
         constexpr bool BJ = decltype(bjc)::value;
