@@ -33,8 +33,9 @@ struct MfConst {
 // level on a conforming grid of boxes, stored cell blocks (with the cell's
 // own face terms) and metric data at the faces' Gauss points, whole stored
 // blocks (agglomerates in a grid whose boxes overlap), or whole blocks of 64
-// rows, a lane per row.
-enum { GEO_BOX = 0, GEO_MAP = 1, GEO_BLK = 2, GEO_HYB = 3, GEO_BLD = 4, GEO_ROW = 5 };
+// rows, a lane per row.  GEO_BOXR: the kernels that take a small level of boxes
+// (GEO_BOX) with a lane per row.
+enum { GEO_BOX = 0, GEO_MAP = 1, GEO_BLK = 2, GEO_HYB = 3, GEO_BLD = 4, GEO_ROW = 5, GEO_BOXR = 6 };
 
 // entry (i, j) of a nodal face block along axis a: node i on the lower cell's
 // upper face or node j on the upper cell's lower face

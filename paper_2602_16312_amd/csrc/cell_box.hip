@@ -4,7 +4,7 @@
 namespace dgmg {
 
 unsigned cell_groups(int geo, int b, int n) {
-    const int nc = cells_per_group(geo, b, n, false, sizeof(double));
+    const int nc = cells_per_group(geo, b, n, false);
     return (unsigned)((n + nc - 1) / nc);
 }
 

@@ -32,6 +32,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <cstdint>
 #include <type_traits>
 
@@ -55,14 +56,14 @@ constexpr int pk(int a, int b) {
 // face where the faces' blocks are streamed
 template <int B, int GEO>
 constexpr int cell_threads() {
-    return 64 * (1 + (GEO == GEO_BLK || GEO == GEO_BLD || GEO == GEO_ROW ? 2 : 1) * dim_of<B>());
+    return GEO == GEO_BOXR ? kWG : 64 * (1 + (GEO == GEO_BLK || GEO == GEO_BLD || GEO == GEO_ROW ? 2 : 1) * dim_of<B>());
 }
 template <typename T, int B, int NCELL, int GEO = GEO_BOX>
 struct CellTile {
     static constexpr int D = dim_of<B>(), Q = ax_nodes_1d(B, D), QN = B / Q;
     static constexpr int NC = NCELL;                  // cells per workgroup, one per lane
     static constexpr int NT = cell_threads<B, GEO>();
-    static constexpr int NW = NT / 64;
+    static constexpr int NS = GEO == GEO_BOXR ? 1 : NT / 64;   // shares of a row's product
     static constexpr int SB = GEO == GEO_ROW ? B : B | 1;   // odd LDS stride of a cell's rows
 };
 
@@ -103,9 +104,9 @@ __device__ __forceinline__ void load_cell(const T* __restrict__ va, const T* __r
 
 // Ends a stage of the box terms.  The FP64 tables of Q = 5 take 50 scalar
 // registers each, and the scheduler, which hoists their loads, spilled them to
-// vector lanes (2,684 lane accesses of 6,351 instructions in one residual): no
-// load crosses a stage.  576 Q4 boxes, FP64: step 7.1 -> 6.5 us, residual 12.9 -> 8.5,
-// product 9.3 -> 7.9; 256^2: 21.0 -> 19.7, 33.3 -> 31.1, 15.7 -> 14.4 us.
+// vector lanes (1,022 lane accesses of 5,297 instructions in one step): no load
+// crosses a stage.  128^2 Q4 boxes, FP64 step 8.3 -> 7.6 us; 256^2: step 21.0 -> 19.7,
+// residual of a pending update 33.3 -> 31.1, product 15.7 -> 14.4 us.
 template <typename T, int B>
 __device__ __forceinline__ void stage_end() {
     if constexpr (B == 25 && sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);
@@ -942,6 +943,136 @@ __device__ __forceinline__ void face_terms_quad(const CellArgs<T>& L, int c, int
         }
 }
 
+// ---- Q4 squares, a lane per row: two cells per wave, every 1D pass through LDS
+// within the wave, so that no barrier separates them.  A lane per cell has 1,200
+// multiply-adds to do one after the other, which is all that a level of a few
+// hundred cells takes; here a row has about 90, and the face terms run beside
+// them: lanes 0 .. 19 of a cell take a node of a face each.  576 boxes, step: FP64
+// 6.5 us by cells, 4.8 us here, FP32 5.4, 4.2 us; residual of a pending update 8.5, 4.9 us.
+template <typename T, int B, int NC, bool VB>
+__device__ __forceinline__ void box_rows(const CellArgs<T>& L, int cell0, const T* __restrict__ va,
+                                         const T* __restrict__ vb, T* sh) {
+    constexpr int Q = 5, CW = 64 / B, NF = 4 * Q, NTAB = 4 * Q * Q + 3 * Q;
+    static_assert(B == Q * Q && Q == kMfMaxQ && NC == CW * kWG / 64, "whole tables, two cells per wave");
+    // the 1D tables lie one after the other at the start of MfConst
+    static_assert(offsetof(MfConst<T>, gw) == (4 * Q * Q + 2 * Q) * sizeof(T), "order of the tables");
+    struct Cell {
+        T p[3][B], fq[3][NF], ft[2][NF];
+    };
+    struct Wave {
+        T tab[NTAB];
+        Cell c[CW];
+    };
+    __shared__ Wave work[kWG / 64];
+    const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
+    const int lc = lane / B, i = lane - lc * B;
+    if (lc >= CW) return;
+    const MfConst<T>& C = L.mf;
+    const T* tabs = reinterpret_cast<const T*>(&C);
+    Wave& W = work[w];
+    Cell& S = W.c[lc];
+    const T *Ig = W.tab, *Gc = W.tab + B, *M1 = W.tab + 2 * B, *N1 = W.tab + 3 * B, *Ed = W.tab + 4 * B,
+            *gw = W.tab + 4 * B + 2 * Q;
+    const int c = min(cell0 + w * CW + lc, L.n - 1);
+    const int ix = i % Q, iy = i / Q;
+    // face item: node m of the face on side s of axis A
+    const bool face = i < NF;
+    const int f = face ? i / Q : 0, m = ix, A = f >> 1, s = f & 1;
+    const int nv = (s ? L.up : L.lo)[(size_t)A * L.n + c], nb = nv >= 0 ? nv : c;
+    auto value = [&](int cell, int k) {
+        const size_t t = (size_t)cell * B + k;
+        return VB ? va[t] + vb[t] : va[t];
+    };
+    const T u = value(c, i);
+    T xn[Q], tv[(NTAB + CW * B - 1) / (CW * B)];
+#pragma unroll
+    for (int j = 0; j < Q; ++j) xn[j] = value(nb, A ? m + Q * j : j + Q * m);
+#pragma unroll
+    for (int k = 0; k < (NTAB + CW * B - 1) / (CW * B); ++k) tv[k] = tabs[min(lane + k * CW * B, NTAB - 1)];
+    const T Dxx = C.D[(size_t)c * 3], Dxy = C.D[(size_t)c * 3 + 1], Dyy = C.D[(size_t)c * 3 + 2];
+    const T nxx = C.D[(size_t)nb * 3], nxy = C.D[(size_t)nb * 3 + 1], nyy = C.D[(size_t)nb * 3 + 2];
+#pragma unroll
+    for (int k = 0; k < (NTAB + CW * B - 1) / (CW * B); ++k)
+        if (lane + k * CW * B < NTAB) W.tab[lane + k * CW * B] = tv[k];
+    S.p[0][i] = u;
+    wave_lds_fence();
+    // x pass; face nodes: traces and normal derivatives of both sides
+    const T hA = A ? C.hinv[1] : C.hinv[0], hT = A ? C.hinv[0] : C.hinv[1];
+    const T kA = (A ? Dyy : Dxx) * hA, kT = Dxy * hT;
+    T a = 0;
+#pragma unroll
+    for (int j = 0; j < Q; ++j) a += Ig[ix * Q + j] * S.p[0][iy * Q + j];
+    S.p[1][i] = a;
+    if (face) {
+        T dK = 0, dN = 0;
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            dK += Ed[s * Q + j] * S.p[0][A ? m + Q * j : j + Q * m];
+            dN += Ed[(1 - s) * Q + j] * xn[j];
+        }
+        const T uK = S.p[0][A ? m + Q * s * (Q - 1) : s * (Q - 1) + Q * m], uN = s ? xn[0] : xn[Q - 1];
+        const T ar = (s ? nv != c : nv >= 0) ? (A ? C.area[1] : C.area[0]) : T(0);
+        const T hs = (s ? T(-0.5) : T(0.5)) * ar;
+        const T sig = (A ? C.eta[1] : C.eta[0]) * T(0.5) * (A ? Dyy + nyy : Dxx + nxx) * ar;
+        const T j = uK - uN;
+        S.fq[0][i] = hs * (kA * dK + (A ? nyy : nxx) * hA * dN) + sig * j;
+        S.fq[1][i] = hs * (kT * uK + nxy * hT * uN);
+        S.fq[2][i] = hs * j;
+    }
+    wave_lds_fence();
+    // y pass; tangential integrals of the faces
+    T g = 0;
+#pragma unroll
+    for (int j = 0; j < Q; ++j) g += Ig[iy * Q + j] * S.p[1][j * Q + ix];
+    S.p[2][i] = g;
+    if (face) {
+        T v = 0, n = 0, t = 0;
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            const T q0 = S.fq[0][f * Q + j], q1 = S.fq[1][f * Q + j], jc = S.fq[2][f * Q + j];
+            v += M1[m * Q + j] * q0 + N1[m * Q + j] * q1;
+            t += N1[j * Q + m] * jc;
+            n += M1[m * Q + j] * jc;
+        }
+        S.ft[0][i] = v + kT * t;
+        S.ft[1][i] = kA * n;
+    }
+    wave_lds_fence();
+    // gradient and weighted fluxes at the Gauss point
+    T gx = 0, gy = 0;
+#pragma unroll
+    for (int h = 0; h < Q; ++h) {
+        gx += Gc[ix * Q + h] * S.p[2][iy * Q + h];
+        gy += Gc[iy * Q + h] * S.p[2][h * Q + ix];
+    }
+    const T wq = gw[ix] * gw[iy] * C.vol, h0 = C.hinv[0], h1 = C.hinv[1];
+    S.p[0][i] = wq * (Dxx * h0 * h0 * gx + Dxy * h0 * h1 * gy);
+    S.p[1][i] = wq * (Dxy * h0 * h1 * gx + Dyy * h1 * h1 * gy);
+    wave_lds_fence();
+    T y = wq * C.cM * g;
+#pragma unroll
+    for (int h = 0; h < Q; ++h) y += Gc[h * Q + ix] * S.p[0][iy * Q + h] + Gc[h * Q + iy] * S.p[1][h * Q + ix];
+    S.p[2][i] = y;
+    wave_lds_fence();
+    // transposed passes, and the faces' terms of the row's test function
+    T b = 0;
+#pragma unroll
+    for (int h = 0; h < Q; ++h) b += Ig[h * Q + ix] * S.p[2][iy * Q + h];
+    S.p[0][i] = b;
+    wave_lds_fence();
+    T r = 0;
+#pragma unroll
+    for (int h = 0; h < Q; ++h) r += Ig[h * Q + iy] * S.p[0][h * Q + ix];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {                        // axis
+        const int n = q ? iy : ix, t = q ? ix : iy;      // normal and tangential index
+        r += Ed[n] * S.ft[1][2 * q * Q + t] + Ed[Q + n] * S.ft[1][(2 * q + 1) * Q + t];
+        if (n == 0) r += S.ft[0][2 * q * Q + t];
+        if (n == Q - 1) r += S.ft[0][(2 * q + 1) * Q + t];
+    }
+    sh[(w * CW + lc) * CellTile<T, B, NC, GEO_BOXR>::SB + i] = r;
+}
+
 // Evaluates the workgroup's shares: sh[w * NC * SB + cell * SB + row].  Lanes past
 // the last cell evaluate cell n - 1 and their rows are not read.  The caller
 // synchronises before it reads the shares.
@@ -954,6 +1085,9 @@ __device__ __forceinline__ void cell_product(const CellArgs<T>& L, int cell0, co
     if constexpr (GEO == GEO_ROW) {
         static_assert(B == 64 && NC == 1, "a workgroup per cell of 64 rows");
         sh[w * 64 + lane] = row_terms<T, VB>(L, cell0, w, lane, va, vb);
+        return;
+    } else if constexpr (GEO == GEO_BOXR) {
+        box_rows<T, B, NC, VB>(L, cell0, va, vb, sh);
         return;
     } else if constexpr (B == 64) {
         static_assert(GEO == GEO_BOX, "3D Q3 cells: boxes or agglomerates by rows");
@@ -992,13 +1126,13 @@ __device__ __forceinline__ T cell_row(const T* sh, int k) {
     using Ct = CellTile<T, B, NC, GEO>;
     T a = sh[k];
 #pragma unroll
-    for (int w = 1; w < Ct::NW; ++w) a += sh[w * Ct::NC * Ct::SB + k];
+    for (int w = 1; w < Ct::NS; ++w) a += sh[w * Ct::NC * Ct::SB + k];
     return a;
 }
 
 #define DGMG_CELL_GROUP(T, B)                                                        \
     using Ct = CellTile<T, B, NC, GEO>;                                                       \
-    __shared__ T sh[Ct::NW * Ct::NC * Ct::SB];                                       \
+    __shared__ T sh[Ct::NS * Ct::NC * Ct::SB];                                       \
     const int cell0 = xcd_tile(blockIdx.x, gridDim.x) * Ct::NC;                      \
     const int rows = min(Ct::NC, L.n - cell0) * B;                                   \
     const size_t t0 = (size_t)cell0 * B;
@@ -1017,12 +1151,12 @@ constexpr int cell_rows() {
 
 // The cell-block term's columns of the thread's U rows (row-major symmetric
 // blocks: the lanes of a cell read consecutive words of a row), requested before
-// the barrier where they fit in registers.  Boxes of 25 DoFs, 576 cells, step: FP64
-// 9.9 -> 8.4 us, FP32 6.7 -> 6.0; of 64, 512 cells: 8.7 -> 8.1, 6.3 -> 6.0.  Boxes of 27
-// (7.5 -> 7.7 us) and mapped cells (25 DoFs FP64 7.5 -> 8.6) were slower with it.
+// the barrier where they fit in registers.  Boxes of 64 DoFs, 512 cells, step: FP64
+// 8.7 -> 8.1 us, FP32 6.3 -> 6.0; boxes of 27 (7.5 -> 7.7 us) and mapped cells (25 DoFs FP64
+// 7.5 -> 8.6) were slower with it.
 template <typename T, int B, int NC, int GEO>
 constexpr bool block_columns_early() {
-    return GEO == GEO_BOX && (B == 25 || B == 64) && cell_rows<B, NC, GEO>() * B * sizeof(T) <= 640;
+    return (GEO == GEO_BOXR || (GEO == GEO_BOX && B == 64)) && cell_rows<B, NC, GEO>() * B * sizeof(T) <= 640;
 }
 template <typename T, int B, int NT, int U>
 __device__ __forceinline__ void load_block_columns(const T* __restrict__ bj, int cell0, int rows, T (*dk)[B]) {

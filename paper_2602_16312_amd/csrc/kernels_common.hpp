@@ -45,6 +45,15 @@ __host__ __device__ constexpr int node_tan(int j, int a, int q) {
     return a == 0 ? (j / q) % q + q * (j / (q * q)) : a == 1 ? j % q + q * (j / (q * q)) : j % (q * q);
 }
 
+// Orders one wave's LDS accesses at the compiler level.  Only lanes of one
+// wave exchange data through the buffers it guards, and LDS executes a
+// wave's instructions in issue order, so no barrier is needed.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Workgroup sum of a double into partial[blockIdx.x] (deterministic order).
 // NT: threads of the workgroup; one slot per wave (the cell kernels run three
 // to seven).

@@ -13,15 +13,6 @@ namespace dgmg {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-// Orders one wave's LDS accesses at the compiler level.  Only lanes of one
-// wave exchange data through the buffers it guards, and LDS executes a
-// wave's instructions in issue order, so no barrier is needed.
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Cells per workgroup of the multi-column kernels, whatever the tile holds: they
 // share no gathered values between lanes of b = 25, so that the idle lanes of
 // its 8-cell tiles buy them nothing (128^2 cells, 8 columns, FP32
