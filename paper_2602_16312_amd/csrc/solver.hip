@@ -914,7 +914,7 @@ static int pcg(dgmg_solver* s, const double* b, double* x, const dgmg_pcg_opts& 
     const bool init0 = update_starts_sweep(s);
     const double c1_0 = 1.0 / (0.5 * (L0.lam_hi + L0.lam_lo));
     if (o.max_it > 0) first();
-    double rlast = r0, rate = 0.0;   // residual norm and its last reduction factor
+    double rlast = r0, rate = 0.0, rate_before = 0.0;   // residual norm and its last two reduction factors
     while (its < o.max_it) {
         if (s->prec == DGMG_PREC_MIXED)
             k_update_xr<float><<<nb, kWG, 0, st>>>(N, sc, s->pv, s->q, x, s->r, partial, rb,
@@ -930,15 +930,17 @@ static int pcg(dgmg_solver* s, const double* b, double* x, const dgmg_pcg_opts& 
         // The GPU would idle while the host waits for ||r|| and queues more.
         // The next direction depends on the test only in whether it is
         // wanted, and touches neither x nor r: it is queued ahead unless this
-        // test may end the solve, when a whole V-cycle would be thrown away: with
-        // one level (an exact inverse: one iteration), when the last reduction
-        // factor comes within 100 of the threshold, or its cube under it (CG
-        // converges faster than linearly: on 4x4 Q1 cells with the cell-block
-        // smoother by 2e-3, then by 1e-7).  Step of 256x256 Q2 cells: 1,272 us
-        // with a stream synchronisation per test, 1,250 us polling, 1,234 us
-        // queued ahead.
+        // test may end the solve, when a whole V-cycle would be thrown away.  One
+        // level (an exact inverse) ends at the first test.  After one reduction
+        // the next may be its square or better (4x4 Q1 cells with the cell-block
+        // smoother: 2e-3, then 1e-7), so its cube has to leave the threshold out
+        // of reach; after two, the last one, improved again as it was over the
+        // one before, has to stay above 100 thresholds.  Step of 256x256 Q2
+        // cells: 1,272 us with a stream synchronisation per test, 1,250 us
+        // polling, 1,234 us queued ahead.
+        const double next_rn = rlast * rate * (its > 1 ? std::min(1.0, rate / rate_before) : 1.0);
         const bool ends = its == 0 ? s->L == 1 || r0 <= 1e4 * thresh
-                                   : rlast * rate <= 100.0 * thresh || rlast * rate * rate * rate <= thresh;
+                                   : next_rn <= 100.0 * thresh || (its == 1 && rlast * rate * rate * rate <= thresh);
         const bool ahead = its + 1 < o.max_it && !ends && how != HostWait::Block;   // a blocking wait is for all of it
         if (ahead) next();
         wait_scalars(s, st, seq, how);
@@ -956,6 +958,7 @@ static int pcg(dgmg_solver* s, const double* b, double* x, const dgmg_pcg_opts& 
             stats->converged = 1;
             return idle.returning(DGMG_OK);
         }
+        rate_before = rate;
         rate = rn / rlast;
         rlast = rn;
         if (!ahead && its < o.max_it) next();
