@@ -172,7 +172,8 @@ def kernel_source_sha():
     the kernels they were taken on)."""
     import hashlib
     h = hashlib.sha256()
-    for name in ("kernels_common.hpp", "kernels.hpp", "kernels_multi.hpp", "kernels_cell.hpp"):
+    for name in ("kernels_common.hpp", "kernels.hpp", "kernels_multi.hpp", "kernels_cell.hpp", "cell.hpp",
+                 "cell_launch.hpp"):
         h.update(open(os.path.join(ROOT, "paper_2602_16312_amd", "csrc", name), "rb").read())
     return h.hexdigest()
 

@@ -284,8 +284,8 @@ int dgmg_get_info(const dgmg_solver* s, dgmg_solver_info* info);
 /* The form in which a level's operator is evaluated.  TILE_ELL, AXIS_ELL and
  * AXIS_ELL_SPARSE: the stored blocks of those layouts, a thread per row.
  * FACES_ONCE: as TILE_ELL, with an FP32 copy that holds every face block once.
- * The others take cells per lane: BOX from the conductivities of identical
- * boxes, MAPPED from metric data at the Gauss points, HYBRID from the cell
+ * The others take a cell per lane (small levels of Q4 boxes a row): BOX from
+ * the conductivities of identical boxes, MAPPED from metric data at the Gauss points, HYBRID from the cell
  * blocks and the faces' metric data (Q1); on agglomerated levels NODAL_BLOCKS
  * and WHOLE_BLOCKS from stored blocks without and with the entries that vanish
  * on nested boxes, ROW_BLOCKS from blocks of 64 rows, a wave per block.

@@ -5,10 +5,9 @@
 
 namespace dgmg {
 
-// Cells per workgroup: 64 fill a wave's lanes; on a level with fewer than one
-// such workgroup per CU, smaller groups spread the cells over more CUs (a
-// lane's scattered loads of its cell then share an address unit with fewer
-// others).  Measured per step, 16 / 64 cells: 1,728 3D Q2 boxes 5.1 / 5.8 us,
+// Cells per workgroup: 64 fill a wave's lanes; on a level of up to 16 cells per
+// CU, groups of 16 spread them over more CUs (a lane's scattered loads of its
+// cell then share an address unit with fewer others).  Measured per step, 16 / 64 cells: 1,728 3D Q2 boxes 5.1 / 5.8 us,
 // 8,000 6.8 / 6.0 us, 64,000 34 / 15 us.  3D Q3 cells take four lanes each.
 // bj: the kernel has the cell-block term, whose epilogue reads b values per row.
 // b = 64: groups of 4 on small levels; 512 cells, 4 / 16 cells: FP64 8.7 / 14.5 us, FP32

@@ -1,24 +1,27 @@
-// Matrix-free fine-level operator for meshes of identical axis-aligned boxes
-// (section 3: cell and interior-face terms of a_h and the mass term of eq.
-// fully_discrete, evaluated by sum factorisation instead of stored blocks).
+// Level operators evaluated per cell: fine levels (section 3: cell and
+// interior-face terms of a_h and the mass term of eq. fully_discrete) by sum
+// factorisation on boxes and mapped cells, Q1 levels from cell blocks and face
+// data, agglomerated levels from stored blocks.
 //
-// On a box of extents h the Q_p basis is a tensor product of 1D Lagrange
+// Mapping: a workgroup takes 64 or 16 consecutive cells, one per lane, and has a
+// wave for the cell terms and one per axis, which evaluates both faces normal to
+// it (stored blocks: one per face), each lane with its cell's B values in
+// registers: every 1D pass is register arithmetic with wave-uniform (scalar
+// register) table entries, so there is no LDS traffic or barrier between
+// passes.  Each wave leaves its share of the B rows in LDS; after the only
+// barrier the epilogue sums the shares in wave order, a lane per row, with
+// coalesced vector accesses.  3D Q3 cells take four lanes each, agglomerates of
+// 64 DoFs a workgroup, small levels of Q4 squares a lane per row.
+//
+// Boxes: on extents h the Q_p basis is a tensor product of 1D Lagrange
 // polynomials on Gauss-Lobatto nodes, the Gauss-Legendre rule with p+1 points
 // integrates every cell and face term exactly, and the only per-cell data is
 // the (scaled) conductivity D_K.
-//
-// Mapping: a workgroup takes 64 consecutive cells, one per lane, and has 1 + D
-// waves.  Wave 0 evaluates the cell terms, wave 1 + a both faces normal to
-// axis a, each lane with its cell's B values in registers: every 1D pass is
-// register arithmetic with wave-uniform (scalar register) table entries, so
-// there is no LDS traffic or barrier between passes.  Each wave leaves its
-// share of the B rows in LDS; after the only barrier the epilogue sums the
-// shares in wave order, a lane per row, with coalesced vector accesses.
 //   cell:  nodal values to the Gauss points by D 1D passes, gradients there by
 //          the collocation derivative G, the weighted fluxes, and the
 //          transposed passes;
 //   face:  the traces (Lobatto end layers) and normal derivatives of both
-//          sides; on a box the tangential integrals are the 1D matrices
+//          sides; the tangential integrals are the 1D matrices
 //          M_ij = int l_i l_j and N_ij = int l_i l_j', applied to
 //            q0 = -s/2 (k_a d_K + k_a^N d_N) + sigma (u_K - u_N),
 //            q_t = -s/2 (k_t u_K + k_t^N u_N),  jc = -s/2 (u_K - u_N),
@@ -27,8 +30,9 @@
 // 3D Q2 cell, 140 per DoF) beside the vector streams; 64^3 Q2, FP32 Chebyshev
 // step: 46 us, 4.4 TB/s on its 202 MB (a thread per DoF with every pass through
 // LDS and eight barriers: 150 us, LDS busy 91%); FP64 130 us (286 us); 128^2 Q4
-// FP64 8.3 us (17.2 us); 16^3 Q3 FP64 8.3 us (18.0 us).
-// Included by cell.hip.
+// FP64 7.6 us (17.2 us); 16^3 Q3 FP64 8.3 us (18.0 us).  The other forms' figures
+// stand beside them.
+// Included by cell_launch.hpp, in one translation unit per form (cell_*.hip).
 #pragma once
 #include <hip/hip_runtime.h>
 

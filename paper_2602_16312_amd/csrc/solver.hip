@@ -83,11 +83,13 @@ static double now_s() {
 
 static inline unsigned blocks_for(int64_t threads) { return (unsigned)((threads + kWG - 1) / kWG); }
 
-// Fine levels of distorted cells (p >= 2) hold metric data from this size on.
-// Below one cell per CU both forms take a launch and its latencies; at 576 Q2
-// squares a step takes 3.3 us against 3.7 us with stored blocks, at 65,536 5.9
-// against 12.0 us.  p = 1, 1,024 squares 2.7 against 3.7 us (FP64), boxes 2.6 us;
-// the shell of 1.0M hexahedra 148 against 214 us.
+// Fine levels of distorted cells hold metric data, and Q1 boxes are evaluated as
+// boxes, from this size on.  A step with stored blocks / in these forms, us:
+//   256 squares  Q1 3.1 / 2.8 (FP64 3.5 / 2.7), boxes 3.0 / 2.8 (3.5 / 2.7); Q2 3.8 / 3.2
+//                (4.9 / 3.7); Q3 4.3 / 3.8 (5.9 / 5.0); Q4 5.3 / 5.0 (7.7 / 6.0)
+//   343 cubes    Q1 4.9 / 3.2 (5.5 / 4.1), boxes 4.9 / 3.5 (5.5 / 3.5); Q2 8.2 / 6.5 (11.8 / 8.0)
+//   65,536 Q2 squares 12.0 / 5.9; the shell of 1.0M hexahedra 214 / 148
+// Below one cell per CU both take a launch and its latencies.
 constexpr int64_t kMinMappedCells = 256;
 // Agglomerated levels in a grid whose blocks go to the cell kernels.  Sweeps of a
 // V-cycle (12 steps, 6 residuals) by rows and by cells, us:
