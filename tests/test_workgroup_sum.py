@@ -16,6 +16,8 @@ PROGRAM = r"""
 #define __host__
 #define __forceinline__ inline
 #define __shared__ static
+#define __builtin_amdgcn_fence(...) ((void)0)
+#define __builtin_amdgcn_wave_barrier() ((void)0)
 struct Dim { unsigned x; };
 static Dim threadIdx{0}, blockIdx{0}, blockDim{THREADS};
 static double __shfl_xor(double, int, int) { return 0.0; }
