@@ -721,7 +721,10 @@ static double read_scalars(dgmg_solver* s, hipStream_t st, int R = 1, const doub
 enum class HostWait { Spin, Yield, Block };
 static HostWait host_wait() {
     unsigned f = 0;
-    if (hipGetDeviceFlags(&f) != hipSuccess) return HostWait::Spin;
+    if (hipGetDeviceFlags(&f) != hipSuccess) {
+        (void)hipGetLastError();
+        return HostWait::Spin;
+    }
     f &= hipDeviceScheduleMask;
     return f == hipDeviceScheduleBlockingSync ? HostWait::Block
            : f == hipDeviceScheduleYield      ? HostWait::Yield : HostWait::Spin;
