@@ -589,13 +589,13 @@ static void vcycle(dgmg_solver* s, int l, hipStream_t st, T** xres, T** dres, bo
         } else if (xzero && !pending) {
             if constexpr (R == 1) {
                 if (bjp) {   // r = b and d = c1 D^-1 b in one pass
-                    DISPATCH_B(s->b, k_block_jacobi<T, BV><<<groups_for(L, kWG / BV), kWG, 0, st>>>(
+                    DISPATCH_B(s->b, klaunch(k_block_jacobi<T, BV>, groups_for(L, kWG / BV), kWG, st, 
                                          L.n, bjp, b, d, T(0), c1, (T*)nullptr, r));
                 } else {
-                    k_cheb_init0<T><<<blocks_for(L.N), kWG, 0, st>>>(L.N, b, dinv, r, d, c1);
+                    klaunch(k_cheb_init0<T>, blocks_for(L.N), kWG, st, L.N, b, dinv, r, d, c1);
                 }
             } else {
-                k_cheb_init0_m<T, R><<<blocks_for(NR), kWG, 0, st>>>(NR, b, dinv, r, d, c1);
+                klaunch(k_cheb_init0_m<T, R>, blocks_for(NR), kWG, st, NR, b, dinv, r, d, c1);
             }
         } else if (pending) {
             // r = b - A(x + d), materialise x + d into x2
@@ -638,7 +638,7 @@ static void vcycle(dgmg_solver* s, int l, hipStream_t st, T** xres, T** dres, bo
     } else {
         if (xzero) {
             // no smoothing: x = 0 and r = b
-            k_fill<T><<<blocks_for(NR), kWG, 0, st>>>(NR, x, (T)0);
+            klaunch(k_fill<T>, blocks_for(NR), kWG, st, NR, x, (T)0);
             xzero = false;
         }
         launch_residual<T, R>(s, L, x, (const T*)nullptr, b, (T*)nullptr, (T*)nullptr, c1, (T*)nullptr,
@@ -695,18 +695,18 @@ static void apply_vcycle(dgmg_solver* s, const double* r, double* z, hipStream_t
         double *x, *d;
         vcycle<double, R>(s, 0, st, &x, &d, R == 1 && init_done);
         if (R == 1 && rz_partial)
-            k_cast_dot<double><<<blocks_for(NR), kWG, 0, st>>>(NR, x, d, z, r, rz_partial);
+            klaunch(k_cast_dot<double>, blocks_for(NR), kWG, st, NR, x, d, z, r, rz_partial);
         else
-            k_cast<double, double><<<blocks_for(NR), kWG, 0, st>>>(NR, x, d, z);
+            klaunch(k_cast<double, double>, blocks_for(NR), kWG, st, NR, x, d, z);
     } else {
         if (!(R == 1 && rb_ready))
-            k_cast<double, float><<<blocks_for(NR), kWG, 0, st>>>(NR, r, nullptr, (float*)L0.vb);
+            klaunch(k_cast<double, float>, blocks_for(NR), kWG, st, NR, r, nullptr, (float*)L0.vb);
         float *x, *d;
         vcycle<float, R>(s, 0, st, &x, &d, R == 1 && init_done);
         if (R == 1 && rz_partial)
-            k_cast_dot<float><<<blocks_for(NR), kWG, 0, st>>>(NR, x, d, z, r, rz_partial);
+            klaunch(k_cast_dot<float>, blocks_for(NR), kWG, st, NR, x, d, z, r, rz_partial);
         else
-            k_cast<float, double><<<blocks_for(NR), kWG, 0, st>>>(NR, x, d, z);
+            klaunch(k_cast<float, double>, blocks_for(NR), kWG, st, NR, x, d, z);
     }
 }
 
@@ -770,7 +770,7 @@ static std::string breakdown_msg(int its, int col, double pq, double gam) {
 static void apply_p(dgmg_solver* s, hipStream_t st, double* partial, double* sc) {
     DevLevel& L0 = s->lv[0];
     launch_apply<double>(s, L0, s->pv, s->q, s->pv, partial, st);
-    k_finalize<<<1, kWG, 0, st>>>(level_tiles<double>(s, L0), partial, sc, 2, 0);
+    klaunch(k_finalize, 1, kWG, st, level_tiles<double>(s, L0), partial, sc, 2, 0, (double*)nullptr, uint64_t(0));
 }
 // whether the PCG update starts the V-cycle's first level-0 sweep (point Jacobi)
 static bool update_starts_sweep(const dgmg_solver* s) {
@@ -780,9 +780,9 @@ static bool update_starts_sweep(const dgmg_solver* s) {
 static void first_direction(dgmg_solver* s, hipStream_t st, double* partial, double* sc) {
     const unsigned nb = blocks_for(s->N);
     apply_vcycle(s, s->r, s->z, st);
-    k_dot<<<nb, kWG, 0, st>>>(s->N, s->r, s->z, partial);
-    k_finalize<<<1, kWG, 0, st>>>(nb, partial, sc, 1, 0);
-    k_update_p<<<nb, kWG, 0, st>>>(s->N, sc, s->z, s->pv, 1);
+    klaunch(k_dot, nb, kWG, st, s->N, s->r, s->z, partial);
+    klaunch(k_finalize, 1, kWG, st, nb, partial, sc, 1, 0, (double*)nullptr, uint64_t(0));
+    klaunch(k_update_p, nb, kWG, st, s->N, sc, s->z, s->pv, 1);
     apply_p(s, st, partial, sc);
 }
 // The rest of an iteration after its stopping test: z = V(r), p, q = A p.
@@ -793,42 +793,38 @@ static void next_direction(dgmg_solver* s, hipStream_t st, double* partial, doub
     if (flexible) {
         std::swap(s->z, s->zold);
         apply_vcycle(s, s->r, s->z, st, true, nullptr, init0);
-        k_dot<<<nb, kWG, 0, st>>>(N, s->r, s->zold, partial);
-        k_finalize<<<1, kWG, 0, st>>>(nb, partial, sc, 5, 0);
-        k_dot<<<nb, kWG, 0, st>>>(N, s->r, s->z, partial);
+        klaunch(k_dot, nb, kWG, st, N, s->r, s->zold, partial);
+        klaunch(k_finalize, 1, kWG, st, nb, partial, sc, 5, 0, (double*)nullptr, uint64_t(0));
+        klaunch(k_dot, nb, kWG, st, N, s->r, s->z, partial);
     } else {
         // z = V(r) with the partials of (r, z) from the exit cast
         apply_vcycle(s, s->r, s->z, st, true, partial, init0);
     }
-    k_finalize<<<1, kWG, 0, st>>>(nb, partial, sc, 3, flexible ? 2 : 1);
-    k_update_p<<<nb, kWG, 0, st>>>(N, sc, s->z, s->pv, 0);
+    klaunch(k_finalize, 1, kWG, st, nb, partial, sc, 3, flexible ? 2 : 1, (double*)nullptr, uint64_t(0));
+    klaunch(k_update_p, nb, kWG, st, N, sc, s->z, s->pv, 0);
     apply_p(s, st, partial, sc);
 }
 
-// Records what `work` launches into a graph.  Only kernels are launched, on the
-// solver's own buffers; `work` must leave the solver as it found it.
+thread_local GraphRecorder* t_recorder = nullptr;
+// Records what `work` launches into a graph (launch.hpp).  Only kernels are
+// launched, through klaunch, on the solver's own buffers; `work` must leave the
+// solver as it found it.
 template <typename F>
 static hipGraphExec_t record_graph(F&& work) {
-    hipStream_t st = nullptr;
-    hipGraph_t g = nullptr;
-    hipGraphExec_t x = nullptr;
-    HIPCHK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
-    hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
-    if (e == hipSuccess) {
-        try {
-            work(st);
-        } catch (...) {
-            (void)hipStreamEndCapture(st, &g);
-            if (g) (void)hipGraphDestroy(g);
-            (void)hipStreamDestroy(st);
-            throw;
+    GraphRecorder rec;
+    HIPCHK(hipGraphCreate(&rec.graph, 0));
+    struct Scope {
+        GraphRecorder& rec;
+        explicit Scope(GraphRecorder& r) : rec(r) { t_recorder = &rec; }
+        ~Scope() {
+            t_recorder = nullptr;
+            (void)hipGraphDestroy(rec.graph);
         }
-        e = hipStreamEndCapture(st, &g);
-    }
-    if (e == hipSuccess) e = hipGraphInstantiate(&x, g, nullptr, nullptr, 0);
-    if (g) (void)hipGraphDestroy(g);
-    (void)hipStreamDestroy(st);
-    if (e != hipSuccess) fail(DGMG_EHIP, std::string("recording the PCG's graph: ") + hipGetErrorString(e));
+    } scope{rec};
+    work(hipStream_t(nullptr));
+    t_recorder = nullptr;
+    hipGraphExec_t x = nullptr;
+    HIPCHK(hipGraphInstantiate(&x, rec.graph, nullptr, nullptr, 0));
     return x;
 }
 // Graphs of first_direction and next_direction (set-up).  Launched one by one,

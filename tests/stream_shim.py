@@ -1,7 +1,7 @@
 """Child processes whose hipStreamSynchronize is counted, and made to report an
 error on request, by a small library loaded before the HIP runtime (the call
-itself is always passed on, so that the GPU runs as it would).  The library can
-also refuse hipStreamBeginCapture."""
+itself is always passed on, so that the GPU runs as it would).  The library also
+counts stream captures and can refuse hipGraphInstantiate."""
 import os
 import subprocess
 import sys
@@ -11,10 +11,19 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SHIM = r"""
 static int (*real)(void*);
 static int (*begin)(void*, int);
-static int calls, failing, refusing;
-void shim_init(void* f, void* g) { real = (int (*)(void*))f; begin = (int (*)(void*, int))g; }
+static int (*instantiate)(void*, void*, void*, char*, unsigned long);
+static int calls, failing, refusing, captures;
+void shim_init(void* f, void* g, void* h) {
+    real = (int (*)(void*))f;
+    begin = (int (*)(void*, int))g;
+    instantiate = (int (*)(void*, void*, void*, char*, unsigned long))h;
+}
 void shim_refuse(int on) { refusing = on; }
-int hipStreamBeginCapture(void* stream, int mode) { return refusing ? 999 : begin(stream, mode); }
+int shim_captures(void) { return captures; }
+int hipStreamBeginCapture(void* stream, int mode) { ++captures; return begin(stream, mode); }
+int hipGraphInstantiate(void* x, void* g, void* n, char* log, unsigned long size) {
+    return refusing ? 999 : instantiate(x, g, n, log, size);
+}
 int shim_calls(void) { return calls; }
 void shim_fail(int on) { failing = on; }
 int hipStreamSynchronize(void* stream) {
@@ -36,7 +45,8 @@ from workloads import make_problem
 F.lib()
 path = next(l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l)
 hip = ctypes.CDLL(path)
-shim.shim_init(*(ctypes.cast(f, ctypes.c_void_p) for f in (hip.hipStreamSynchronize, hip.hipStreamBeginCapture)))
+shim.shim_init(*(ctypes.cast(f, ctypes.c_void_p) for f in (hip.hipStreamSynchronize, hip.hipStreamBeginCapture,
+                                                         hip.hipGraphInstantiate)))
 """
 
 

@@ -79,3 +79,66 @@ assert torch.equal(*x)
 """)
     lines = [l.split(None, 1)[1] for l in out.splitlines() if l.startswith("graphs")]
     assert lines[0] == "held" and lines[1].startswith("failed: ") and len(lines[1]) > 12, out
+
+
+def test_set_up_captures_no_stream(tmp_path):
+    """While one thread captures a stream, other threads' calls on the legacy stream fail."""
+    say("captures (child process)")
+    out = run_child(tmp_path, r"""
+pr = make_problem("c2", n=16, group=[4])
+b = torch.from_numpy(np.random.default_rng(1).standard_normal(pr["N"])).cuda()
+h, s = problem.build(pr, precision="mixed")
+x = torch.zeros_like(b)
+api.pcg_solve(s, b, x, tol=1e-9)
+print("graphs", s.forms()["pcg_graphs"], "captures", shim.shim_captures(), flush=True)
+""")
+    assert "graphs held captures 0" in out, out
+
+
+def test_solvers_of_several_threads():
+    """Set-ups and solves of four threads at once, each on a stream of its own: no call
+    fails and every result equals the serial one."""
+    import threading
+    import numpy as np
+    from gpu_util import torch
+    from paper_2602_16312_amd import api
+    cases = [("c1", dict(n=16), "fp64"), ("c2", dict(n=16, group=[4]), "mixed"), ("e1", dict(n=12, p=4, group=[3]), "fp64"),
+             ("c3", dict(n=6, group=[3]), "mixed")]
+    prs = [make_problem(name, **kw) for name, kw, _ in cases]
+
+    def work(k, out, stream):
+        with torch.cuda.stream(stream):
+            b = torch.from_numpy(np.random.default_rng(k).standard_normal(prs[k]["N"])).cuda()
+            res = []
+            for _ in range(8):
+                h, s = problem.build(prs[k], precision=cases[k][2])
+                for _ in range(3):
+                    x = torch.zeros_like(b)
+                    its = api.pcg_solve(s, b, x, tol=1e-9, stream=stream)["its"]
+                    res.append((its, x.cpu().numpy()))
+                assert s.forms()["pcg_graphs"] == "held"
+            out[k] = res
+
+    say("threads, serial")
+    ref = {}
+    for k in range(len(cases)):
+        work(k, ref, torch.cuda.current_stream())
+    for r in range(3):
+        say("threads, round", r)
+        out, failed = {}, []
+
+        def guarded(k):
+            try:
+                work(k, out, torch.cuda.Stream())
+            except Exception as e:   # reported by the test's own thread
+                failed.append((k, e))
+
+        threads = [threading.Thread(target=guarded, args=(k,)) for k in range(len(cases))]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert not failed, failed
+        for k in range(len(cases)):
+            for (i0, x0), (i1, x1) in zip(ref[k], out[k]):
+                assert i0 == i1 and np.array_equal(x0, x1), k

@@ -109,3 +109,22 @@ for k, solve in enumerate((api.pcg_solve, api.pcg_solve_noalloc)):
         calls, its = {m: int(v[k][0]) for m, v in got.items()}, int(got[0][k][1])
         assert calls[0] == 1 and calls[2] == 1 and calls[4] == its + 2   # the first residual's and the end's
         assert got[0][k][1:] == got[2][k][1:] == got[4][k][1:]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("mg", [dict(cheb_sweeps=0), dict(cheb_sweeps=1, cheb_degree=2), dict(cheb_sweeps=0, jacobi="cell_block")])
+def test_recorded_directions_without_or_with_one_sweep(prec, mg):
+    """Graphs against single launches where the V-cycle has other kernels than usual."""
+    import numpy as np
+    from gpu_util import dev, host, torch
+    from paper_2602_16312_amd import api, problem
+    from workloads import make_problem
+    pr = make_problem("c2", n=16, group=[2, 4])
+    h, s = problem.build(pr, precision=prec, **mg)
+    assert s.forms()["pcg_graphs"] == "held"
+    b = dev(np.random.default_rng(3).standard_normal(pr["N"]))
+    for _ in range(3):
+        x = [torch.zeros_like(b) for _ in range(2)]
+        say("recorded directions", prec, mg)
+        its = [f(s, b, y, tol=1e-9, max_it=3) for f, y in ((api.pcg_solve, x[0]), (api.pcg_solve_noalloc, x[1]))]
+        assert its[0] == its[1] and np.array_equal(host(x[0]), host(x[1]))
