@@ -36,9 +36,7 @@ struct LaunchEvents {
 // A graph under construction: kernels in the order in which they are added.
 // Its nodes are built from the launches' arguments and not by capturing a
 // stream: while one is captured, in whatever mode, calls of other threads on the
-// legacy stream fail.  (Replays of captured graphs are a little faster: a time
-// step of a shell of 14,909 hexahedra 1,211 us, 1,227 us here; 32x32 Q1 cells no
-// difference beyond the spread.)
+// legacy stream fail.
 struct GraphRecorder {
     hipGraph_t graph = nullptr;
     hipGraphNode_t last = nullptr;

@@ -825,6 +825,16 @@ static hipGraphExec_t record_graph(F&& work) {
     t_recorder = nullptr;
     hipGraphExec_t x = nullptr;
     HIPCHK(hipGraphInstantiate(&x, rec.graph, nullptr, nullptr, 0));
+    // uploaded here and not by the first solve, on a stream that waits for no other
+    hipStream_t st = nullptr;
+    hipError_t e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipGraphUpload(x, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (st) (void)hipStreamDestroy(st);
+    if (e != hipSuccess) {
+        (void)hipGraphExecDestroy(x);
+        fail(DGMG_EHIP, std::string("uploading the PCG's graph: ") + hipGetErrorString(e));
+    }
     return x;
 }
 // Graphs of first_direction and next_direction (set-up).  Launched one by one,
